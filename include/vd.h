@@ -72,14 +72,9 @@ extern "C" {
                               with VD_FLAG_GRAPH, device clock stamps captured
                               in the frame time the finest level's CG
                               iterations (class VD_PROF_CG_A) of every
-                              replay, unless that level runs its CG solves
-                              as persistent launches (then nothing is
-                              stamped) */
-#define VD_FLAG_PERSIST 8u /* on levels of at most 128 tiles, run each CG
-                              solve as one persistent launch with a grid
-                              barrier between iterations (default: on levels
-                              of at most 16 tiles; one launch per CG
-                              iteration on larger ones) */
+                              replay */
+#define VD_FLAG_PERSIST 8u /* accepted for earlier programs: one-launch CG
+                              solves are the default wherever they fit */
 #define VD_FLAG_ACTIVE_SET 16u /* optimise only the set M of Sec. 6-7: on each
                                   level the corners of the cells holding
                                   samples (the isosurface's points) plus their
@@ -91,16 +86,16 @@ extern "C" {
                                   from the previous build's: points that join
                                   it are initialised by extrapolating the
                                   field (Sec. 8; see vd_get_active) */
-#define VD_FLAG_ITERATIVE 32u /* one launch per CG iteration on every level
-                                 (overrides VD_FLAG_PERSIST and the default
-                                 persistent launch of levels of at most 16
-                                 tiles; the iterates are the same).  A
-                                 persistent launch needs all its workgroups
-                                 resident at once; if concurrent work on the
-                                 GPU prevents that, its barrier's bounded
-                                 wait gives up and the report carries
-                                 VD_REPORT_BARRIER_TIMEOUT: use this flag
-                                 there */
+#define VD_FLAG_ITERATIVE 32u /* one launch per CG iteration on every level.
+                                 By default a level of at most 256 tiles runs
+                                 each CG solve as one launch whose workgroups
+                                 stay resident and exchange halos (the
+                                 iterates are the same).  If concurrent work
+                                 keeps them from becoming resident together,
+                                 those that are finish the solve from a ticket
+                                 counter, slower and with the same results;
+                                 VD_REPORT_BARRIER_TIMEOUT reports a wait that
+                                 gave up nevertheless */
 
 /* ---- kernel classes timed under VD_FLAG_PROFILE ------------------------ */
 #define VD_PROF_GRADIENT 0  /* gradient / CG initialisation pass */
@@ -119,10 +114,9 @@ extern "C" {
                                      the previous rotation */
 #define VD_REPORT_WARM_REJECTED 8u /* the predicted initialisation had the
                                       higher energy and was dropped */
-#define VD_REPORT_BARRIER_TIMEOUT 16u /* a persistent CG loop's grid barrier
-                                         gave up waiting: the frame's result
-                                         is unreliable (rerun it without
-                                         VD_FLAG_PERSIST) */
+#define VD_REPORT_BARRIER_TIMEOUT 16u /* a wait of a one-launch CG solve gave
+                                         up: the frame's result is unreliable
+                                         (rerun it with VD_FLAG_ITERATIVE) */
 
 #define VD_MAX_LEVELS 4
 #define VD_TILE_KINDS 8
@@ -399,6 +393,11 @@ int vd_debug_sort_pairs(const uint32_t* keys, const int32_t* vals, uint32_t* key
  * in[0 .. i).  Synchronous, on `stream`. */
 int vd_debug_exclusive_scan(const int32_t* in, int32_t* out, int64_t n, int32_t mem,
                             void* stream);
+
+/* on != 0: later one-launch CG solves of the handle behave as if their
+ * workgroups could not all become resident together: they are abandoned at
+ * their first exchange and finished from the ticket counter.  Same results. */
+int vd_debug_abandon_loops(vd_lattice* l, int32_t on);
 
 /* Prolongation of a coarse per-node field (level-1) to `level`: out[3N_fine]
  * = trilinear evaluation of coarse[3N_coarse] at the fine rest positions.

@@ -46,6 +46,7 @@ EXPORTED = (
     "vd_get_energy", "vd_get_state", "vd_set_state", "vd_level_info", "vd_strerror",
     "vd_debug_apply", "vd_debug_gradient", "vd_debug_energy", "vd_debug_diag",
     "vd_debug_rotations", "vd_debug_fit_rotations", "vd_debug_prolong", "vd_tune",
+    "vd_debug_abandon_loops",
     "vd_batch_create", "vd_batch_solve", "vd_batch_destroy", "vd_batch_profile",
     "vd_get_profile", "vd_warm_features", "vd_net_param_count", "vd_net_create", "vd_net_destroy",
     "vd_net_set_params", "vd_net_get_params", "vd_net_forward", "vd_net_gradients",
@@ -225,6 +226,7 @@ def _load() -> C.CDLL:
         "vd_batch_tune": ([vp, i32, C.POINTER(C.c_int32), dp], C.c_int),
         "vd_get_state64": ([vp, vp, vp, i32], C.c_int),
         "vd_debug_prolong": ([vp, i32, vp, vp, i32], C.c_int),
+        "vd_debug_abandon_loops": ([vp, i32], C.c_int),
         "vd_tune": ([vp, i32, C.POINTER(C.c_int32), dp], C.c_int),
         "vd_batch_create": ([C.POINTER(vp), i32, C.POINTER(vp)], C.c_int),
         "vd_batch_solve": ([vp, C.POINTER(SolveOpts), dp], C.c_int),
@@ -664,6 +666,9 @@ class Lattice:
         _check(_lib.vd_debug_rotations(self._h, level, pos.ctypes.data, rot_prev.ctypes.data,
                                        out.ctypes.data, VD_MEM_HOST), "vd_debug_rotations")
         return out
+
+    def debug_abandon_loops(self, on: bool = True) -> None:
+        _check(_lib.vd_debug_abandon_loops(self._h, int(on)), "vd_debug_abandon_loops")
 
     def debug_prolong(self, level: int, coarse) -> np.ndarray:
         n = self.n_nodes(level)

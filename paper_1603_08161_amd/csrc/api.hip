@@ -155,6 +155,7 @@ struct LevelData {
   T* A27r = nullptr;         // [N][kA27Row] 27-point data blocks of A, per node slot
   Scalars* sc = nullptr;
   double* scg[2] = {nullptr, nullptr};  // CG block partials [4][max_tiles], alternating
+  double* gang = nullptr;               // head and slots of one-launch CG solves
   double* pe = nullptr;                 // energy block partials [3][energy blocks]
   int cap_pe = 0;                       // doubles in pe
   // constraint rows and cell cache
@@ -174,7 +175,7 @@ struct LevelData {
     v.h = (T)h; v.wr = (T)wr;
     v.d = d; v.r = r; v.r2 = r2; v.pa = pa; v.pb = pb; v.ap = ap; v.ap2 = ap2;
     v.dinv = dinv; v.bnode = bnode; v.base = base; v.rot = rot;
-    v.scg0 = scg[0]; v.scg1 = scg[1]; v.pe = pe;
+    v.scg0 = scg[0]; v.scg1 = scg[1]; v.gang = gang; v.pe = pe;
     v.cell_map = cell_map; v.K = K; v.node_slot = node_slot; v.A27r = A27r;
     v.act = act;
     v.row_cell = row_cell; v.row_f = row_f; v.row_sn = row_sn; v.row_rho = row_rho;
@@ -246,6 +247,7 @@ class ISolver {
   virtual int tune(int iters, int* tile_out, double* us_out) = 0;
   virtual int warm_features(const float* prev2, uint16_t* x, int mem) = 0;
   virtual int profile(double* us, int* n) = 0;
+  virtual int abandon_loops(int on) = 0;
   virtual int set_depth_frame(const vd_depth_frame* f) = 0;
   virtual int get_pose(double* pose) = 0;
   virtual int set_pose(const double* pose) = 0;
@@ -323,8 +325,11 @@ class Solver final : public ISolver {
       }
       VD_CHECK(pool_.alloc(&v.scg[0], 4 * (size_t)v.max_tiles));
       VD_CHECK(pool_.alloc(&v.scg[1], 4 * (size_t)v.max_tiles));
+      VD_CHECK(pool_.alloc(&v.gang, kGangHead + 12 * (size_t)v.max_tiles));
       VD_CHECK(ensure_partials(v, 0));
     }
+    for (int k = 0; k < kTileKinds; ++k)
+      VD_TRY(cg_loop_capacity<T>(k, (desc_.flags & VD_FLAG_ACTIVE_SET) != 0, &loop_cap_[k]));
     if ((desc_.flags & VD_FLAG_PROFILE) && (desc_.flags & VD_FLAG_GRAPH))
       VD_CHECK(pool_.alloc(&stamps_, 2 * kMaxStamped));  // written by captured CG launches
     VD_CHECK(pool_.alloc(&node_flags_, (size_t)finest().N));
@@ -1101,6 +1106,12 @@ class Solver final : public ISolver {
     return download_aos(out, 3 * f.N, mem);
   }
 
+  int abandon_loops(int on) override {
+    loop_ticks_ = on ? -1 : kAssembleTicks;
+    ++alloc_gen_;  // captured schedules hold the old limit
+    return VD_OK;
+  }
+
   // Tile autotuner: times the CG iteration kernel with every tile kind.
   int tune(int iters, int* tile_out, double* us_out) override {
     if (!have_constraints_) return VD_ESTATE;
@@ -1200,8 +1211,17 @@ class Solver final : public ISolver {
           return launch_stencil<T>(kModeRhs, tiles_of(V), nullptr, nullptr, s);
         }));
         if (loop && pcg > 0) {
+          // captured frame: the loop itself stamps the start of iteration 1
+          // and of its last step
+          unsigned long long* stamp = nullptr;
+          if (graph_prof && l == L_ - 1 && pcg > 1) {
+            if (!stamps_) return VD_ESTATE;  // allocated at creation with both flags
+            stamp = stamps_ + 2 * n_stamped_;
+            if (n_stamped_ < kMaxStamped - 1) ++n_stamped_;
+            stamped_launches_ = pcg - 1;
+          }
           VD_CHECK(timed(on, VD_PROF_CG_LOOP, s,
-                         [&] { return launch_cg_loop<T>(pcg, tiles_of(V), s); }));
+                         [&] { return launch_cg_loop<T>(pcg, tiles_of(V), s, stamp, loop_ticks_); }));
         } else if (graph_prof && l == L_ - 1 && pcg > 1) {
           // captured frame: the device clock at the start of CG iteration 1
           // and of the final step (first workgroup of each), written on
@@ -1211,7 +1231,7 @@ class Solver final : public ISolver {
           const int a = 2 * n_stamped_;
           for (int m = 1; m < pcg; ++m)
             VD_TRY(launch_cg<T>(m, tiles_of(V), s, m == 1 ? stamps_ + a : nullptr));
-          if (n_stamped_ < kMaxStamped) ++n_stamped_;
+          if (n_stamped_ < kMaxStamped - 1) ++n_stamped_;
           stamped_launches_ = pcg - 1;
           VD_TRY(launch_cg_final<T>(pcg - 1, nodes_of(V), s, stamps_ + a + 1));
         } else {
@@ -1232,19 +1252,11 @@ class Solver final : public ISolver {
     return VD_OK;
   }
 
-  // Levels of at most this many tiles run each CG solve as one persistent
-  // launch by default (fewer launches; measured faster at 16^3, slower at
-  // 32^3 with 128 tiles).
-  static constexpr int kLoopDefaultMaxTiles = 16;
-
-  // Whether a level's CG solve runs as one persistent launch: with
-  // VD_FLAG_ITERATIVE never (one launch per CG iteration); with
-  // VD_FLAG_PERSIST on levels of at most kPersistMaxTiles tiles; by default on
-  // levels of at most kLoopDefaultMaxTiles tiles.
+  // Whether a level's CG solve runs as one launch: wherever all its tiles fit
+  // on the GPU together, unless VD_FLAG_ITERATIVE asks for one launch per
+  // iteration.
   bool cg_loop(const LevelData<T>& v) const {
-    if (desc_.flags & VD_FLAG_ITERATIVE) return false;
-    if (desc_.flags & VD_FLAG_PERSIST) return v.ntiles <= kPersistMaxTiles;
-    return v.ntiles <= kLoopDefaultMaxTiles;
+    return !(desc_.flags & VD_FLAG_ITERATIVE) && v.ntiles <= loop_cap_[v.tile];
   }
 
   template <typename F>
@@ -1621,6 +1633,8 @@ class Solver final : public ISolver {
   bool have_constraints_ = false;
   bool energy_fresh_ = false;
   EventTimer timer_;  // timing of the last profiled frame
+  int loop_ticks_ = kAssembleTicks;
+  int loop_cap_[kTileKinds] = {};  // most tiles of a one-launch CG solve, by tile kind
   // test scratch
   float* dbg_f_ = nullptr;
   T *dbg_t1_ = nullptr, *dbg_t2_ = nullptr, *dbg_rot_ = nullptr;
@@ -2250,6 +2264,11 @@ int vd_debug_rotations(vd_lattice* l, int32_t level, const float* pos, const flo
                        float* rot_out, int32_t mem) {
   if (!l) return VD_EINVAL;
   return l->impl->debug_rotations(level, pos, rot_prev, rot_out, mem);
+}
+
+int vd_debug_abandon_loops(vd_lattice* l, int32_t on) {
+  if (!l) return VD_EINVAL;
+  return l->impl->abandon_loops(on);
 }
 
 int vd_debug_prolong(vd_lattice* l, int32_t level, const float* coarse, float* out, int32_t mem) {

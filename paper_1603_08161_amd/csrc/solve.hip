@@ -7,6 +7,8 @@
 // Unknowns are displacements d = t - t_hat; node vectors are SoA [3][N] in
 // x-fastest order (rotations [9][N]).
 
+#include <algorithm>
+
 #include "vd_device.h"
 #include "vd_kernels.h"
 
@@ -121,7 +123,25 @@ int tile_blocks(int kind, int nx, int ny, int nz) {
   }
 }
 
-int default_tile(int nx, int ny, int nz) { return tile_blocks(1, nx, ny, nz) >= 512 ? 1 : 0; }
+// The tile of a level unless the caller or the tuner chooses one: the kind with
+// the most workgroups whose tiles fit a one-launch CG solve, as smaller tiles
+// spread the data rows over more compute units (us per iteration with the
+// gradient pass: 32^3 in 128 tiles of 8x8x4 4.7, in 64 of 16x4x8 4.9, in 32 of
+// 32x8x4 8.7; 48^3 in 216 of 16x4x8 6.7, in 108 of 32x8x4 8.1); among the
+// 1024-node kinds the one that pads least.  Larger levels run one launch per
+// iteration, fastest with 128-byte rows (96^3: 37.7 with 32x8x4 on 256
+// threads, 42.6 with 8x8x8).
+int default_tile(int nx, int ny, int nz) {
+  const int order[] = {7, 6, 3, 5, 4};
+  int best = -1;
+  for (const int k : order) {
+    const int n = tile_blocks(k, nx, ny, nz);
+    if (n > kGangMaxTiles) continue;
+    if (k == 7 || k == 6) return k;
+    if (best < 0 || n < tile_blocks(best, nx, ny, nz)) best = k;
+  }
+  return best >= 0 ? best : nx >= 24 ? 2 : 1;
+}
 int node_blocks(int N) { return blocks_for(N); }
 int energy_blocks(int rblocks, int N) { return rblocks + blocks_for(N); }
 
@@ -328,6 +348,27 @@ __device__ __forceinline__ void eval_data_nodes(const LevelView<T>& L,
   }
 }
 
+// Exchange slots of a one-launch CG solve (k_cg_loop): [3 sets][4 sums][tiles]
+// after the head of LevelView::gang.
+
+__device__ __forceinline__ unsigned long long* gang_slots(const double* gang) {
+  return (unsigned long long*)(gang + kGangHead);
+}
+
+// A slot that holds no sum yet.  A NaN sum is published as the canonical NaN,
+// so no sum looks empty.
+constexpr unsigned long long kEmptySlot = ~0ull;
+
+// The gradient pass before a solve empties the tile's slots (a tile without
+// unknowns: its sums, zero, for every iterate) and resets the head.
+__device__ __forceinline__ void gang_prepare(double* gang, int tiles, int local, bool empty) {
+  if (threadIdx.x < 12) {
+    const int set = threadIdx.x / 4, k = threadIdx.x % 4;
+    gang_slots(gang)[((size_t)set * 4 + k) * tiles + local] = empty ? 0ull : kEmptySlot;
+  }
+  if (local == 0 && threadIdx.x < kGangHead) ((unsigned long long*)gang)[threadIdx.x] = 0ull;
+}
+
 // kModeRhs : p = d; g = A d - b + w_r sum_j (2I - R_i - R_j) e_ij is the
 //            gradient J^T r; r = -g is stored (the CG residual r_0).
 // kModeApply / kModeGrad : A p or g written to `out` (test entry points).
@@ -343,8 +384,6 @@ __global__ __launch_bounds__(TL::NT) void k_stencil(Dispatch<T> D, const T* __re
   const TilePos<TL> t(L.nx, L.ny, w.local);
   const size_t N = L.N;
   const gptr<const T> __restrict__ src = glob<const T>((MODE == kModeRhs) ? L.d : pin);
-  // the CG solve that follows a gradient pass counts its grid barrier from 0
-  if (MODE == kModeRhs && w.local == 0 && threadIdx.x == 0) L.sc->bar = 0u;
   // MASK: the optimised set M (a lattice of the launch may still have none)
   const gptr<const unsigned char> __restrict__ act =
       MASK ? glob<const unsigned char>(L.act) : nullptr;
@@ -360,8 +399,12 @@ __global__ __launch_bounds__(TL::NT) void k_stencil(Dispatch<T> D, const T* __re
       if ((TilePos<TL>::owner() && in_box(gx, gy, gz, L.nx, L.ny, L.nz)))
         any |= act[gx + (size_t)L.nx * (gy + (size_t)L.ny * gz)];
     }
-    if (!__syncthreads_or(any)) return;
+    if (!__syncthreads_or(any)) {
+      gang_prepare(L.gang, L.ntiles, w.local, w.local != 0);
+      return;
+    }
   }
+  if (MODE == kModeRhs) gang_prepare(L.gang, L.ntiles, w.local, false);
   // own nodes' data-block slots (loaded with the tile)
   int own_slot[TL::NPT];
 #pragma unroll
@@ -540,11 +583,10 @@ struct Step {
   __device__ __forceinline__ T axpy(T x, T y) const { return fma(lo, y, fma(hi, y, x)); }
 };
 
-template <typename T, int NT = kBlock>
-__device__ __forceinline__ void cg_scalars(const double* s, int n, Step<T>& alpha, Step<T>& beta,
-                                           Scalars* sc, bool count_guard) {
-  double v[4];
-  sum_partials_k<4, NT>(s, n, v);
+// alpha and beta from the sums v of the previous iterate.
+template <typename T>
+__device__ __forceinline__ void cg_steps(const double (&v)[4], Step<T>& alpha, Step<T>& beta,
+                                         Scalars* sc, bool count_guard) {
   const double rz = v[0], pap = v[1], apdr = v[2], apdap = v[3];
   const double a = pap > 0.0 ? rz / pap : 0.0;
   double rz_new = rz - 2.0 * a * apdr + a * a * apdap;
@@ -554,8 +596,16 @@ __device__ __forceinline__ void cg_scalars(const double* s, int n, Step<T>& alph
   if (count_guard && threadIdx.x == 0 && !(pap > 0.0)) sc->guard_hits += 1;
 }
 
-// One CG iteration m on the tile of workgroup w (body of k_cg and of the
-// persistent k_cg_loop).  The own nodes' data-block slot, preconditioner,
+template <typename T, int NT = kBlock>
+__device__ __forceinline__ void cg_scalars(const double* s, int n, Step<T>& alpha, Step<T>& beta,
+                                           Scalars* sc, bool count_guard) {
+  double v[4];
+  sum_partials_k<4, NT>(s, n, v);
+  cg_steps<T>(v, alpha, beta, sc, count_guard);
+}
+
+// One CG iteration m on the tile of workgroup w (body of k_cg and of abandoned
+// one-launch solves).  The own nodes' data-block slot, preconditioner,
 // displacement and previous direction are loaded together with the halo,
 // before the CG scalars, so that every workgroup pays one memory round trip
 // before it stages the tile (a form that loaded them at their use, for more
@@ -756,73 +806,669 @@ __global__ __launch_bounds__(TL::NT) void k_cg(Dispatch<T> D, int m, unsigned lo
   cg_body<T, TL, FIRST, MASK>(w, m, sp, sr, sm, ds);
 }
 
-// Grid barrier of a launch whose workgroups are all resident: every
-// workgroup publishes its writes (agent-scope release), counts itself in,
-// waits for `target` arrivals and then acquires.  The wait is bounded: after
-// kSpinLimit polls it gives up and counts a timeout, so the kernel always
-// ends (the result of such a frame is then reported as unreliable).
-constexpr unsigned kSpinLimit = 1u << 18;
+// ---------------------------------------------------------------------------
+// a whole CG solve in one launch
+// ---------------------------------------------------------------------------
+//
+// One workgroup per tile for all iterations.  A workgroup keeps r, D^-1, d and
+// A p of its own nodes, r and D^-1 of its halo nodes and (as far as one round
+// of items covers them) the rows of its data nodes in registers and p in LDS,
+// and applies the scalar updates to its halo itself, so per iteration it
+// exchanges only A p of the tile's surface nodes and the four block partials.
+// The per-iteration launches stream every vector instead (36 MB at 64^3).
+//
+// Exchange without a cache flush: A p and the partials are stored and loaded
+// at agent scope (past the caches that are private to a die), A p in one of
+// two alternating buffers, the partials in slots that are empty until they
+// are written.  A workgroup stores its surface A p, waits for those stores,
+// then stores its partials; a reader that finds all partials of iterate m
+// therefore finds A p_m too.  (Marks in A p itself instead of that order cost
+// more than the wait, which the wave sums cover: 6.2 against 5.2 us per
+// iteration at 16^3.)  Iterate m uses slot set m % 3; during iterate m a
+// workgroup empties its slots of set (m + 1) % 3, which every workgroup has
+// read by then: it has seen every partial of m - 1, each stored after its
+// writer had read all of m - 2.
+//
+// Such a solve needs all tiles resident together, which concurrent work can
+// prevent.  The first exchange decides: workgroup 0 of the lattice declares
+// the solve running once it has seen every workgroup's first partials, and
+// any workgroup that has waited `ticks` of the clock declares it abandoned (one
+// compare-and-swap word, so all agree).  Once it runs every workgroup stays
+// resident until its end, so no later wait can starve.  An abandoned solve
+// has changed nothing but scratch: its workgroups, and those that start later,
+// finish it from a ticket counter, one (iterate, tile) per ticket in order.
+// The holder of a ticket waits only for tickets handed out before its own, so
+// this makes progress with any number of resident workgroups.
+//
+// What bounds an iteration is the instructions of the 16 waves of a compute
+// unit and the exchange's latency, so one wave alone forms the scalars, the
+// four sums share their wave reductions (wave_sum4), and the stencil has no
+// branches in waves away from the lattice's border.  The arithmetic and the
+// order of every sum are those of k_cg, so the results are the same bits.
 
-__device__ __forceinline__ void grid_barrier(unsigned* bar, unsigned target, int* timeouts) {
+constexpr unsigned kSpinLimit = 1u << 18;         // polls before a wait gives up
+
+enum GangState : unsigned { kGangForming = 0, kGangRunning = 1, kGangAbandoned = 2 };
+
+template <typename U>
+__device__ __forceinline__ U load_agent(const U* p) {
+  return __hip_atomic_load(glob<U>(const_cast<U*>(p)), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename U>
+__device__ __forceinline__ void store_agent(U* p, U v) {
+  __hip_atomic_store(glob<U>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// All vector-memory operations of the calling wave are complete.
+__device__ __forceinline__ void wait_stores() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+__device__ __forceinline__ unsigned long long slot_bits(double v) {
+  return v != v ? 0x7ff8000000000000ull : (unsigned long long)__double_as_longlong(v);
+}
+
+__device__ __forceinline__ double pack_double(unsigned lo, unsigned hi) {
+  return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
+
+// Wave sums of four values at once, the sum of v[k] left in the lanes with
+// lane % 4 == k.  The pairs added are those of wave_sum (every lane of a
+// group holds the same partial sum there), so the sums have the same bits;
+// sharing the lanes takes 7 additions instead of 28.
+__device__ __forceinline__ double wave_sum4(const double (&v)[4]) {
+  const bool o1 = threadIdx.x & 1, o2 = threadIdx.x & 2;
+  double a = o1 ? v[1] : v[0], b = o1 ? v[3] : v[2];
+  a += dpp_move<0xB1>(o1 ? v[0] : v[1]);  // lane ^ 1
+  b += dpp_move<0xB1>(o1 ? v[2] : v[3]);
+  double s = o2 ? b : a;
+  s += dpp_move<0x4E>(o2 ? a : b);                     // lane ^ 2
+  s += dpp_move<0x1B>(dpp_move<0x141>(s));             // lane ^ 4
+  s += dpp_move<0x128>(s);                             // lane ^ 8
+  // rows of 16 lanes: (row 0 + row 1) + (row 2 + row 3); the swaps leave the
+  // lower row (half) of each pair in the first result, the upper in the second
+  const long long e = __double_as_longlong(s);
+  const auto l16 = __builtin_amdgcn_permlane16_swap((unsigned)e, (unsigned)e, false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap((unsigned)(e >> 32), (unsigned)(e >> 32),
+                                                    false, false);
+  s = pack_double(l16[0], h16[0]) + pack_double(l16[1], h16[1]);
+  const long long c = __double_as_longlong(s);
+  const auto l32 = __builtin_amdgcn_permlane32_swap((unsigned)c, (unsigned)c, false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap((unsigned)(c >> 32), (unsigned)(c >> 32),
+                                                    false, false);
+  return pack_double(l32[0], h32[0]) + pack_double(l32[1], h32[1]);
+}
+
+// The n-th node of a tile's halo shell: the two z faces, then the rings of
+// the layers between them.
+template <typename TL>
+__device__ __forceinline__ void shell_node(int n, int& lx, int& ly, int& lz) {
+  constexpr int FACE = TL::HX * TL::HY, RING = 2 * TL::HX + 2 * TL::TY;
+  if (n < 2 * FACE) {
+    lz = n < FACE ? 0 : TL::HZ - 1;
+    const int q = n < FACE ? n : n - FACE;
+    lx = q % TL::HX;
+    ly = q / TL::HX;
+    return;
+  }
+  const int r = n - 2 * FACE;
+  lz = 1 + r / RING;
+  const int q = r % RING;
+  if (q < 2 * TL::HX) {
+    ly = q < TL::HX ? 0 : TL::HY - 1;
+    lx = q % TL::HX;
+  } else {
+    ly = 1 + (q - 2 * TL::HX) / 2;
+    lx = (q & 1) ? TL::HX - 1 : 0;
+  }
+}
+
+// Waves 0 .. 3 wait for the partials of an iterate (slots s[4][n], n <= 256)
+// and leave in sums[k][g] the sum of quantity k over the tiles 64 g .. 64 g +
+// 63, as wave g of sum_partials_k forms it.  `limit` bounds the polls; a wait
+// that gives up counts a timeout and leaves one poll to later ones.
+__device__ __forceinline__ void gang_poll(const unsigned long long* s, int n, double* sums,
+                                          unsigned& limit, int* timeouts) {
+  const int b = threadIdx.x, lane = threadIdx.x & (kWave - 1);
+  unsigned long long u[4];
+  for (unsigned spins = 0;;) {
+    bool all = true;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) u[k] = b < n ? load_agent(s + k * n + b) : 0ull;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) all &= u[k] != kEmptySlot;
+    if (all) break;
+    if (++spins > limit) {
+      atomicAdd(timeouts, 1);
+      limit = 1;
+      break;
+    }
+  }
+  double v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = __longlong_as_double((long long)u[k]);
+  const double x = wave_sum4(v);
+  if (lane < 4) sums[lane * 4 + threadIdx.x / kWave] = x;
+}
+
+// Whether the solve runs as a gang (see above), decided at its first
+// exchange; the same answer in every workgroup of the lattice.
+__device__ __forceinline__ bool gang_assembled(double* gang, const unsigned long long* s, int n,
+                                               bool first_tile, int ticks) {
+  __shared__ unsigned state;
+  unsigned* word = (unsigned*)gang;
+  const long long t0 = wall_clock64();
+  if (first_tile) {
+    int late = ticks < 0 ? 1 : 0;
+    if (threadIdx.x < kWave)
+      for (int b = threadIdx.x; b < n && !late; b += kWave)
+        while (load_agent(s + 3 * n + b) == kEmptySlot)
+          if (wall_clock64() - t0 > ticks) {
+            late = 1;
+            break;
+          }
+    late = __syncthreads_or(late);
+    if (threadIdx.x == 0) {
+      const unsigned want = late ? kGangAbandoned : kGangRunning;
+      const unsigned old = atomicCAS(word, (unsigned)kGangForming, want);
+      state = old == kGangForming ? want : old;
+    }
+  } else if (threadIdx.x == 0) {
+    unsigned v;
+    while ((v = load_agent(word)) == kGangForming) {
+      __builtin_amdgcn_s_sleep(1);
+      if (wall_clock64() - t0 > ticks) {
+        v = atomicCAS(word, (unsigned)kGangForming, (unsigned)kGangAbandoned);
+        if (v == kGangForming) v = kGangAbandoned;
+        break;
+      }
+    }
+    state = v;
+  }
+  __syncthreads();
+  return state == kGangRunning;
+}
+
+// Tickets of an abandoned solve (solo workgroups): the next (iterate, tile) in
+// order, or -1 when all are handed out.  Waits until every ticket of the
+// earlier iterates is done, then drops stale cache lines.
+__device__ __forceinline__ long long take_ticket(double* gang, long long n, long long iters,
+                                                 unsigned& limit, int* timeouts) {
+  __shared__ long long ticket;
+  unsigned long long* next = (unsigned long long*)gang + 1;
+  unsigned long long* done = (unsigned long long*)gang + 2;
   __syncthreads();
   if (threadIdx.x == 0) {
-    __threadfence();
-    atomicAdd(bar, 1u);
-    unsigned spins = 0;
-    while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      __builtin_amdgcn_s_sleep(1);
-      if (++spins > kSpinLimit) {
+    const long long k = (long long)atomicAdd(next, 1ull);
+    const bool valid = k < n * (iters + 1);
+    for (unsigned spins = 0; valid && (long long)load_agent(done) < k / n * n;) {
+      __builtin_amdgcn_s_sleep(4);
+      if (++spins > limit) {
         atomicAdd(timeouts, 1);
+        limit = 1;
         break;
       }
     }
     __threadfence();
+    ticket = valid ? k : -1;
   }
   __syncthreads();
+  return ticket;
 }
 
-// The last step d += alpha p of CG iterate `last` on the tile's own nodes.
-template <typename T, typename TL>
-__device__ __forceinline__ void cg_final_tile(const Where<T>& w, int last) {
-  const LevelView<T>& L = w.L;
-  const TilePos<TL> t(L.nx, L.ny, w.local);
-  const bool odd = (last & 1) != 0;
-  Step<T> alpha, beta;
-  cg_scalars<T, TL::NT>(odd ? L.scg1 : L.scg0, L.ntiles, alpha, beta, L.sc, w.local == 0);
-  const size_t N = L.N;
-  const gptr<const T> __restrict__ p = glob<const T>(odd ? L.pb : L.pa);
-  const gptr<T> __restrict__ d = glob<T>(L.d);
-#pragma unroll
-  for (int kk = 0; kk < TL::NPT; ++kk) {
-    const int c = TilePos<TL>::own(kk);
-    const int lx = c % TL::HX, ly = (c / TL::HX) % TL::HY, lz = c / (TL::HX * TL::HY);
-    const int gx = t.x0 + lx, gy = t.y0 + ly, gz = t.z0 + lz;
-    if (!(TilePos<TL>::owner() && in_box(gx, gy, gz, L.nx, L.ny, L.nz))) continue;
-    const size_t i = gx + (size_t)L.nx * (gy + (size_t)L.ny * gz);
-    if (L.act && !L.act[i]) continue;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) d[a * N + i] = alpha.axpy(d[a * N + i], p[a * N + i]);
+// The calling workgroup's ticket is done: its stores first.
+__device__ __forceinline__ void finish_ticket(double* gang) {
+  wait_stores();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();
+    atomicAdd((unsigned long long*)gang + 2, 1ull);
   }
 }
 
-// All iterations of one CG solve (single lattice, every tile resident).
-template <typename T, typename TL, bool MASK>
-__global__ __launch_bounds__(TL::NT) void k_cg_loop(Dispatch<T> D, int iters) {
+// The tile of workgroup g: lattices in dispatch order (so that a launch over
+// several fills up lattice by lattice), and within a lattice a contiguous
+// range of tiles per die.
+template <typename T>
+__device__ __forceinline__ Where<T> locate_gang(const Dispatch<T>& D) {
+  Where<T> w = locate(D, blockIdx.x);
+  const int first = blockIdx.x - w.local;   // the lattice's first workgroup
+  const int die = blockIdx.x % kXcds;
+  int before = 0;                           // tiles of the lower-numbered dies
+  for (int x = 0; x < die; ++x) {
+    const int lead = (x - first % kXcds + kXcds) % kXcds;  // first workgroup on die x
+    if (lead < w.count) before += (w.count - lead - 1) / kXcds + 1;
+  }
+  w.local = before + w.local / kXcds;
+  return w;
+}
+
+// One-launch solve of a tile on PT threads.  With fewer threads than owners a
+// thread stands for VT owning threads of the per-iteration kernel, PT apart,
+// and keeps their sums apart too.
+template <typename T, typename TL_, int PT_>
+struct Loop {
+  using TL = TL_;
+  static constexpr int PT = PT_, PW = PT / kWave;
+  static constexpr int VT = TL::OWNERS > PT ? TL::OWNERS / PT : 1;
+  static constexpr int NV = VT * TL::NPT;                   // own nodes per thread
+  static constexpr int OW = (TL::OWNERS + kWave - 1) / kWave;  // owning waves
+  static constexpr int SEG = kWave * TL::NPT;               // list entries per owning wave
+  static constexpr int ENT = OW * SEG;
+  static constexpr int SHELL = TL::HALO - TL::TX * TL::TY * TL::TZ;
+  static constexpr int SPT = (SHELL + PT - 1) / PT;         // halo nodes per thread
+  static constexpr int ROUND = PW * kNodesPerWave;          // data nodes per round
+  // rounds of items whose rows stay in registers (54 values per lane each)
+  static constexpr int KEEP = sizeof(T) == 8 ? (NV > 1 || SPT > 2 ? 0 : 1)
+                                             : (NV > 1 ? 1 : 2);
+  // data nodes of the tile by owning wave, and the three parts of their sums
+  struct Share {
+    int slot[ENT], node[ENT], cnt[OW];
+    T d[3][3][ENT];  // [part][component][entry]
+  };
+  __device__ __forceinline__ static int owner(int j) {  // the owning thread of own node j
+    return (int)threadIdx.x + (j / TL::NPT) * PT;
+  }
+  __device__ __forceinline__ static bool owns(int j) {
+    return TL::OWNERS % PT == 0 || owner(j) < TL::OWNERS;
+  }
+  __device__ __forceinline__ static int own(int j) {  // LDS index of own node j
+    const int t = owns(j) ? owner(j) : 0;
+    const int lx = t % TL::TX + 1, ly = (t / TL::TX) % TL::TY + 1;
+    const int lz = (t / (TL::TX * TL::TY)) * TL::NPT + j % TL::NPT + 1;
+    return lx + TL::HX * (ly + TL::HY * lz);
+  }
+};
+
+// Entry of list position v, or -1 past the end.
+template <typename LP>
+__device__ __forceinline__ int list_entry(const typename LP::Share& ls, int v) {
+  int at = 0, e = -1;
+  for (int u = 0; u < LP::OW; ++u) {
+    const int c = ls.cnt[u];
+    if (v >= at && v < at + c) e = u * LP::SEG + (v - at);
+    at += c;
+  }
+  return e;
+}
+
+// One (node, part) item: the part's nine blocks times p.
+template <typename T, int HX, int LEN, typename R>
+__device__ __forceinline__ void part_product(const T (&sp)[3][LEN], int cz, R&& row, T (&o)[3]) {
+  o[0] = o[1] = o[2] = T(0);
+#pragma unroll
+  for (int j = 0; j < 9; ++j) {
+    const int q = cz + (j % 3 - 1) + HX * (j / 3 - 1);
+    const T s0 = row(6 * j), s1 = row(6 * j + 1), s2 = row(6 * j + 2), s3 = row(6 * j + 3),
+            s4 = row(6 * j + 4), s5 = row(6 * j + 5);
+    const T q0 = sp[0][q], q1 = sp[1][q], q2 = sp[2][q];
+    o[0] += s0 * q0 + s1 * q1 + s2 * q2;
+    o[1] += s1 * q0 + s3 * q1 + s4 * q2;
+    o[2] += s2 * q0 + s4 * q1 + s5 * q2;
+  }
+}
+
+// All iterations of one CG solve and its last step.  stamp (may be null):
+// two clock stamps, at the start of iteration 1 and of the last step.
+template <typename T, typename LP, bool MASK>
+__global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
+                                                    unsigned long long* stamp, int ticks) {
   if (skipped(D)) return;
-  __shared__ T sp[3][TL::HALO];
-  __shared__ T sr[3][TL::HALO];
+  using TL = typename LP::TL;
+  constexpr int NV = LP::NV, SPT = LP::SPT;
+  constexpr int CW = 16 / (int)sizeof(T);  // entries per 16-byte chunk of a row
+  __shared__ T sp[3][TL::HALO + 1];  // + 1: where threads past the shell write
   __shared__ unsigned char sm[TL::HALO];
-  __shared__ DataShare<T, TL> ds;
-  const Where<T> w = locate(D, xcd_remap(blockIdx.x, gridDim.x));
-  Scalars* sc = w.L.sc;
-  for (int m = 0; m < iters; ++m) {
-    if (m == 0)
-      cg_body<T, TL, true, MASK>(w, m, sp, sr, sm, ds);
-    else
-      cg_body<T, TL, false, MASK>(w, m, sp, sr, sm, ds);
-    grid_barrier(&sc->bar, (unsigned)(m + 1) * gridDim.x, &sc->bar_timeouts);
+  __shared__ typename LP::Share ls;
+  __shared__ double sums[4 * LP::OW];   // the block's partials by owning wave
+  __shared__ double gsums[16];          // the tiles' partials [4 sums][4 waves]
+  __shared__ Step<T> steps[2];
+  const Where<T> w = locate_gang(D);
+  const LevelView<T>& L = w.L;
+  const int n_tiles = L.ntiles;
+  const size_t N = L.N;
+  // (as values: a choice between two members of L would keep L in memory)
+  T* const v_r = L.r;
+  T* const v_r2 = L.r2;
+  T* const v_pa = L.pa;
+  T* const v_pb = L.pb;
+  T* const v_ap = L.ap;
+  T* const v_ap2 = L.ap2;
+  unsigned long long* const slots = gang_slots(L.gang);
+  const gptr<T> __restrict__ dvec = glob<T>(L.d);
+  const gptr<const unsigned char> __restrict__ act =
+      MASK ? glob<const unsigned char>(L.act) : nullptr;
+  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  const int part_id = lane % kPartsPerNode, item = wv * kNodesPerWave + lane / kPartsPerNode;
+  const bool has_item = lane / kPartsPerNode < kNodesPerWave;
+  T r[NV][3], q[NV][3], d[NV][3], ap[NV][3];  // own nodes
+  int node[NV];       // global index, -1: not an unknown
+  int rank[NV];       // entry of the node's data blocks in the wave's list
+  unsigned nbr[NV];   // bits 0..5: the neighbours it couples to (-x +x -y +y -z +z);
+                      // bit 6: on the tile's surface, neighbours read its A p
+  T hr[SPT][3], hq[SPT][3];  // halo nodes
+  int hnode[SPT], hc[SPT];   // global index (-1: none), LDS index
+  T keep[LP::KEEP > 0 ? LP::KEEP : 1][54];  // rows of the lane's first items,
+  // LDS centre and list entry (-1: none) of the kept items and of one more
+  // round; the slot of the latter
+  int kcz[LP::KEEP + 1], ke[LP::KEEP + 1], kslot = 0;
+  int n_data = 0;
+  Step<T> alpha = Step<T>::of(0.0), beta = Step<T>::of(0.0);
+  unsigned limit = kSpinLimit;
+  bool solo = false, load = true;
+  int tile = w.local, m = 0;
+  for (;;) {
+    if (solo) {
+      const long long k = take_ticket(L.gang, n_tiles, iters, limit, &L.sc->bar_timeouts);
+      if (k < 0) return;
+      m = (int)(k / n_tiles);
+      tile = (int)(k % n_tiles);
+      load = true;
+    }
+    const bool last = m == iters, odd = (m & 1) != 0;
+    if (load) {
+      // the tile's state: r_0 and d, or (solo) that of iterate m - 1
+      load = false;
+      const TilePos<TL> t(L.nx, L.ny, tile);
+      const gptr<const T> __restrict__ rin = glob<const T>(m == 0 || odd ? v_r : v_r2);
+      const gptr<const T> __restrict__ pin = glob<const T>(odd ? v_pa : v_pb);
+      const gptr<const T> __restrict__ apin = glob<const T>(odd ? v_ap : v_ap2);
+      const gptr<const T> __restrict__ dinv = glob<const T>(L.dinv);
+      int slot[NV];
+#pragma unroll
+      for (int kk = 0; kk < NV; ++kk) {
+        const int c = LP::own(kk);
+        const int lx = c % TL::HX, ly = (c / TL::HX) % TL::HY, lz = c / (TL::HX * TL::HY);
+        const int gx = t.x0 + lx, gy = t.y0 + ly, gz = t.z0 + lz;
+        const bool in = LP::owns(kk) && in_box(gx, gy, gz, L.nx, L.ny, L.nz);
+        const size_t i = in ? gx + (size_t)L.nx * (gy + (size_t)L.ny * gz) : 0;
+        node[kk] = in && (!act || act[i]) ? (int)i : -1;
+        // (solo: every A p is read back from memory)
+        nbr[kk] = (gx > 0) | (gx < L.nx - 1) << 1 | (gy > 0) << 2 | (gy < L.ny - 1) << 3 |
+                  (gz > 0) << 4 | (gz < L.nz - 1) << 5 |
+                  (node[kk] >= 0 && (solo || lx == 1 || lx == TL::TX || ly == 1 || ly == TL::TY ||
+                                     lz == 1 || lz == TL::TZ)) << 6;
+        slot[kk] = node[kk] >= 0 ? glob<const int>(L.node_slot)[i] : -1;
+        if (MASK && LP::owns(kk)) sm[c] = node[kk] >= 0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          r[kk][a] = node[kk] >= 0 ? rin[a * N + i] : T(0);
+          q[kk][a] = node[kk] >= 0 ? dinv[a * N + i] : T(0);
+          d[kk][a] = node[kk] >= 0 ? dvec[a * N + i] : T(0);
+          const bool past = solo && m > 0 && node[kk] >= 0;  // else A p = p = 0
+          ap[kk][a] = past ? apin[a * N + i] : T(0);
+          if (LP::owns(kk)) sp[a][c] = past ? pin[a * N + i] : T(0);
+        }
+      }
+      if (MASK && act && !solo) {
+        // a tile without unknowns: its slots hold zeros already
+        int any = 0;
+#pragma unroll
+        for (int kk = 0; kk < NV; ++kk) any |= node[kk] >= 0;
+        if (!__syncthreads_or(any) && tile != 0) return;
+      }
+#pragma unroll
+      for (int h = 0; h < SPT; ++h) {
+        const int n = threadIdx.x + h * LP::PT;
+        int lx = 0, ly = 0, lz = 0;
+        shell_node<TL>(n < LP::SHELL ? n : 0, lx, ly, lz);
+        const int gx = t.x0 + lx, gy = t.y0 + ly, gz = t.z0 + lz;
+        const bool in = n < LP::SHELL && in_box(gx, gy, gz, L.nx, L.ny, L.nz);
+        const size_t i = in ? gx + (size_t)L.nx * (gy + (size_t)L.ny * gz) : 0;
+        hc[h] = n < LP::SHELL ? lx + TL::HX * (ly + TL::HY * lz) : TL::HALO;
+        hnode[h] = in && (!act || act[i]) ? (int)i : -1;
+        if (MASK && n < LP::SHELL) sm[hc[h]] = hnode[h] >= 0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          hr[h][a] = hnode[h] >= 0 ? rin[a * N + i] : T(0);
+          hq[h][a] = hnode[h] >= 0 ? dinv[a * N + i] : T(0);
+          sp[a][hc[h]] = solo && m > 0 && hnode[h] >= 0 ? pin[a * N + i] : T(0);
+        }
+      }
+      // the lists of data nodes, one per owning wave
+#pragma unroll
+      for (int vt = 0; vt < LP::VT; ++vt) {
+        const int ow = wv + vt * LP::PW;
+        if (ow >= LP::OW) continue;
+        int base = 0;
+#pragma unroll
+        for (int z = 0; z < TL::NPT; ++z) {
+          const int kk = vt * TL::NPT + z;
+          const unsigned long long has = __ballot(slot[kk] >= 0);
+          rank[kk] = -1;
+          if (slot[kk] >= 0) {
+            rank[kk] = ow * LP::SEG + base + __popcll(has & ((1ull << lane) - 1ull));
+            ls.slot[rank[kk]] = slot[kk];
+            ls.node[rank[kk]] = LP::own(kk);
+          }
+          base += __popcll(has);
+        }
+        if (lane == 0) ls.cnt[ow] = base;
+      }
+      __syncthreads();
+      if (MASK && act) {  // only the edges inside M
+        constexpr int off[3] = {1, TL::HX, TL::HX * TL::HY};
+#pragma unroll
+        for (int kk = 0; kk < NV; ++kk) {
+          const int c = LP::own(kk);
+#pragma unroll
+          for (int k = 0; k < 6; ++k)
+            if (!sm[c + ((k & 1) ? off[k / 2] : -off[k / 2])]) nbr[kk] &= ~(1u << k);
+        }
+      }
+      n_data = 0;
+      for (int u = 0; u < LP::OW; ++u) n_data += ls.cnt[u];
+#pragma unroll
+      for (int x = 0; x <= LP::KEEP; ++x) {
+        ke[x] = has_item ? list_entry<LP>(ls, x * LP::ROUND + item) : -1;
+        kcz[x] = ke[x] >= 0 ? ls.node[ke[x]] + TL::HX * TL::HY * (part_id - 1) : 0;
+        if (x == LP::KEEP) kslot = ke[x] >= 0 ? ls.slot[ke[x]] : 0;
+        if (x < LP::KEEP && ke[x] >= 0) {
+          const gptr<const T> __restrict__ A = glob<const T>(static_cast<const T*>(
+              __builtin_assume_aligned(L.A27r + (size_t)ls.slot[ke[x]] * kA27Row + part_id * CW,
+                                       16)));
+#pragma unroll
+          for (int y = 0; y < 54; ++y) keep[x][y] = A[kPartsPerNode * CW * (y / CW) + y % CW];
+        }
+      }
+    }
+    if (stamp != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {
+      if (m == 1) stamp[0] = (unsigned long long)wall_clock64();
+      if (last) stamp[1] = (unsigned long long)wall_clock64();
+    }
+    T ha[SPT][3];
+#pragma unroll
+    for (int h = 0; h < SPT; ++h) ha[h][0] = ha[h][1] = ha[h][2] = T(0);
+    if (m > 0) {
+      // 1. the scalars of iterate m - 1 (wave 0) and the halo's A p
+      const unsigned long long* s = slots + (size_t)((m - 1) % 3) * 4 * n_tiles;
+      if (m == 1 && !solo && !gang_assembled(L.gang, s, n_tiles, tile == 0, ticks)) {
+        solo = true;
+        continue;
+      }
+      if (wv < 4) gang_poll(s, n_tiles, gsums, limit, &L.sc->bar_timeouts);
+      __syncthreads();
+      const T* const ap_in = odd ? v_ap : v_ap2;
+#pragma unroll
+      for (int h = 0; h < SPT; ++h) {
+        if (hnode[h] < 0) continue;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) ha[h][a] = load_agent(ap_in + a * N + (unsigned)hnode[h]);
+      }
+      if (wv == 0) {
+        double v[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          v[x] = 0.0;
+#pragma unroll
+          for (int g = 0; g < 4; ++g) v[x] += gsums[4 * x + g];
+        }
+        Step<T> al, be;
+        cg_steps<T>(v, al, be, L.sc, tile == 0);
+        if (lane == 0) {
+          steps[0] = al;
+          steps[1] = be;
+        }
+      }
+      __syncthreads();
+      alpha = steps[0];
+      beta = steps[1];
+    }
+    // 2. r_m, p_m and the step of d (iterate 0: alpha = beta = 0, so p = D^-1 r)
+    if (wv < LP::OW) {
+#pragma unroll
+      for (int kk = 0; kk < NV; ++kk) {
+        const int c = LP::own(kk);
+        T p[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) p[a] = sp[a][c];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          d[kk][a] = alpha.axpy(d[kk][a], p[a]);
+          r[kk][a] = alpha.axpy(r[kk][a], -ap[kk][a]);
+          p[a] = beta.axpy(q[kk][a] * r[kk][a], p[a]);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) sp[a][c] = p[a];
+      }
+    }
+    if (last || solo) {
+#pragma unroll
+      for (int kk = 0; kk < NV; ++kk) {
+        if (node[kk] < 0) continue;
+        const int c = LP::own(kk);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          dvec[a * N + node[kk]] = d[kk][a];
+          if (last) continue;
+          glob<T>(odd ? v_pb : v_pa)[a * N + node[kk]] = sp[a][c];
+          if (m > 0) glob<T>(odd ? v_r2 : v_r)[a * N + node[kk]] = r[kk][a];
+        }
+      }
+      if (last) {
+        if (!solo) return;
+        finish_ticket(L.gang);
+        continue;
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < SPT; ++h) {
+      T p[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) p[a] = sp[a][hc[h]];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        hr[h][a] = alpha.axpy(hr[h][a], -ha[h][a]);
+        p[a] = beta.axpy(hq[h][a] * hr[h][a], p[a]);
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) sp[a][hc[h]] = p[a];
+    }
+    __syncthreads();
+    // 3. A p_m: the data part by (node, part) items, the first rounds from
+    // the rows kept in registers
+#pragma unroll
+    for (int x = 0; x < LP::KEEP; ++x) {
+      if (ke[x] < 0) continue;
+      T o[3];
+      part_product<T, TL::HX>(sp, kcz[x], [&](int y) { return keep[x][y]; }, o);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) ls.d[part_id][a][ke[x]] = o[a];
+    }
+    for (int v0 = LP::KEEP * LP::ROUND; v0 < n_data; v0 += LP::ROUND) {
+      int e = ke[LP::KEEP], cz = kcz[LP::KEEP], at = kslot;
+      if (v0 > LP::KEEP * LP::ROUND) {
+        e = has_item ? list_entry<LP>(ls, v0 + item) : -1;
+        cz = e >= 0 ? ls.node[e] + TL::HX * TL::HY * (part_id - 1) : 0;
+        at = e >= 0 ? ls.slot[e] : 0;
+      }
+      if (e < 0) continue;
+      const gptr<const T> __restrict__ A = glob<const T>(static_cast<const T*>(
+          __builtin_assume_aligned(L.A27r + (size_t)at * kA27Row + part_id * CW, 16)));
+      T o[3];
+      part_product<T, TL::HX>(sp, cz,
+                              [&](int y) { return A[kPartsPerNode * CW * (y / CW) + y % CW]; },
+                              o);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) ls.d[part_id][a][e] = o[a];
+    }
+    __syncthreads();
+    T* const ap_out = odd ? v_ap2 : v_ap;
+    // empty the slots of the next iterate
+    if (m > 0 && !solo && threadIdx.x < 4)
+      store_agent(slots + ((size_t)((m + 1) % 3) * 4 + threadIdx.x) * n_tiles + tile, kEmptySlot);
+    const T w2 = T(2) * L.wr;
+#pragma unroll
+    for (int vt = 0; vt < LP::VT; ++vt) {
+      const int ow = wv + vt * LP::PW;
+      if (ow >= LP::OW) continue;
+      double part[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int z = 0; z < TL::NPT; ++z) {
+        const int kk = vt * TL::NPT + z;
+        const int c = LP::own(kk);
+        constexpr int off[3] = {1, TL::HX, TL::HX * TL::HY};
+        T l[3] = {T(0), T(0), T(0)};
+        const T p0[3] = {sp[0][c], sp[1][c], sp[2][c]};
+        if (__all((nbr[kk] & 63u) == 63u)) {
+#pragma unroll
+          for (int k = 0; k < 6; ++k)
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+              l[a] += p0[a] - sp[a][c + ((k & 1) ? off[k / 2] : -off[k / 2])];
+        } else {
+#pragma unroll
+          for (int k = 0; k < 6; ++k)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+              const T x = p0[a] - sp[a][c + ((k & 1) ? off[k / 2] : -off[k / 2])];
+              l[a] += (nbr[kk] >> k & 1u) ? x : T(0);
+            }
+        }
+        T dd[3] = {T(0), T(0), T(0)};
+        if (rank[kk] >= 0) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+            dd[a] = (ls.d[0][a][rank[kk]] + ls.d[1][a][rank[kk]]) + ls.d[2][a][rank[kk]];
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          T o;
+          {
+#pragma clang fp contract(off)
+            o = w2 * l[a];  // rounded before the data part, as in k_cg
+            o = o + dd[a];
+          }
+          ap[kk][a] = node[kk] >= 0 ? o : T(0);
+          const double qd = (double)q[kk][a], rd = (double)r[kk][a], pd = (double)p0[a];
+          const double ad = (double)ap[kk][a];
+          part[0] += rd * qd * rd;
+          part[1] += pd * ad;
+          part[2] += ad * qd * rd;
+          part[3] += ad * qd * ad;
+        }
+        if (nbr[kk] & 64u) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+            store_agent(ap_out + a * N + (unsigned)node[kk], ap[kk][a]);
+        }
+      }
+      const double x = wave_sum4(part);
+      if (lane < 4) sums[lane * LP::OW + ow] = x;
+    }
+    // 4. the block's partials, published after A p
+    wait_stores();
+    __syncthreads();
+    if (threadIdx.x < 4) {
+      double x = 0.0;
+#pragma unroll
+      for (int u = 0; u < LP::OW; ++u) x += sums[threadIdx.x * LP::OW + u];
+      store_agent(slots + ((size_t)(m % 3) * 4 + threadIdx.x) * n_tiles + tile, slot_bits(x));
+    }
+    if (solo) finish_ticket(L.gang);
+    else ++m;
   }
-  cg_final_tile<T, TL>(w, iters - 1);
 }
 
 // d += alpha p of the last CG iterate (node workgroups).
@@ -880,28 +1526,47 @@ hipError_t launch_cg_final(int last, const Dispatch<T>& D, hipStream_t s,
   return hipGetLastError();
 }
 
-template <typename T, bool MASK>
-void launch_cg_loop_t(int iters, const Dispatch<T>& D, hipStream_t s) {
-  switch (D.one.tile) {
-    case 1: k_cg_loop<T, TileM, MASK><<<D.blocks, TileM::NT, 0, s>>>(D, iters); break;
-    case 2: k_cg_loop<T, TileW, MASK><<<D.blocks, TileW::NT, 0, s>>>(D, iters); break;
-    case 3: k_cg_loop<T, TileX, MASK><<<D.blocks, TileX::NT, 0, s>>>(D, iters); break;
-    case 4: k_cg_loop<T, TileZ, MASK><<<D.blocks, TileZ::NT, 0, s>>>(D, iters); break;
-    case 5: k_cg_loop<T, TileY, MASK><<<D.blocks, TileY::NT, 0, s>>>(D, iters); break;
-    case 6: k_cg_loop<T, TileH, MASK><<<D.blocks, TileH::NT, 0, s>>>(D, iters); break;
-    case 7: k_cg_loop<T, TileC, MASK><<<D.blocks, TileC::NT, 0, s>>>(D, iters); break;
-    default: k_cg_loop<T, TileS, MASK><<<D.blocks, TileS::NT, 0, s>>>(D, iters); break;
+// Calls f(kernel, threads) with the k_cg_loop instance of a tile kind.  512
+// threads leave 256 registers each, which hold two rounds of rows (336 data
+// nodes) beside the state of a 1024-node tile; on 1024 threads of 128
+// registers each the same state spilled.
+template <typename T, bool MASK, typename F>
+hipError_t with_loop_kernel(int kind, F&& f) {
+  switch (kind) {
+    case 1: return f(k_cg_loop<T, Loop<T, TileM, 512>, MASK>, 512);
+    case 2: return f(k_cg_loop<T, Loop<T, TileW, 256>, MASK>, 256);
+    case 3: return f(k_cg_loop<T, Loop<T, TileX, 512>, MASK>, 512);
+    case 4: return f(k_cg_loop<T, Loop<T, TileZ, 512>, MASK>, 512);
+    case 5: return f(k_cg_loop<T, Loop<T, TileY, 512>, MASK>, 512);
+    case 6: return f(k_cg_loop<T, Loop<T, TileH, 512>, MASK>, 512);
+    default: return f(k_cg_loop<T, Loop<T, TileS, 512>, MASK>, 512);
   }
 }
 
 template <typename T>
-hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s) {
+hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s,
+                          unsigned long long* stamp, int ticks) {
   if (D.blocks <= 0 || iters <= 0) return hipSuccess;
-  if (D.n != 1 || D.blocks > kPersistMaxTiles || D.blocks != D.one.ntiles)
-    return hipErrorInvalidValue;
-  if (D.masked) launch_cg_loop_t<T, true>(iters, D, s);
-  else launch_cg_loop_t<T, false>(iters, D, s);
-  return hipGetLastError();
+  auto go = [&](auto kernel, int threads) {
+    kernel<<<D.blocks, threads, 0, s>>>(D, iters, stamp, ticks);
+    return hipGetLastError();
+  };
+  return D.masked ? with_loop_kernel<T, true>(D.one.tile, go)
+                  : with_loop_kernel<T, false>(D.one.tile, go);
+}
+
+template <typename T>
+hipError_t cg_loop_capacity(int kind, bool masked, int* tiles) {
+  int dev = 0, cus = 0, per_cu = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  auto ask = [&](auto kernel, int threads) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0);
+  };
+  e = masked ? with_loop_kernel<T, true>(kind, ask) : with_loop_kernel<T, false>(kind, ask);
+  *tiles = std::min(cus * per_cu, kGangMaxTiles);
+  return e;
 }
 
 // ===========================================================================
@@ -1220,7 +1885,9 @@ hipError_t launch_set_rest(const Dispatch<T>& D, hipStream_t s) {
                                           unsigned long long*);                                 \
   template hipError_t launch_energy<T>(const Dispatch<T>&, const Dispatch<T>&, int, hipStream_t); \
   template hipError_t launch_reset_counters<T>(const Dispatch<T>&, hipStream_t);                 \
-  template hipError_t launch_cg_loop<T>(int, const Dispatch<T>&, hipStream_t);                   \
+  template hipError_t launch_cg_loop<T>(int, const Dispatch<T>&, hipStream_t,                    \
+                                         unsigned long long*, int);                             \
+  template hipError_t cg_loop_capacity<T>(int, bool, int*);                                      \
   template hipError_t launch_polar<T>(const Dispatch<T>&, hipStream_t);                          \
   template hipError_t launch_inject<T>(const Dispatch<T>&, const Dispatch<T>&, int, hipStream_t); \
   template hipError_t launch_prolong<T>(const Dispatch<T>&, const Dispatch<T>&, int, hipStream_t); \

@@ -21,6 +21,9 @@ namespace vd {
 constexpr int kA27Part = 56;
 constexpr int kA27Row = 3 * kA27Part;
 
+constexpr int kGangMaxTiles = 256;  // tiles of a lattice in a one-launch CG solve
+constexpr int kGangHead = 16;  // 8-byte words before the slots of LevelView::gang
+
 struct Scalars {
   double rz;      // r^T D^-1 r of the current CG iterate
   double pap;     // p^T A p
@@ -35,8 +38,7 @@ struct Scalars {
   int n_trace;
   int rows;        // constraint rows of the current frame (dense + 3 sparse)
   int n_dense;     // dense rows among them
-  unsigned bar;      // arrivals at the grid barrier of the persistent CG loop
-  int bar_timeouts;  // grid barrier waits that gave up (bounded spin)
+  int bar_timeouts;  // waits of one-launch CG solves that gave up (bounded spin)
   // energy-target mode: the target, set once E_total <= target (every
   // guarded launch then returns at entry), and iterations completed
   double target;
@@ -73,6 +75,8 @@ struct LevelView {
   const unsigned char* act;
   double* scg0;  // CG block partials [4][ntiles], even / odd iterates
   double* scg1;
+  double* gang;  // one-launch CG solve: kGangHead words (state, next ticket,
+                 // tickets done), then the exchange slots [3][4][ntiles]
   double* pe;    // energy block partials [3][rblocks + node blocks]
   // constraint cache
   const int* cell_map;  // (nx-1)(ny-1)(nz-1) -> active cell index or -1
@@ -206,12 +210,21 @@ template <typename T>
 hipError_t launch_cg_final(int last, const Dispatch<T>& D, hipStream_t s,
                            unsigned long long* stamp = nullptr);
 
-// All `iters` CG iterations and the last step of one position solve in one
-// launch (one lattice; all its tiles resident at once, with a grid barrier
-// between iterations).  Same arithmetic as launch_cg + launch_cg_final.
-constexpr int kPersistMaxTiles = 128;
+// All `iters` CG iterations and the last step of the position solve of every
+// lattice of D in one launch (tile workgroups; each lattice at most
+// cg_loop_capacity tiles).  Follows a gradient pass, which resets its
+// exchange slots.  Same bits as launch_cg + launch_cg_final.  stamp (may be
+// NULL): the device clock at the start of iteration 1 and of the last step.
+// ticks: how long a workgroup waits for the others before the solve is
+// abandoned to the ticket path (100 MHz clock; negative: at once, for tests).
+constexpr int kAssembleTicks = 30000;
 template <typename T>
-hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s);
+hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s,
+                          unsigned long long* stamp = nullptr, int ticks = kAssembleTicks);
+
+// Tiles of a kind that fit on the GPU together in launch_cg_loop.
+template <typename T>
+hipError_t cg_loop_capacity(int kind, bool masked, int* tiles);
 
 // Energy of eq. (1) into each lattice's sc->energy (rows+nodes workgroups for
 // De, one workgroup per lattice for D1).

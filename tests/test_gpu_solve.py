@@ -344,3 +344,27 @@ def test_graph_profile_events_time_the_finest_cg_and_change_nothing():
     assert n["cg_a"] == gn * (pcg - 1)
     assert 0.5 < us["cg_a"] < 5000.0
     np.testing.assert_array_equal(prof.get_energy(), e_plain)
+
+
+@pytest.mark.parametrize("tile", range(1, 9))
+@pytest.mark.parametrize("precision,active", [("fp32", False), ("fp32", True), ("fp64", False)])
+def test_one_launch_solves_equal_per_iteration_launches(tile, precision, active):
+    """One-launch CG solves with every tile kind on a ragged lattice (remainders
+    in every axis; up to 256 nodes of a tile carry data blocks, more than one
+    round of the lanes), run as a gang and abandoned to the ticket counter,
+    with 1, 2 and 7 iterations: the bits of one launch per iteration."""
+    scene = make_tiny(seed=5, dims=(37, 11, 18), num_levels=2, gn=2, pcg=7, n_dense=3000,
+                      n_sparse=20, spacing=0.6, origin=(0.2, -1.0, 0.4))
+    for pcg in (1, 2, 7):
+        scene.spec.pcg_iters = (pcg, pcg)
+        out = {}
+        for mode in ("iterative", "gang", "tickets"):
+            lat = make_lattice(scene, tiles=(tile, tile), iterative=mode == "iterative",
+                               precision=precision, active_set=active)
+            lat.debug_abandon_loops(mode == "tickets")
+            rep = lat.solve_frame(reset=True, report=True)
+            assert not rep["bits"] & 16
+            out[mode] = (rep["energy"], lat.get_state64()[0])
+        for mode in ("gang", "tickets"):
+            np.testing.assert_array_equal(out[mode][0], out["iterative"][0])
+            np.testing.assert_array_equal(out[mode][1], out["iterative"][1])
