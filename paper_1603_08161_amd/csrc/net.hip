@@ -11,8 +11,8 @@
 // matching 8 k of one output channel from the pre-packed weights.  The same
 // kernel runs the backward data pass (flipped, transposed weights; a stride-2
 // layer reads its output gradient at (o + tap - 1) / 2 where that is even).
-// Weight gradients are a split-K GEMM over voxels with both operands staged
-// transposed in LDS, followed by a fixed-order reduction of the partials.
+// Weight gradients are a split-K GEMM over voxels with both operands read
+// transposed from LDS, followed by a fixed-order reduction of the partials.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -277,16 +277,251 @@ inline size_t conv_lds_bytes(const ConvArgs& A, int MB) {
 }
 
 // ---------------------------------------------------------------------------
-// weight gradients: dW[k][co] = sum_v X[v][k] dY[v][co], plus the bias row
-// k = 27 c_in (X = 1).  Workgroup (mtile, chunk) sums the voxels of its chunk
-// for 64 rows k and all columns; partials [chunk][mpad][npad].
+// weight gradients: dW[k][co] = sum_v X[v][k] dY[v][co], k = tap * c_in + ci,
+// plus the bias row k = 27 c_in (X = 1)
 // ---------------------------------------------------------------------------
+//
+// Voxels are split into chunks; a chunk's sum runs over its voxels in linear
+// order, 32 per matrix op, and the chunks are added in order, so every path
+// below gives the same bits.
+//
+// Path of grids whose rows fit in LDS (k_wgrad): workgroup (chunk, tap plane
+// and 16 input channels), all columns.  It stages blocks of 32 KS voxels: dY as it
+// lies in memory, and the input rows that the block's nine taps of plane tz
+// touch, channels-last.  Its eight waves share the taps.  The transposing LDS
+// read (ds_read_b64_tr_b16) gives a lane four voxels of its channel from
+// voxel-major rows at any addresses, so a tap is an address offset and a block
+// may cross rows and planes.  The next block's loads are in flight while the
+// current one is computed.  Every input is loaded three times (once per tap
+// plane) instead of 27.
+//
+// What bounds it: the LDS reads of the operands, 18 + 16 CO half-kilobyte
+// reads per 32 voxels and workgroup.  Gathering 8 channels per lane and tap
+// from memory and transposing through 2-byte LDS stores (k_wgrad_gather, still
+// the path of wider rows) took 755 us for the layers of 16 columns at 64^3,
+// batch 4, on average, against 185 us here (32 columns: 197 and 66 us); the
+// training step went from 6.69 to 3.16 ms.
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+constexpr int kWgThreads = 512;
+constexpr int kWgLoads = 8;  // 16-byte loads per thread and block
+
+// Four voxels of the calling lane's channel; `row` is the lane's own address:
+// voxel (lane % 16) / 4 of the four, channel 4 (lane % 4).
+__device__ __forceinline__ s16x4 read_tr(const uint16_t* row) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s16x4*)const_cast<uint16_t*>(row));
+}
+
+__device__ __forceinline__ bf16x8 join8(s16x4 lo, s16x4 hi) {
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// A voxel's place in a staged block: its x and the LDS line of tap row ty = 0.
+// Lines are the input rows of the block's planes in order, each plane's from
+// the row above its first output row (in the block) to the one below its
+// last: plane p's are y = -1 .. S oh + 1 - S, LP = S oh + 3 - S of them.
+template <int S>
+struct WgPlace {
+  int x, y, line;
+  // the voxel `ahead` after (x0, y0), the block's first
+  __device__ __forceinline__ void at(int x0, int y0, int ahead, int ow, int oh) {
+    x = x0 + ahead;
+    y = y0;
+    line = 0;
+    while (x >= ow) wrap(ow, oh);
+  }
+  __device__ __forceinline__ void wrap(int ow, int oh) {  // past a row's end
+    const bool r = x >= ow;
+    x -= r ? ow : 0;
+    line += r ? S : 0;
+    y += r ? 1 : 0;
+    const bool pl = y == oh;
+    y = pl ? 0 : y;
+    line += pl ? 3 - S : 0;
+  }
+  __device__ __forceinline__ void step(int ow, int oh) {
+    x += 32;
+    wrap(ow, oh);
+    if (ow < 32)
+      while (x >= ow) wrap(ow, oh);
+  }
+};
+
+template <int CO, int S>
+__global__ __launch_bounds__(kWgThreads) void k_wgrad(ConvArgs A, WgradArgs G) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t wg_lds[];
+  const int W = S * (A.ow - 1) + 3, LP = S * A.oh + 3 - S;
+  uint16_t* const ys = wg_lds;                             // [32 KS][CO * 16]
+  uint16_t* const xs = wg_lds + 32 * G.ksteps * CO * 16;   // [lines][W][16]
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int chunk = blockIdx.x, tz = blockIdx.y % 3, ci0 = blockIdx.y / 3 * 16;
+  // (at most 2^28 voxels: 32-bit indices)
+  const int v_begin = chunk * (int)G.vox_per_chunk;
+  const int v_end = min(v_begin + (int)G.vox_per_chunk, A.batch * A.od * A.oh * A.ow);
+  // source of the 16 channels (a concatenation's boundary is a multiple of 16)
+  const uint16_t* src = A.a;
+  int C = A.ca, cc = ci0;
+  if (cc >= A.ca) {
+    src = A.b;
+    C = A.cb;
+    cc -= A.ca;
+  }
+  const int nch8 = C - cc >= 16 ? 2 : 1;  // 16-byte groups that exist
+  const int block_vox = 32 * G.ksteps;
+  // the wave's taps (ty, tx) of plane tz: wave, and 8 for wave 0; wave 1 of
+  // the first plane and channels sums the bias row instead
+  const bool second = wave == 0, bias = wave == 1 && blockIdx.y == 0;
+  const int off0 = (wave / 3 * W + wave % 3) * 16, off1 = (2 * W + 2) * 16;
+  f32x4 acc[2][CO];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int j = 0; j < CO; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const short one = (lane & 15) == 0 ? (short)0x3f80 : (short)0;  // bfloat16 1, first row
+  const s16x4 ones = {one, one, one, one};
+  const int sub = (lane & 15) >> 2, quad = (lane & 3) * 4, first = 8 * (lane >> 4) + sub;
+  const int ny = block_vox * CO * 2;  // 16-byte groups of a block's dY
+  uint4 pre[kWgLoads];
+  // the input line and x of each of the thread's loads: line << 16 | x, -1: none
+  int place[kWgLoads];
+#pragma unroll
+  for (int i = 0; i < kWgLoads; ++i) {
+    const int q = threadIdx.x + i * kWgThreads - ny, l = (q >> 1) / W;
+    place[i] = q >= 0 && l < G.lines && (q & 1) < nch8 ? l << 16 | ((q >> 1) - l * W) : -1;
+  }
+  // limits of the input coordinates (up-sampled layers: of the fine grid)
+  const bool up = A.mode == kGatherUp;
+  const unsigned nx = up ? A.ow : A.sw, nyl = up ? A.oh : A.sh, nz = up ? A.od : A.sd;
+  const bool many_planes = G.lines + S * A.oh > 2 * LP;
+  // block starts: the block being fetched, then (one behind) the one computed
+  int fx = v_begin % A.ow, fy = v_begin / A.ow % A.oh, fz = v_begin / (A.ow * A.oh) % A.od,
+      fb = v_begin / (A.ow * A.oh * A.od);
+  auto fetch = [&](int v) {
+#pragma unroll
+    for (int i = 0; i < kWgLoads; ++i) {
+      const int q = threadIdx.x + i * kWgThreads;
+      const uint16_t* p = nullptr;
+      if (q < ny) {
+        const int m = v + q / (CO * 2), c = q % (CO * 2) * 8;
+        if (m < v_end && c < G.cdy) p = G.dy + (size_t)m * G.cdy + c;
+      } else if (place[i] >= 0) {
+        int py = (place[i] >> 16) + S * fy, z = fz, b = fb;
+        do {  // into the next plane
+          const bool w = py >= LP;
+          py -= w ? LP : 0;
+          z += w ? 1 : 0;
+          const bool nb = z == A.od;
+          z = nb ? 0 : z;
+          b += nb ? 1 : 0;
+        } while (many_planes && py >= LP);
+        int px = (place[i] & 0xffff) - 1, pz = S * z + tz - 1;
+        --py;
+        if ((unsigned)px < nx && (unsigned)py < nyl && (unsigned)pz < nz && b < A.batch) {
+          px >>= up;
+          py >>= up;
+          pz >>= up;
+          const int sv = ((b * A.sd + pz) * A.sh + py) * A.sw + px;
+          p = src + (size_t)sv * C + cc + 8 * ((q - ny) & 1);
+        }
+      }
+      pre[i] = p ? *reinterpret_cast<const uint4*>(p) : uint4{0u, 0u, 0u, 0u};
+    }
+  };
+  WgPlace<S> lo, hi;
+  // operands of one step at the places lo, hi
+  struct Frags {
+    bf16x8 b[CO], a0, a1;
+  };
+  auto read = [&](int s) {
+    Frags f;
+    const uint16_t* yrow = ys + (32 * s + first) * CO * 16 + quad;
+    const uint16_t* xlo = xs + (lo.line * W + S * lo.x) * 16 + quad;
+    const uint16_t* xhi = xs + (hi.line * W + S * hi.x) * 16 + quad;
+#pragma unroll
+    for (int j = 0; j < CO; ++j)
+      f.b[j] = join8(read_tr(yrow + 16 * j), read_tr(yrow + 4 * CO * 16 + 16 * j));
+    f.a0 = join8(read_tr(xlo + off0), read_tr(xhi + off0));
+    f.a1 = second ? join8(read_tr(xlo + off1), read_tr(xhi + off1)) : join8(ones, ones);
+    return f;
+  };
+  auto multiply = [&](const Frags& f) {
+#pragma unroll
+    for (int j = 0; j < CO; ++j)
+      acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a0, f.b[j], acc[0][j], 0, 0, 0);
+    if (second || bias) {
+#pragma unroll
+      for (int j = 0; j < CO; ++j)
+        acc[1][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a1, f.b[j], acc[1][j], 0, 0, 0);
+    }
+  };
+  fetch(v_begin);
+  for (int v = v_begin; v < v_end; v += block_vox) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kWgLoads; ++i) {
+      const int q = threadIdx.x + i * kWgThreads;
+      if (q < ny + G.lines * W * 2) *reinterpret_cast<uint4*>(wg_lds + 8 * q) = pre[i];
+    }
+    __syncthreads();
+    lo.at(fx, fy, first, A.ow, A.oh);
+    hi.at(fx, fy, first + 4, A.ow, A.oh);
+    if (v + block_vox < v_end) {
+      fx += block_vox;
+      const int rows = fx / A.ow;
+      fx -= rows * A.ow;
+      fy += rows;
+      while (fy >= A.oh) {
+        fy -= A.oh;
+        if (++fz == A.od) {
+          fz = 0;
+          ++fb;
+        }
+      }
+      fetch(v + block_vox);
+    }
+    const int left = (v_end - v + 31) / 32;
+    const int steps = min(left, G.ksteps);
+    // the next step's reads are issued before a step's products
+    Frags f = read(0);
+    for (int s = 0; s < steps; s += 2) {
+      lo.step(A.ow, A.oh);
+      hi.step(A.ow, A.oh);
+      Frags g = f;
+      if (s + 1 < steps) g = read(s + 1);
+      multiply(f);
+      if (s + 1 >= steps) break;
+      lo.step(A.ow, A.oh);
+      hi.step(A.ow, A.oh);
+      if (s + 2 < steps) f = read(s + 2);
+      multiply(g);
+    }
+  }
+  float* out = G.partial + (size_t)chunk * G.mpad * G.npad;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (t == 1 && !second && !bias) continue;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int ci = ci0 + 4 * (lane >> 4) + r;
+      const bool is_bias = t == 1 && bias;
+      if (is_bias ? ci > 0 : ci >= A.cin) continue;
+      const int row = is_bias ? 27 * A.cin : (tz * 9 + (t == 0 ? wave : 8)) * A.cin + ci;
+#pragma unroll
+      for (int j = 0; j < CO; ++j)
+        out[(size_t)row * G.npad + j * 16 + (lane & 15)] = acc[t][j][r];
+    }
+  }
+}
+
+// Grids whose rows do not fit: workgroup (mtile, chunk) sums the voxels of its
+// chunk for 64 rows k and all columns; partials [chunk][mpad][npad].
 
 constexpr int kWgVox = 32;          // voxels per LDS stage (one MFMA K step)
 constexpr int kWgPitch = kWgVox + 8;  // bf16 per LDS row (80 bytes, 16-aligned)
 
 template <int NB>
-__global__ __launch_bounds__(kBlock) void k_wgrad(ConvArgs A, WgradArgs G) {
+__global__ __launch_bounds__(kBlock) void k_wgrad_gather(ConvArgs A, WgradArgs G) {
   __shared__ __attribute__((aligned(16))) uint16_t xt[64 * kWgPitch];
   __shared__ __attribute__((aligned(16))) uint16_t gt[64 * kWgPitch];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -347,26 +582,24 @@ __global__ __launch_bounds__(kBlock) void k_wgrad(ConvArgs A, WgradArgs G) {
     }
 }
 
-// grad[off + p] = sum over chunks (fixed order) of the partial at (row, co).
-__global__ __launch_bounds__(kBlock) void k_wgrad_reduce(const float* __restrict__ partial,
-                                                         int nchunks, int mpad, int npad,
-                                                         int cin, int cout, float* grad) {
-  const int nw = cout * cin * 27;
-  const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p >= nw + cout) return;
-  int row, co;
-  if (p < nw) {
-    co = p / (cin * 27);
-    const int rem = p - co * cin * 27;
-    const int ci = rem / 27, t = rem - ci * 27;
-    row = t * cin + ci;
-  } else {
-    co = p - nw;
-    row = 27 * cin;
-  }
+// grad[p] = sum over chunks (in order) of the partial at (row, co), one thread
+// per entry in the partials' order.
+__global__ __launch_bounds__(kWave) void k_wgrad_reduce(const float* __restrict__ partial,
+                                                        int nchunks, int mpad, int npad, int cin,
+                                                        int cout, float* grad) {
+  const int e = blockIdx.x * kWave + threadIdx.x;
+  const int row = e / npad, co = e - row * npad;
+  if (row > 27 * cin || co >= cout) return;
+  const float* p = partial + (size_t)row * npad + co;
   float s = 0.f;
-  for (int c = 0; c < nchunks; ++c) s += partial[((size_t)c * mpad + row) * npad + co];
-  grad[p] = s;
+#pragma unroll 16
+  for (int c = 0; c < nchunks; ++c) s += p[(size_t)c * mpad * npad];
+  if (row == 27 * cin) {
+    grad[(size_t)cout * cin * 27 + co] = s;
+  } else {
+    const int t = row / cin, ci = row - t * cin;
+    grad[((size_t)co * cin + ci) * 27 + t] = s;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -940,6 +1173,26 @@ class Net {
     return A;
   }
 
+  // The staged block of k_wgrad: the most 32-voxel steps (at most 16) whose
+  // dY and input lines a workgroup loads at once and two workgroups hold in a
+  // compute unit's LDS.  Returns the LDS bytes, 0 where not even one step
+  // fits (rows of some 600 voxels) and k_wgrad_gather runs instead.
+  static size_t wgrad_block(const ConvArgs& A, int co, WgradArgs* G) {
+    const int S = A.stride, W = S * (A.ow - 1) + 3;
+    for (int ks = 16; ks >= 1; ks /= 2) {
+      // voxels of a block lie in at most this many rows and planes
+      const int64_t rows = (32 * ks + A.ow - 2) / A.ow + 1;
+      const int64_t planes = (rows + A.oh - 2) / A.oh + 1;
+      const int64_t lines = S * (rows - 1) + (3 - S) * (planes - 1) + 3;
+      const int64_t groups = 32 * ks * co * 2 + lines * W * 2;
+      if (groups > kWgLoads * kWgThreads || groups * 16 > 80 * 1024) continue;
+      G->ksteps = ks;
+      G->lines = (int)lines;
+      return (size_t)groups * 16;
+    }
+    return 0;
+  }
+
   hipError_t launch_wgrad(int l, const uint16_t* x, const uint16_t* gy, int batch) {
     const WgPlan p = wg_plan(l, batch);
     const ConvArgs A = fwd_args(l, x, batch);
@@ -950,18 +1203,31 @@ class Net {
     G.npad = p.npad;
     G.vox_per_chunk = p.vox_per_chunk;
     G.partial = wpart_;
-    const dim3 grid(p.mtiles, p.nchunks);
-    switch (p.nb) {
-      case 1: k_wgrad<1><<<grid, kBlock, 0, stream_>>>(A, G); break;
-      case 2: k_wgrad<2><<<grid, kBlock, 0, stream_>>>(A, G); break;
-      case 4: k_wgrad<4><<<grid, kBlock, 0, stream_>>>(A, G); break;
-      default: return hipErrorInvalidValue;
+    const size_t lds = wgrad_block(A, p.nb, &G);
+    if (lds > 0) {
+      const dim3 grid(p.nchunks, 3 * ((A.cin + 15) / 16));
+      auto run = [&](auto kernel) { kernel<<<grid, kWgThreads, lds, stream_>>>(A, G); };
+      switch (10 * A.stride + p.nb) {
+        case 11: run(k_wgrad<1, 1>); break;
+        case 12: run(k_wgrad<2, 1>); break;
+        case 14: run(k_wgrad<4, 1>); break;
+        case 22: run(k_wgrad<2, 2>); break;
+        case 24: run(k_wgrad<4, 2>); break;
+        default: return hipErrorInvalidValue;
+      }
+    } else {
+      const dim3 grid(p.mtiles, p.nchunks);
+      switch (p.nb) {
+        case 1: k_wgrad_gather<1><<<grid, kBlock, 0, stream_>>>(A, G); break;
+        case 2: k_wgrad_gather<2><<<grid, kBlock, 0, stream_>>>(A, G); break;
+        case 4: k_wgrad_gather<4><<<grid, kBlock, 0, stream_>>>(A, G); break;
+        default: return hipErrorInvalidValue;
+      }
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const LayerDef& d = kLayers[l];
-    const int64_t np = layer_params(d);
-    k_wgrad_reduce<<<(unsigned)((np + kBlock - 1) / kBlock), kBlock, 0, stream_>>>(
+    k_wgrad_reduce<<<(unsigned)((p.mpad * p.npad + kWave - 1) / kWave), kWave, 0, stream_>>>(
         wpart_, p.nchunks, p.mpad, p.npad, d.ca + d.cb, d.cout, grad_ + off_[l]);
     return hipGetLastError();
   }

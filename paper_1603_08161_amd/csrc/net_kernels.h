@@ -57,6 +57,7 @@ struct WgradArgs {
   int cdy;             // cout rounded up to 8
   int mpad, npad;      // partial tile: rows 27 cin + 1 rounded to 64, columns
   int64_t vox_per_chunk;
+  int ksteps, lines;   // block of k_wgrad: 32-voxel steps, input lines
   float* partial;      // [chunks][mpad][npad]
 };
 

@@ -320,3 +320,70 @@ def test_adam_three_steps_match_oracle_sequence():
         assert np.all(err <= tol), t
         # the step after t = 1 is no longer +-lr: the recursion is exercised
         assert t == 1 or np.abs(np.abs(got - v0) - t * lr).max() > 1e-2 * lr
+
+
+@pytest.mark.parametrize("dims,batch", [((17, 9, 6), 1), ((16, 8, 4), 3), ((33, 5, 9), 2)])
+def test_weight_gradients_across_rows_and_planes(dims, batch):
+    """Weight gradients on ragged grids whose 32-voxel steps cross rows, planes
+    and samples, and on one where they end with them, with fewer samples than
+    the handle holds (other chunks of partials).  On grids this small a bfloat16 rounding that falls the other
+    way flips a ReLU that is a per cent of its layer, so the gate of each
+    parameter is the file's 1e-2 plus three times what the oracle itself
+    moves when its values are perturbed by float32 accumulation noise (3e-7)
+    before they are rounded."""
+    from paper_1603_08161_amd import Net
+    n = dims[0] * dims[1] * dims[2]
+    v = _params(11)
+    nt = Net(dims, max_batch=batch + 1)
+    nt.set_params(v)
+    bits = _input(12, dims, batch)
+    target = np.random.default_rng(13).normal(size=(batch, 3, n)).astype(np.float32)
+    _, g = nt.gradients(bits, target, batch=batch)
+    p = _oracle_params(v)
+
+    def oracle_gradients(noise, seed):
+        rng = np.random.default_rng(seed)
+
+        def rnd(a):
+            return onet.bf16_round(np.asarray(a) * (1 + noise * rng.normal(size=np.shape(a))))
+
+        total = None
+        for b in range(batch):
+            x = _from_bits(bits[b]).reshape(dims[2], dims[1], dims[0], 8).transpose(3, 0, 1, 2)
+            out, acts = onet.forward(p, x, act_round=rnd)
+            diff = out - target[b].reshape(3, dims[2], dims[1], dims[0]).astype(np.float64)
+            gb = onet.backward(p, acts, 2.0 * diff / (batch * n), grad_round=rnd)
+            gb.pop("x")
+            total = gb if total is None else {k: total[k] + gb[k] for k in gb}
+        return total
+
+    ref = oracle_gradients(0.0, 0)
+    moved = [oracle_gradients(3e-7, s) for s in (1, 2, 3)]
+    got = onet.unflatten(g.astype(np.float64))
+    for k in ref:
+        gate = 1e-2 + 3 * max(rel_err(m[k], ref[k]) for m in moved)
+        assert rel_err(got[k], ref[k]) < gate, k
+
+
+def test_weight_gradients_of_rows_too_wide_for_lds():
+    """A grid of 700-voxel rows, which the staged weight-gradient kernel cannot
+    hold (the finest layers take the gathering kernel, the coarser ones the
+    staged one).  Gate: 1e-2 plus three times the 1.1e-2 that the oracle moves
+    when its values are perturbed by 3e-7 before they are rounded."""
+    from paper_1603_08161_amd import Net
+    dims = (700, 3, 2)
+    n = dims[0] * dims[1] * dims[2]
+    v = _params(15)
+    nt = Net(dims, max_batch=1)
+    nt.set_params(v)
+    bits = _input(16, dims, 1)
+    target = np.random.default_rng(17).normal(size=(1, 3, n)).astype(np.float32)
+    _, g = nt.gradients(bits, target, batch=1)
+    p = _oracle_params(v)
+    out, acts = _oracle_forward(p, bits[0], dims)
+    diff = out - target[0].reshape(3, dims[2], dims[1], dims[0]).astype(np.float64)
+    ref = onet.backward(p, acts, 2.0 * diff / n, grad_round=onet.bf16_round)
+    got = onet.unflatten(g.astype(np.float64))
+    for name, *_ in onet.LAYERS:
+        for part in (".W", ".b"):
+            assert rel_err(got[name + part], ref[name + part]) < 4.4e-2, name + part
