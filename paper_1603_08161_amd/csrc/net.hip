@@ -6,11 +6,12 @@
 // rows are output voxels, columns output channels, and the reduction index
 // k = tap * c_in + channel runs over the 27 taps and the input channels.  A
 // wavefront issues v_mfma_f32_16x16x32_bf16 on 16-voxel x 16-channel tiles:
-// each lane gathers 8 consecutive k of one voxel (8 channels of one tap, a
-// single 16-byte load, since every channel count is a multiple of 8) and the
-// matching 8 k of one output channel from the pre-packed weights.  The same
-// kernel runs the backward data pass (flipped, transposed weights; a stride-2
-// layer reads its output gradient at (o + tap - 1) / 2 where that is even).
+// each lane reads 8 consecutive k of one voxel (8 channels of one tap, a
+// single 16-byte LDS read, since every channel count is a multiple of 8) and
+// the matching 8 k of one output channel from the pre-packed weights.  The
+// same kernel runs the backward data pass (flipped, transposed weights; a
+// stride-2 layer reads its output gradient at (o + tap - 1) / 2 where that is
+// even).
 // Weight gradients are a split-K GEMM over voxels with both operands read
 // transposed from LDS, followed by a fixed-order reduction of the partials.
 #include <hip/hip_runtime.h>
@@ -96,184 +97,165 @@ __device__ inline uint4 gather8(const ConvArgs& A, int b, int z, int y, int x, i
 // convolution (forward and backward data)
 // ---------------------------------------------------------------------------
 
-// Epilogue of a 16 x (16 NB) tile pair: bias, skip addend, ReLU / ReLU mask,
-// bfloat16 stores split over the concatenated outputs, or float32 output.
-template <int MB, int NB>
-__device__ __forceinline__ void conv_epilogue(const ConvArgs& A, const f32x4 (&acc)[MB][NB],
-                                              int64_t mbase, int lane) {
-  const int64_t M = (int64_t)A.batch * A.od * A.oh * A.ow;
-  // result tile: lane holds rows 4*(lane/16) + r, column lane % 16
+// A workgroup computes a brick of 16 x BY x BZ output voxels for NB blocks of
+// 16 output channels.  It stages the brick's input with its halo in LDS, one
+// plane per group of 8 channels, so that the 16 voxels of a fragment are 256
+// contiguous bytes whatever the tap.  Its four waves hold MB = BY BZ / 4 rows
+// of 16 voxels each; the weights of a 32-wide chunk of k are loaded once for
+// them, and with the brick's extents known to the compiler a fragment's
+// address is one register and an immediate.  The products are taken
+// transposed (weights as the first operand), which leaves four consecutive
+// output channels of a voxel in a lane: 8-byte stores.  Chunks run in order, so
+// the sums do not depend on the brick.
+//
+// What bounds it: one KB of LDS per matrix op with 16 output channels (about 3
+// us for a 16 -> 16 layer at 64^3), the staging's round trip and the launch.
+// Gathering every tap from memory, or staging rows of 128 voxels with weights
+// loaded once per two fragments, took 413 us per forward pass at 64^3 (33 us
+// for that layer).
+
+// Four output channels co .. co + 3 of voxel m at (b, n): bias, skip addend,
+// ReLU / ReLU mask, bfloat16 or float32 output.
+__device__ __forceinline__ void conv_store(const ConvArgs& A, f32x4 v, int m, int b, int n, int co) {
+  if (A.bias) {
 #pragma unroll
-  for (int i = 0; i < MB; ++i) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t m = mbase + i * 16 + 4 * (lane >> 4) + r;
-      if (m >= M) continue;
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const int co = j * 16 + (lane & 15);
-        float v = acc[i][j][r];
-        if (A.out_f32) {
-          if (co < A.cout) {
-            if (A.bias) v += A.bias[co];
-            const int64_t npb = (int64_t)A.od * A.oh * A.ow;
-            const int64_t b = m / npb, n = m - b * npb;
-            A.out_f32[(b * A.cout + co) * npb + n] = v;
-          }
-          continue;
-        }
-        if (co < A.c0) {
-          const size_t e = (size_t)m * A.c0 + co;
-          if (A.bias) v += A.bias[co];
-          if (A.add0) v += bf2f(A.add0[e]);
-          if (A.relu) v = fmaxf(v, 0.f);
-          if (A.mask0 && !bf_pos(A.mask0[e])) v = 0.f;
-          A.dst0[e] = f2bf(v);
-        } else if (co < A.c0 + A.c1) {
-          const size_t e = (size_t)m * A.c1 + (co - A.c0);
-          if (A.bias) v += A.bias[co];
-          if (A.add1) v += bf2f(A.add1[e]);
-          if (A.relu) v = fmaxf(v, 0.f);
-          if (A.mask1 && !bf_pos(A.mask1[e])) v = 0.f;
-          A.dst1[e] = f2bf(v);
-        }
-      }
-    }
+    for (int r = 0; r < 4; ++r)
+      if (co + r < A.cout) v[r] += A.bias[co + r];
   }
+  if (A.out_f32) {
+    const int64_t npb = (int64_t)A.od * A.oh * A.ow;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (co + r < A.cout) A.out_f32[((int64_t)b * A.cout + co + r) * npb + n] = v[r];
+    return;
+  }
+  // channels [0, c0) go to dst0, [c0, c0 + c1) to dst1 (multiples of 16)
+  const bool lower = co < A.c0;
+  const int c = lower ? A.c0 : A.c1, cc = lower ? co : co - A.c0;
+  if (cc >= c) return;
+  const size_t e = (size_t)m * c + cc;
+  const uint16_t* const add = lower ? A.add0 : A.add1;
+  const uint16_t* const mask = lower ? A.mask0 : A.mask1;
+  if (add) {
+    const uint2 s = *reinterpret_cast<const uint2*>(add + e);
+    v[0] += bf2f((uint16_t)s.x);
+    v[1] += bf2f((uint16_t)(s.x >> 16));
+    v[2] += bf2f((uint16_t)s.y);
+    v[3] += bf2f((uint16_t)(s.y >> 16));
+  }
+  if (A.relu) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
+  }
+  if (mask) {
+    const uint2 s = *reinterpret_cast<const uint2*>(mask + e);
+    if (!bf_pos((uint16_t)s.x)) v[0] = 0.f;
+    if (!bf_pos((uint16_t)(s.x >> 16))) v[1] = 0.f;
+    if (!bf_pos((uint16_t)s.y)) v[2] = 0.f;
+    if (!bf_pos((uint16_t)(s.y >> 16))) v[3] = 0.f;
+  }
+  uint2 o;
+  o.x = f2bf(v[0]) | (uint32_t)f2bf(v[1]) << 16;
+  o.y = f2bf(v[2]) | (uint32_t)f2bf(v[3]) << 16;
+  *reinterpret_cast<uint2*>((lower ? A.dst0 : A.dst1) + e) = o;
 }
 
-template <int MB, int NB>
+constexpr int kConvX = 16;  // brick extent along x
+
+template <int CIN, int NB, int S, int BY, int BZ>
 __global__ __launch_bounds__(kBlock) void k_conv(ConvArgs A) {
+  constexpr int HX = S * (kConvX - 1) + 3, HY = S * (BY - 1) + 3, HZ = S * (BZ - 1) + 3;
+  constexpr int VOX = HX * HY * HZ, CG = CIN / 8, MB = BY * BZ / 4;
+  constexpr int NCH = (27 * CIN + 31) / 32;
+  __shared__ uint4 s_in[CG * VOX];  // [channel group][z][y][x]
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int64_t M = (int64_t)A.batch * A.od * A.oh * A.ow;
-  const int64_t mbase = ((int64_t)blockIdx.x * (kBlock / kWave) + wave) * (16 * MB);
-  if (mbase >= M) return;
-  int vb[MB], vz[MB], vy[MB], vx[MB];
-  bool vok[MB];
+  int q = blockIdx.x;
+  const int nbx = (A.ow + kConvX - 1) / kConvX, nby = (A.oh + BY - 1) / BY,
+            nbz = (A.od + BZ - 1) / BZ;
+  const int ox = q % nbx * kConvX;
+  q /= nbx;
+  const int oy = q % nby * BY;
+  q /= nby;
+  const int oz = q % nbz * BZ, b = q / nbz;
+  const int j0 = blockIdx.y * NB;
+  // limits of the input coordinates (up-sampled and transposed layers: of the
+  // fine grid)
+  const bool plain = A.mode == kGatherPlain, odd_zero = A.mode == kGatherTransposed2;
+  const int half = plain ? 0 : 1;
+  const unsigned nx = A.mode == kGatherUp ? A.ow : A.sw << half,
+                 ny = A.mode == kGatherUp ? A.oh : A.sh << half,
+                 nz = A.mode == kGatherUp ? A.od : A.sd << half;
 #pragma unroll
-  for (int i = 0; i < MB; ++i) {
-    const int64_t m = mbase + i * 16 + (lane & 15);
-    vok[i] = m < M;
-    int64_t r = vok[i] ? m : 0;
-    vx[i] = (int)(r % A.ow);
-    r /= A.ow;
-    vy[i] = (int)(r % A.oh);
-    r /= A.oh;
-    vz[i] = (int)(r % A.od);
-    vb[i] = (int)(r / A.od);
-  }
-  f32x4 acc[MB][NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int kq = 8 * (lane >> 4);
-  const uint4* __restrict__ W = A.w;
-  for (int ch = 0; ch < A.nchunk; ++ch) {
-    bf16x8 af[MB];
-#pragma unroll
-    for (int i = 0; i < MB; ++i) {
-      const uint4 v = vok[i] ? gather8(A, vb[i], vz[i], vy[i], vx[i], ch * 32 + kq)
-                             : uint4{0u, 0u, 0u, 0u};
-      af[i] = as_bf16x8(v);
-    }
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const bf16x8 bw = as_bf16x8(W[((size_t)ch * NB + j) * kWave + lane]);
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bw, acc[i][j], 0, 0, 0);
-    }
-  }
-  conv_epilogue<MB, NB>(A, acc, mbase, lane);
-}
-
-// Stride-1 convolutions whose workgroup block (64 MB voxels: 4 waves of MB
-// 16-voxel tiles) is R = 64 MB / ow whole rows of one (batch, z) plane: the
-// block's input (3 planes x (R + 2) rows x
-// (ow + 2) voxels x cin channels, zero outside the grid) is staged in LDS once,
-// and the 27 taps of every output voxel read it there instead of gathering
-// from global memory.  The fragments and the matrix ops, in their order, are
-// those of k_conv, so the results are the same bits.
-template <int MB, int NB>
-__global__ __launch_bounds__(kBlock) void k_conv_lds(ConvArgs A) {
-  constexpr int kConvBlockVox = (kBlock / kWave) * 16 * MB;
-  extern __shared__ uint4 s_in[];  // [voxel][cin / 8]
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int ow = A.ow, R = kConvBlockVox / ow, W2 = ow + 2, H2 = R + 2;
-  const int cg = A.cin >> 3;  // 16-byte channel groups per voxel
-  const int64_t blk0 = (int64_t)blockIdx.x * kConvBlockVox;
-  int64_t r = blk0 / ow;
-  const int y0 = (int)(r % A.oh);
-  r /= A.oh;
-  const int z = (int)(r % A.od), b = (int)(r / A.od);
-  const int nq = 3 * H2 * W2 * cg;
-  for (int q = threadIdx.x; q < nq; q += kBlock) {
-    const int v = q / cg, g = q - v * cg;
-    const int lx = v % W2, ly = (v / W2) % H2, lz = v / (W2 * H2);
-    const int sz = z + lz - 1, sy = y0 + ly - 1, sx = lx - 1;
+  for (int it = 0; it < (CG * VOX + kBlock - 1) / kBlock; ++it) {  // all loads in flight
+    const int i = threadIdx.x + it * kBlock;
+    if (i >= CG * VOX) break;
+    const int v = i / CG, g = i % CG;
+    const int px = S * ox + v % HX - 1, py = S * oy + v / HX % HY - 1,
+              pz = S * oz + v / (HX * HY) - 1;
     uint4 val = {0u, 0u, 0u, 0u};
-    if (sz >= 0 && sz < A.sd && sy >= 0 && sy < A.sh && sx >= 0 && sx < A.sw) {
-      int c = g * 8;
-      const uint16_t* base = A.a;
-      int C = A.ca;
-      if (c >= A.ca) {
-        base = A.b;
-        C = A.cb;
-        c -= A.ca;
-      }
-      const size_t sv = (((size_t)b * A.sd + sz) * A.sh + sy) * A.sw + sx;
-      val = *reinterpret_cast<const uint4*>(base + sv * C + c);
+    if ((unsigned)px < nx && (unsigned)py < ny && (unsigned)pz < nz &&
+        !(odd_zero && ((px | py | pz) & 1))) {
+      const int sv = ((b * A.sd + (pz >> half)) * A.sh + (py >> half)) * A.sw + (px >> half);
+      const int c = 8 * g;
+      val = *reinterpret_cast<const uint4*>(c < A.ca ? A.a + (size_t)sv * A.ca + c
+                                                     : A.b + (size_t)sv * A.cb + c - A.ca);
     }
-    s_in[q] = val;
+    s_in[g * VOX + v] = val;
   }
   __syncthreads();
-  const int64_t mbase = blk0 + wave * (16 * MB);
-  int vy[MB], vx[MB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i) {
-    const int ml = wave * (16 * MB) + i * 16 + (lane & 15);
-    vy[i] = ml / ow;
-    vx[i] = ml - vy[i] * ow;
-  }
   f32x4 acc[MB][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int kq = 8 * (lane >> 4);
-  const uint4* __restrict__ W = A.w;
-  for (int ch = 0; ch < A.nchunk; ++ch) {
-    const int k0 = ch * 32 + kq;
-    const bool kin = k0 < A.ktot;
-    const int t = kin ? (k0 >> A.lcin) : 0, g = (k0 & (A.cin - 1)) >> 3;
-    const int tz = t / 9, ty = (t / 3) % 3, tx = t % 3;
-    bf16x8 af[MB];
+  // the wave's first row, and the lane's voxel and channel group in it
+  const int y0 = wave * MB % BY, z0 = wave * MB / BY, quarter = lane >> 4;
+  const int base = ((S * z0 * HY + S * y0) * HX + S * (lane & 15)) +
+                   (CIN >= 32 ? quarter : CIN == 16 ? quarter & 1 : 0) * VOX;
+  const uint4* __restrict__ W = A.w + (size_t)j0 * kWave + lane;
+  auto tap = [](int t) { return ((t / 9) * HY + (t / 3) % 3) * HX + t % 3; };
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch) {
+    bf16x8 bw[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) bw[j] = as_bf16x8(W[(ch * A.nb + j) * kWave]);
+    // the lane's k: taps t .. t + 32 / CIN - 1 by lane quarter
+    const int t = ch * 32 / CIN;
+    int at = base;
+    bool pad = false;  // past the last tap
+    if (CIN >= 32) {
+      at += tap(t) + (CIN == 64 ? (ch & 1) * 4 * VOX : 0);
+    } else if (CIN == 16) {
+      at += quarter < 2 ? tap(t) : tap(t + 1 < 27 ? t + 1 : t);
+      pad = t + 1 >= 27 && quarter >= 2;
+    } else {
+      const int far = quarter < 2 ? (quarter == 0 ? tap(t) : tap(t + 1))
+                                  : (quarter == 2 ? tap(t + 2) : tap(t + 3 < 27 ? t + 3 : t));
+      at += far;
+      pad = t + 3 >= 27 && quarter == 3;
+    }
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-      const uint4 v = kin ? s_in[((tz * H2 + vy[i] + ty) * W2 + vx[i] + tx) * cg + g]
-                          : uint4{0u, 0u, 0u, 0u};
-      af[i] = as_bf16x8(v);
-    }
+      uint4 x = s_in[at + i * S * HX];
+      if (pad) x = uint4{0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const bf16x8 bw = as_bf16x8(W[((size_t)ch * NB + j) * kWave + lane]);
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bw, acc[i][j], 0, 0, 0);
+      for (int j = 0; j < NB; ++j)
+        acc[i][j] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[j], as_bf16x8(x), acc[i][j], 0, 0, 0);
     }
   }
-  conv_epilogue<MB, NB>(A, acc, mbase, lane);
-}
-
-// LDS bytes k_conv_lds<MB, *> needs for A, or 0 where it does not apply.
-inline size_t conv_lds_bytes(const ConvArgs& A, int MB) {
-  const int block = (kBlock / kWave) * 16 * MB;
-  if (A.mode != kGatherPlain || A.stride != 1 || A.ow <= 0 || block % A.ow != 0) return 0;
-  const int R = block / A.ow;
-  if (A.oh % R != 0 || A.sd != A.od || A.sh != A.oh || A.sw != A.ow) return 0;
-  const size_t bytes = (size_t)3 * (R + 2) * (A.ow + 2) * (A.cin / 8) * 16;
-  return bytes <= 65536 ? bytes : 0;
+  // lane: voxel lane % 16 of its row, channels 4 (lane / 16) .. + 3 of a block
+  const int x = ox + (lane & 15), z = oz + z0;
+  if (x >= A.ow || z >= A.od) return;
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int y = oy + y0 + i;
+    if (y >= A.oh) continue;
+    const int n = (z * A.oh + y) * A.ow + x;
+    const int m = b * (A.od * A.oh * A.ow) + n;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) conv_store(A, acc[i][j], m, b, n, (j0 + j) * 16 + 4 * quarter);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1114,26 +1096,44 @@ class Net {
     return A;
   }
 
-  hipError_t launch_conv(const ConvArgs& A) {
-    const int64_t M = (int64_t)A.batch * A.od * A.oh * A.ow;
-    const unsigned blocks = (unsigned)((M + 127) / 128);
-    // (4 tiles per wave, 256-voxel blocks, measured no faster than k_conv)
-    if (const size_t lds = conv_lds_bytes(A, 2)) {
-      switch (A.nb) {
-        case 1: k_conv_lds<2, 1><<<blocks, kBlock, lds, stream_>>>(A); break;
-        case 2: k_conv_lds<2, 2><<<blocks, kBlock, lds, stream_>>>(A); break;
-        case 4: k_conv_lds<2, 4><<<blocks, kBlock, lds, stream_>>>(A); break;
-        default: return hipErrorInvalidValue;
-      }
+  // Bricks: 512 voxels (8 rows x 4 planes) where that leaves more than 600
+  // workgroups, else 128, else 64 with the output channels split over
+  // workgroups too: a workgroup waits for its staging, and only others on its
+  // compute unit cover that, while small bricks load more halo (64 input
+  // channels or stride 2: at most 128 voxels, for their LDS).  Forward pass at
+  // 64^3 / 57x41x50 with two samples: 181 / 210 us with lines at 256 and 128
+  // workgroups, 165 / 178 with 600 for the first, 157 / 192 with 600 for the
+  // second; the batch-4 training step is the same with each.
+  template <int CIN, int NB, int S>
+  hipError_t launch_conv_t(const ConvArgs& A) {
+    auto run = [&](auto kernel, int by, int bz, int groups) {
+      const int64_t n = (int64_t)((A.ow + kConvX - 1) / kConvX) * ((A.oh + by - 1) / by) *
+                        ((A.od + bz - 1) / bz) * A.batch;
+      kernel<<<dim3((unsigned)n, groups), kBlock, 0, stream_>>>(A);
       return hipGetLastError();
+    };
+    const int64_t rows = (int64_t)((A.ow + kConvX - 1) / kConvX) * A.oh * A.od * A.batch;
+    if constexpr (S == 1 && CIN < 64) {
+      if (rows / 32 > 600) return run(k_conv<CIN, NB, S, 8, 4>, 8, 4, 1);
     }
-    switch (A.nb) {
-      case 1: k_conv<2, 1><<<blocks, kBlock, 0, stream_>>>(A); break;
-      case 2: k_conv<2, 2><<<blocks, kBlock, 0, stream_>>>(A); break;
-      case 4: k_conv<2, 4><<<blocks, kBlock, 0, stream_>>>(A); break;
+    if (rows / 8 > 600) return run(k_conv<CIN, NB, S, 4, 2>, 4, 2, 1);
+    return run(k_conv<CIN, 1, S, 4, 1>, 4, 1, NB);
+  }
+
+  hipError_t launch_conv(const ConvArgs& A) {
+    switch (1000 * A.stride + 10 * A.cin + A.nb) {
+      case 1081: return launch_conv_t<8, 1, 1>(A);
+      case 1161: return launch_conv_t<16, 1, 1>(A);
+      case 1162: return launch_conv_t<16, 2, 1>(A);
+      case 1321: return launch_conv_t<32, 1, 1>(A);
+      case 1322: return launch_conv_t<32, 2, 1>(A);
+      case 1324: return launch_conv_t<32, 4, 1>(A);
+      case 1642: return launch_conv_t<64, 2, 1>(A);
+      case 1644: return launch_conv_t<64, 4, 1>(A);
+      case 2162: return launch_conv_t<16, 2, 2>(A);
+      case 2324: return launch_conv_t<32, 4, 2>(A);
       default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
   }
 
   hipError_t run_forward(const uint16_t* x, int batch, float* out) {

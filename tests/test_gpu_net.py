@@ -387,3 +387,22 @@ def test_weight_gradients_of_rows_too_wide_for_lds():
     for name, *_ in onet.LAYERS:
         for part in (".W", ".b"):
             assert rel_err(got[name + part], ref[name + part]) < 4.4e-2, name + part
+
+
+@pytest.mark.parametrize("dims,batch", [((16, 8, 4), 1), ((17, 9, 5), 2), ((15, 1, 3), 1),
+                                        ((64, 65, 33), 4), ((70, 40, 36), 8)])
+def test_forward_at_brick_edges(dims, batch):
+    """The convolution's bricks of 64, 128 and 512 voxels (the last two sizes
+    take the larger ones at their finer levels), at, one past and below their
+    edges, at the gate of the forward test above."""
+    from paper_1603_08161_amd import Net
+    v = _params(21)
+    nt = Net(dims, max_batch=batch)
+    nt.set_params(v)
+    bits = _input(22, dims, batch)
+    out = nt.forward(bits, batch=batch)
+    p = _oracle_params(v)
+    n = dims[0] * dims[1] * dims[2]
+    b = batch - 1
+    ref, _ = _oracle_forward(p, bits[b], dims)
+    assert rel_err(out[b], ref.reshape(3, n)) < 1e-2
