@@ -869,37 +869,6 @@ __device__ __forceinline__ unsigned long long slot_bits(double v) {
   return v != v ? 0x7ff8000000000000ull : (unsigned long long)__double_as_longlong(v);
 }
 
-__device__ __forceinline__ double pack_double(unsigned lo, unsigned hi) {
-  return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
-}
-
-// Wave sums of four values at once, the sum of v[k] left in the lanes with
-// lane % 4 == k.  The pairs added are those of wave_sum (every lane of a
-// group holds the same partial sum there), so the sums have the same bits;
-// sharing the lanes takes 7 additions instead of 28.
-__device__ __forceinline__ double wave_sum4(const double (&v)[4]) {
-  const bool o1 = threadIdx.x & 1, o2 = threadIdx.x & 2;
-  double a = o1 ? v[1] : v[0], b = o1 ? v[3] : v[2];
-  a += dpp_move<0xB1>(o1 ? v[0] : v[1]);  // lane ^ 1
-  b += dpp_move<0xB1>(o1 ? v[2] : v[3]);
-  double s = o2 ? b : a;
-  s += dpp_move<0x4E>(o2 ? a : b);                     // lane ^ 2
-  s += dpp_move<0x1B>(dpp_move<0x141>(s));             // lane ^ 4
-  s += dpp_move<0x128>(s);                             // lane ^ 8
-  // rows of 16 lanes: (row 0 + row 1) + (row 2 + row 3); the swaps leave the
-  // lower row (half) of each pair in the first result, the upper in the second
-  const long long e = __double_as_longlong(s);
-  const auto l16 = __builtin_amdgcn_permlane16_swap((unsigned)e, (unsigned)e, false, false);
-  const auto h16 = __builtin_amdgcn_permlane16_swap((unsigned)(e >> 32), (unsigned)(e >> 32),
-                                                    false, false);
-  s = pack_double(l16[0], h16[0]) + pack_double(l16[1], h16[1]);
-  const long long c = __double_as_longlong(s);
-  const auto l32 = __builtin_amdgcn_permlane32_swap((unsigned)c, (unsigned)c, false, false);
-  const auto h32 = __builtin_amdgcn_permlane32_swap((unsigned)(c >> 32), (unsigned)(c >> 32),
-                                                    false, false);
-  return pack_double(l32[0], h32[0]) + pack_double(l32[1], h32[1]);
-}
-
 // The n-th node of a tile's halo shell: the two z faces, then the rings of
 // the layers between them.
 template <typename TL>

@@ -190,11 +190,23 @@ __device__ __forceinline__ void rigid_terms(const Pair& a, const double q[3], do
 }
 
 __device__ __forceinline__ void write_rigid_partials(double (&acc)[kRigidSums], double* partials) {
-  __shared__ double lds[kRigidSums * (kBlock / kWave)];
-  block_sum<kRigidSums>(acc, lds);
-  if (threadIdx.x == 0) {
+  constexpr int NW = kBlock / kWave;
+  __shared__ double lds[NW][kRigidStride];
+  const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
 #pragma unroll
-    for (int k = 0; k < kRigidSums; ++k) partials[(size_t)blockIdx.x * kRigidStride + k] = acc[k];
+  for (int k = 0; k < kRigidStride; k += 4) {
+    double v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = k + j < kRigidSums ? acc[k + j < kRigidSums ? k + j : 0] : 0.0;
+    const double x = wave_sum4(v);
+    if (lane < 4) lds[wid][k + lane] = x;
+  }
+  __syncthreads();
+  if (threadIdx.x < kRigidSums) {
+    double x = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) x += lds[w][threadIdx.x];
+    partials[(size_t)blockIdx.x * kRigidStride + threadIdx.x] = x;
   }
 }
 
@@ -351,7 +363,10 @@ hipError_t launch_rigid_reduce_lattice(const CamAssoc& c, const float* depth,
 
 // One workgroup: the partial sums in fixed order (value k by 8 threads, each
 // over every 8th workgroup, then the 8 in order), the Cholesky factorisation
-// of the 6x6 system, the step xi = -H^-1 g and the pose update.
+// of the 6x6 system, the step xi = -H^-1 g and the pose update.  Bound by
+// latency: 16 loads are in flight per thread, and every loop of the serial part
+// is unrolled, which keeps its matrices in registers (rolled loops indexed
+// them in scratch memory: 16.0 us per launch for 390 workgroups, now 6.1).
 __global__ __launch_bounds__(kBlock) void k_rigid_solve(const double* __restrict__ partials,
                                                         int blocks, double* pose, double* hist) {
   __shared__ double part[8][kRigidStride];
@@ -359,11 +374,13 @@ __global__ __launch_bounds__(kBlock) void k_rigid_solve(const double* __restrict
   const int k = threadIdx.x % kRigidStride, s = threadIdx.x / kRigidStride;
   double acc = 0.0;
   if (k < kRigidSums)
+#pragma unroll 16
     for (int b = s; b < blocks; b += 8) acc += partials[(size_t)b * kRigidStride + k];
   part[s][k] = acc;
   __syncthreads();
   if (threadIdx.x < kRigidSums) {
     double t = 0.0;
+#pragma unroll
     for (int j = 0; j < 8; ++j) t += part[j][threadIdx.x];
     tot[threadIdx.x] = t;
   }
@@ -376,40 +393,54 @@ __global__ __launch_bounds__(kBlock) void k_rigid_solve(const double* __restrict
   }
   double H[6][6], g[6];
   int e = 0;
+#pragma unroll
   for (int i = 0; i < 6; ++i)
+#pragma unroll
     for (int j = i; j < 6; ++j) {
       H[i][j] = tot[e];
       H[j][i] = tot[e];
       ++e;
     }
+#pragma unroll
   for (int i = 0; i < 6; ++i) g[i] = tot[21 + i];
   if (count < 6.0) return;
   double dmax = 0.0;
+#pragma unroll
   for (int i = 0; i < 6; ++i) dmax = fmax(dmax, H[i][i]);
   if (!(dmax > 0.0)) return;
   // H = L L^T
   double L[6][6];
+#pragma unroll
   for (int i = 0; i < 6; ++i)
+#pragma unroll
     for (int j = 0; j < 6; ++j) L[i][j] = 0.0;
+#pragma unroll
   for (int j = 0; j < 6; ++j) {
     double dj = H[j][j];
+#pragma unroll
     for (int q = 0; q < j; ++q) dj -= L[j][q] * L[j][q];
     if (!(dj > 1e-8 * dmax)) return;  // numerically singular: the pose stays
     L[j][j] = sqrt(dj);
+#pragma unroll
     for (int i = j + 1; i < 6; ++i) {
       double v = H[i][j];
+#pragma unroll
       for (int q = 0; q < j; ++q) v -= L[i][q] * L[j][q];
       L[i][j] = v / L[j][j];
     }
   }
   double y[6], xi[6];
+#pragma unroll
   for (int i = 0; i < 6; ++i) {
     double v = -g[i];
+#pragma unroll
     for (int q = 0; q < i; ++q) v -= L[i][q] * y[q];
     y[i] = v / L[i][i];
   }
+#pragma unroll
   for (int i = 5; i >= 0; --i) {
     double v = y[i];
+#pragma unroll
     for (int q = i + 1; q < 6; ++q) v -= L[q][i] * xi[q];
     xi[i] = v / L[i][i];
   }
@@ -420,16 +451,22 @@ __global__ __launch_bounds__(kBlock) void k_rigid_solve(const double* __restrict
     const double ax = xi[0] / th, ay = xi[1] / th, az = xi[2] / th;
     const double K[3][3] = {{0.0, -az, ay}, {az, 0.0, -ax}, {-ay, ax, 0.0}};
     const double sn = sin(th), cs = 1.0 - cos(th);
+#pragma unroll
     for (int i = 0; i < 3; ++i)
+#pragma unroll
       for (int j = 0; j < 3; ++j) {
         const double kk = K[i][0] * K[0][j] + K[i][1] * K[1][j] + K[i][2] * K[2][j];
         Q[i][j] = Q[i][j] + sn * K[i][j] + cs * kk;
       }
   }
   double R[9], t[3];
+#pragma unroll
   for (int i = 0; i < 9; ++i) R[i] = pose[i];
+#pragma unroll
   for (int i = 0; i < 3; ++i) t[i] = pose[9 + i];
+#pragma unroll
   for (int i = 0; i < 3; ++i) {
+#pragma unroll
     for (int j = 0; j < 3; ++j)
       pose[3 * i + j] = Q[i][0] * R[j] + Q[i][1] * R[3 + j] + Q[i][2] * R[6 + j];
     pose[9 + i] = Q[i][0] * t[0] + Q[i][1] * t[1] + Q[i][2] * t[2] + xi[3 + i];
