@@ -263,8 +263,10 @@ int vd_solve_frame(vd_lattice* l, const vd_solve_opts* opts, vd_solve_report* re
  * workgroups of all lattices of one precision, with per-lattice reductions;
  * the float64 lattices, if any, form a second part that runs on a
  * library-owned stream forked from the lattices' stream and joined back into
- * it, so both parts overlap on the GPU.  The batch does not own the handles:
- * they must outlive it.  Creating it sets every handle's stencil tile, per
+ * it, so both parts overlap on the GPU, unless both have levels whose CG
+ * solves are one launch (those hold whole compute units until their lattice
+ * is done; the parts then run one after the other).  The batch does not own
+ * the handles: they must outlive it.  Creating it sets every handle's stencil tile, per
  * level, to the tile of the largest lattice of its part at that level.
  * VD_EINVAL on mismatched handles. */
 int vd_batch_create(vd_lattice* const* lattices, int32_t n, vd_batch** out);

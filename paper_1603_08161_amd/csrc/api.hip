@@ -986,6 +986,8 @@ class Solver final : public ISolver {
   const vd_lattice_desc& desc() const { return desc_; }
   int level_nodes(int l) const { return lv_[l].N; }
   int level_tile(int l) const { return lv_[l].tile; }
+  int level_capacity(int l) const { return loop_cap_[lv_[l].tile]; }
+  bool level_loop(int l) const { return cg_loop(lv_[l]); }
   void force_tile(int l, int kind) {
     if (lv_[l].tile == kind) return;
     lv_[l].tile = kind;
@@ -1693,6 +1695,7 @@ class IBatch {
  public:
   virtual ~IBatch() {}
   // Queue one frame of every lattice on `s` (graph replay or eager).
+  virtual bool one_launch() const = 0;  // some level's solves are one launch each
   virtual int launch(const vd_solve_opts* o, hipStream_t s) = 0;
   // Final energies (4 per lattice) after the frame finished.
   virtual int energies(double* e) = 0;
@@ -1735,6 +1738,12 @@ class Batch final : public IBatch {
     }
     gens_.assign(n_, -1);
     return VD_OK;
+  }
+
+  bool one_launch() const override {
+    for (int l = 0; l < L_; ++l)
+      if (loops(l)) return true;
+    return false;
   }
 
   int launch(const vd_solve_opts* o, hipStream_t s) override {
@@ -1791,15 +1800,52 @@ class Batch final : public IBatch {
     LevelView<T> first{};
   };
 
+  // Whether the position solves of level l run as one launch.
+  bool loops(int l) const {
+    for (const auto* h : h_)
+      if (!h->level_loop(l)) return false;
+    return true;
+  }
+
+  // The lattices in launch order.  A lattice of a one-launch solve waits until
+  // all its tiles are resident, and tiles become resident in launch order:
+  // groups that fill the GPU (first fit, largest first) leave the fewest
+  // compute units waiting for an earlier lattice to end.
+  std::vector<int> launch_order() const {
+    std::vector<int> by_size(n_);
+    for (int b = 0; b < n_; ++b) by_size[b] = b;
+    const int F = L_ - 1;
+    if (!loops(F)) return by_size;
+    auto tiles = [&](int b) { return h_[b]->level_view(F).ntiles; };
+    std::stable_sort(by_size.begin(), by_size.end(),
+                     [&](int a, int b) { return tiles(a) > tiles(b); });
+    std::vector<std::vector<int>> groups;
+    std::vector<int> left;
+    for (const int b : by_size) {
+      size_t g = 0;
+      while (g < groups.size() && left[g] < tiles(b)) ++g;
+      if (g == groups.size()) {
+        groups.emplace_back();
+        left.push_back(h_[0]->level_capacity(F));
+      }
+      groups[g].push_back(b);
+      left[g] -= tiles(b);
+    }
+    std::vector<int> order;
+    for (const auto& g : groups) order.insert(order.end(), g.begin(), g.end());
+    return order;
+  }
+
   // Device tables of the lattices' level views and the first workgroup of
   // each lattice for every workgroup kind (rebuilt when a handle reallocates).
   int build_tables() {
+    const std::vector<int> order = launch_order();
     for (int l = 0; l < L_; ++l) {
       std::vector<LevelView<T>> views(n_);
       std::vector<int> st[4];
       for (int k = 0; k < 4; ++k) st[k].assign(n_ + 1, 0);
       for (int b = 0; b < n_; ++b) {
-        const LevelView<T> V = h_[b]->level_view(l);
+        const LevelView<T> V = h_[order[b]]->level_view(l);
         views[b] = V;
         const int cnt[4] = {V.ntiles, node_blocks(V.N), energy_blocks(V.rblocks, V.N), 1};
         for (int k = 0; k < 4; ++k) st[k][b + 1] = st[k][b] + cnt[k];
@@ -1874,7 +1920,7 @@ class Batch final : public IBatch {
           if (rc != VD_OK) break;
           VD_TRY(hipEventRecord(e0, s));
           VD_TRY(launch_stencil<T>(kModeRhs, D(l, kTiles), nullptr, nullptr, s));
-          for (int m = 0; m < iters; ++m) VD_TRY(launch_cg<T>(m, D(l, kTiles), s));
+          VD_CHECK(solve(l, iters, false, s));
           VD_TRY(hipEventRecord(e1, s));
           VD_TRY(hipEventSynchronize(e1));
           VD_TRY(hipEventElapsedTime(&ms, e0, e1));
@@ -1905,6 +1951,26 @@ class Batch final : public IBatch {
     return rc;
   }
 
+  // The CG solve of level l: one launch where every lattice allows it (25
+  // float32 lattices of 33 .. 64 nodes per axis: 154 us per iteration of the
+  // finest level against 165 with one launch per iteration, which streams
+  // every row and vector again; fewer or smaller lattices gain more).  A
+  // lattice that is launched behind others waits for one of their solves, so
+  // the limit of that wait grows with the iterations (50 us each).
+  int solve(int l, int pcg, bool on, hipStream_t s) {
+    if (pcg > 0 && loops(l))
+      return timer_.timed(on, VD_PROF_CG_LOOP, s, [&] {
+        return launch_cg_loop<T>(pcg, D(l, kTiles), s, nullptr, kAssembleTicks + 5000 * std::min(pcg, 10000));
+      });
+    for (int m = 0; m < pcg; ++m)
+      VD_CHECK(timer_.timed(on, VD_PROF_CG_A, s,
+                            [&] { return launch_cg<T>(m, D(l, kTiles), s); }));
+    if (pcg > 0)
+      VD_CHECK(timer_.timed(on, VD_PROF_CG_B, s,
+                            [&] { return launch_cg_final<T>(pcg - 1, D(l, kNodes), s); }));
+    return VD_OK;
+  }
+
   // The frame schedule of Solver::enqueue_frame with every launch batched.
   int enqueue(int reset, hipStream_t s) {
     const int F = L_ - 1;
@@ -1927,12 +1993,7 @@ class Batch final : public IBatch {
         VD_CHECK(timer_.timed(on, VD_PROF_GRADIENT, s, [&] {
           return launch_stencil<T>(kModeRhs, D(l, kTiles), nullptr, nullptr, s);
         }));
-        for (int m = 0; m < pcg; ++m)
-          VD_CHECK(timer_.timed(on, VD_PROF_CG_A, s,
-                                [&] { return launch_cg<T>(m, D(l, kTiles), s); }));
-        if (pcg > 0)
-          VD_CHECK(timer_.timed(on, VD_PROF_CG_B, s,
-                                [&] { return launch_cg_final<T>(pcg - 1, D(l, kNodes), s); }));
+        VD_CHECK(solve(l, pcg, on, s));
         VD_CHECK(timer_.timed(on, VD_PROF_ROTATION, s,
                               [&] { return launch_polar<T>(D(l, kNodes), s); }));
       }
@@ -1969,7 +2030,8 @@ struct vd_lattice {
 // A batch holds up to two single-precision batches: the float32 lattices
 // (part 0) and the float64 ones (part 1), each with the caller's positions of
 // its lattices.  Part 1 runs on a library-owned stream, forked from and
-// joined back into the lattices' stream, so both overlap on the GPU.
+// joined back into the lattices' stream, so both overlap on the GPU, or after
+// part 0 where both have one-launch CG solves.
 struct vd_batch {
   vd::IBatch* part[2] = {nullptr, nullptr};
   std::vector<int> index[2];
@@ -2123,7 +2185,14 @@ int vd_batch_create(vd_lattice* const* ls, int32_t n, vd_batch** out) {
 int vd_batch_solve(vd_batch* b, const vd_solve_opts* o, double* energies) {
   if (!b) return VD_EINVAL;
   if (o && (o->init_delta || o->energy_target != 0.0)) return VD_EINVAL;
-  if (b->part[0] && b->part[1]) {
+  if (b->part[0] && b->part[1] && b->part[0]->one_launch() && b->part[1]->one_launch()) {
+    // both parts' solves hold whole compute units and wait for their tiles:
+    // beside each other they would wait for one another
+    for (int k = 0; k < 2; ++k) {
+      const int rc = b->part[k]->launch(o, b->stream);
+      if (rc != VD_OK) return rc;
+    }
+  } else if (b->part[0] && b->part[1]) {
     if (hipEventRecord(b->fork, b->stream) != hipSuccess ||
         hipStreamWaitEvent(b->side, b->fork, 0) != hipSuccess)
       return VD_EHIP;

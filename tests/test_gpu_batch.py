@@ -145,3 +145,21 @@ def test_batch_tuner_keeps_the_state_and_the_bits(graph):
         rep = ref.solve_frame(reset=True, report=True)
         np.testing.assert_array_equal(e, rep["energy"])
         np.testing.assert_array_equal(lat.get_state()[0], ref.get_state()[0])
+
+
+@pytest.mark.parametrize("tile", [4, 5])
+def test_batch_of_more_tiles_than_the_gpu_holds(tile):
+    """One-launch solves of lattices that fill the GPU more than twice over
+    (the largest alone fills it; later ones become resident piecemeal while
+    earlier ones run): the bits of one launch per iteration."""
+    from paper_1603_08161_amd import Batch
+    scenes = [make_batch_lattice(700 + k, n, 1500, 20, gn=1, pcg=5)
+              for k, n in enumerate([50, 64, 39, 57, 33])]
+    kw = {"tiles": (tile, tile, tile)}
+    lats = [make_lattice(s, **kw) for s in scenes]
+    E = Batch(lats).solve(reset=True, energies=True)
+    for s, lat, e in zip(scenes, lats, E):
+        ref = make_lattice(s, iterative=True, **kw)
+        rep = ref.solve_frame(reset=True, report=True)
+        np.testing.assert_array_equal(e, rep["energy"])
+        np.testing.assert_array_equal(lat.get_state()[0], ref.get_state()[0])
