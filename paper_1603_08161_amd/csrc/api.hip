@@ -161,6 +161,10 @@ struct LevelData {
   // constraint rows and cell cache
   int cap_rows = 0, cap_cells = 0;
   int *row_cell = nullptr, *sorted = nullptr, *seg_start = nullptr, *active_cell = nullptr;
+  // scratch of the build: sorted rows' cells, the sort, counts per block
+  unsigned* keys = nullptr;
+  unsigned char *sort_temp = nullptr, *touched = nullptr;
+  int *heads = nullptr, *node_counts = nullptr;
   T *row_f = nullptr, *row_sn = nullptr, *row_rho = nullptr, *K = nullptr, *bcell = nullptr;
   int ntiles = 0;     // workgroups of the current tile kind
   int max_tiles = 0;  // most workgroups over all tile kinds (partials capacity)
@@ -314,6 +318,7 @@ class Solver final : public ISolver {
       VD_CHECK(pool_.alloc(&v.rot, 9 * N));
       VD_CHECK(pool_.alloc(&v.cell_map, (size_t)v.ncell));
       VD_CHECK(pool_.alloc(&v.node_slot, N));
+      VD_CHECK(pool_.alloc(&v.node_counts, (size_t)build_node_blocks(v.N)));
       VD_CHECK(pool_.alloc(&v.A27r, (size_t)kA27Row * N));
       VD_CHECK(pool_.alloc(&v.sc, 1));
       VD_TRY(hipMemsetAsync(v.sc, 0, sizeof(Scalars), stream_));
@@ -321,6 +326,7 @@ class Solver final : public ISolver {
       VD_CHECK(pool_.alloc(&v.ap2, 3 * N));
       if (desc_.flags & VD_FLAG_ACTIVE_SET) {
         VD_CHECK(pool_.alloc(&v.act, N));
+        VD_CHECK(pool_.alloc(&v.touched, N));
         VD_TRY(hipMemsetAsync(v.act, 1, N, stream_));
       }
       VD_CHECK(pool_.alloc(&v.scg[0], 4 * (size_t)v.max_tiles));
@@ -332,7 +338,6 @@ class Solver final : public ISolver {
       VD_TRY(cg_loop_capacity<T>(k, (desc_.flags & VD_FLAG_ACTIVE_SET) != 0, &loop_cap_[k]));
     if ((desc_.flags & VD_FLAG_PROFILE) && (desc_.flags & VD_FLAG_GRAPH))
       VD_CHECK(pool_.alloc(&stamps_, 2 * kMaxStamped));  // written by captured CG launches
-    VD_CHECK(pool_.alloc(&node_flags_, (size_t)finest().N));
     // the canonical TSDF on the finest grid (Sec. 4): D = W = 0, never observed
     VD_CHECK(pool_.alloc(&tsdf_d_, (size_t)finest().N));
     VD_CHECK(pool_.alloc(&tsdf_w_, (size_t)finest().N));
@@ -345,7 +350,6 @@ class Solver final : public ISolver {
       VD_CHECK(pool_.alloc(&known_, (size_t)finest().N));
       VD_CHECK(pool_.alloc(&fresh_, (size_t)finest().N));
     }
-    VD_CHECK(pool_.alloc(&node_scan_, (size_t)finest().N));
     VD_CHECK(pool_.alloc(&d_flags_, 4));
     VD_TRY(hipHostMalloc((void**)&h_flags_, 4 * sizeof(int), hipHostMallocDefault));
     VD_TRY(hipHostMalloc((void**)&h_sc_, sizeof(Scalars), hipHostMallocDefault));
@@ -405,29 +409,28 @@ class Solver final : public ISolver {
   int build_levels(const RawConstraints& raw, int C, int S, bool structure) {
     const int rows = C + 3 * S;
     if (structure) VD_CHECK(ensure_rows(rows));
+    BuildLevels<T> B{};
+    SortLevels so{};
+    B.n = so.n = L_;
+    so.rows = rows;
+    so.counted = 1;
     for (int l = 0; l < L_; ++l) {
-      LevelData<T>& v = lv_[l];
-      const LevelView<T> V = v.view(desc_.w_arap);
-      const RowView<T> R = v.rows_view(rows, C);
-      VD_TRY(launch_rows<T>(raw, V, R, desc_.origin, desc_.w_dense, desc_.w_sparse, keys_in_,
-                            vals_in_, stream_));
-      if (structure) {
-        VD_TRY(sort_pairs(sort_temp_, sort_temp_bytes_, keys_in_, keys_out_, vals_in_, v.sorted,
-                          rows, bits_for(v.ncell), stream_));
-        VD_TRY(launch_heads(keys_out_, rows, heads_, stream_));
-        VD_TRY(exclusive_scan(sort_temp_, sort_temp_bytes_, heads_, scan_, rows, stream_));
-        VD_TRY(launch_segments<T>(V, R, keys_out_, scan_, v.cell_map, v.ncell, stream_));
-      }
-      VD_TRY(launch_build_cells<T>(V, R, v.K, std::min(v.cap_cells, 8192), stream_));
-      VD_TRY(launch_node_flags<T>(V, node_flags_, stream_));
-      // the optimised set M: the isosurface points (corners of the cells
-      // holding samples) and their one-ring
-      if (v.act) VD_TRY(launch_dilate<T>(V, node_flags_, v.act, stream_));
-      VD_TRY(exclusive_scan(sort_temp_, sort_temp_bytes_, node_flags_, node_scan_, v.N, stream_));
-      VD_TRY(launch_assemble_nodes<T>(V, R, node_flags_, node_scan_, v.node_slot, v.A27r,
-                                      stream_));
-      VD_TRY(launch_set_counts(v.sc, rows, C, stream_));
+      const LevelData<T>& v = lv_[l];
+      SortLevel& q = so.level[l];
+      q = sort_level(v.sort_temp, v.cap_rows, bits_for(v.ncell));
+      q.kin = (const unsigned*)v.row_cell;
+      q.kout = v.keys;
+      q.vout = v.sorted;
+      so.passes = std::max(so.passes, q.passes);
+      BuildLevel<T>& b = B.level[l];
+      b.L = v.view(desc_.w_arap);
+      b.R = v.rows_view(rows, C);
+      b.ncell = v.ncell; b.cap_cells = v.cap_cells; b.cell_map = v.cell_map; b.K = v.K;
+      b.node_slot = v.node_slot; b.A27r = v.A27r; b.act = v.act; b.skeys = v.keys;
+      b.heads = v.heads; b.nodes = v.node_counts; b.touched = v.act ? v.touched : nullptr;
     }
+    VD_TRY(launch_build<T>(raw, B, so, desc_.origin, desc_.w_dense, desc_.w_sparse, structure,
+                           scan_temp_, scan_temp_bytes_, stream_));
     rows_ = rows;
     n_dense_ = C;
     have_constraints_ = true;
@@ -1469,19 +1472,13 @@ class Solver final : public ISolver {
   }
 
   int ensure_rows(int rows) {
-    if (rows > cap_rows_ || !keys_in_) {
+    if (rows > cap_rows_ || !scan_temp_) {
       VD_TRY(hipStreamSynchronize(stream_));
       const int cap = rows + rows / 4 + 256;
-      pool_.release(keys_in_); pool_.release(keys_out_); pool_.release(vals_in_);
-      pool_.release(heads_); pool_.release(scan_); pool_.release(sort_temp_);
-      VD_CHECK(pool_.alloc(&keys_in_, cap));
-      VD_CHECK(pool_.alloc(&keys_out_, cap));
-      VD_CHECK(pool_.alloc(&vals_in_, cap));
-      VD_CHECK(pool_.alloc(&heads_, cap));
-      VD_CHECK(pool_.alloc(&scan_, cap));
-      sort_temp_bytes_ = std::max({vd::sort_temp_bytes(cap), vd::scan_temp_bytes(cap),
-                                   vd::scan_temp_bytes(finest().N)});
-      VD_CHECK(pool_.alloc((unsigned char**)&sort_temp_, sort_temp_bytes_));
+      pool_.release(scan_temp_);
+      scan_temp_bytes_ = vd::scan_temp_bytes(
+          std::max(build_row_blocks(cap), build_node_blocks(finest().N)));
+      VD_CHECK(pool_.alloc((unsigned char**)&scan_temp_, scan_temp_bytes_));
       cap_rows_ = cap;
       ++alloc_gen_;
     }
@@ -1496,6 +1493,10 @@ class Solver final : public ISolver {
         VD_CHECK(pool_.alloc(&v.row_f, 3 * (size_t)cap));
         VD_CHECK(pool_.alloc(&v.row_sn, 3 * (size_t)cap));
         VD_CHECK(pool_.alloc(&v.row_rho, cap));
+        pool_.release(v.keys); pool_.release(v.heads); pool_.release(v.sort_temp);
+        VD_CHECK(pool_.alloc(&v.keys, cap));
+        VD_CHECK(pool_.alloc(&v.heads, (size_t)build_row_blocks(cap)));
+        VD_CHECK(pool_.alloc(&v.sort_temp, vd::sort_temp_bytes(cap)));
         v.cap_rows = cap;
         ++alloc_gen_;
       }
@@ -1618,18 +1619,14 @@ class Solver final : public ISolver {
   Pool pool_;
   int* d_flags_ = nullptr;
   int* h_flags_ = nullptr;
-  int* node_flags_ = nullptr;  // per-node scratch of the constraint build
-  int* node_scan_ = nullptr;
   Scalars* h_sc_ = nullptr;
   // staging of the raw constraints
   float *st_canon_ = nullptr, *st_target_ = nullptr, *st_normal_ = nullptr, *st_weight_ = nullptr,
         *st_scanon_ = nullptr, *st_starget_ = nullptr;
   int cap_dense_ = 0, cap_sparse_ = 0;
   // sort scratch
-  unsigned *keys_in_ = nullptr, *keys_out_ = nullptr;
-  int *vals_in_ = nullptr, *heads_ = nullptr, *scan_ = nullptr;
-  void* sort_temp_ = nullptr;
-  size_t sort_temp_bytes_ = 0;
+  void* scan_temp_ = nullptr;
+  size_t scan_temp_bytes_ = 0;
   int cap_rows_ = 0;
   int rows_ = 0, n_dense_ = 0;
   bool have_constraints_ = false;

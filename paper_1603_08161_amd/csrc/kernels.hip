@@ -5,6 +5,8 @@
 // numbers, which keeps float32 accurate even when the lattice sits far from
 // the world origin.  Every node vector is SoA [3][N] in x-fastest node order.
 
+#include <algorithm>
+
 #include "vd_device.h"
 #include "vd_kernels.h"
 
@@ -26,6 +28,9 @@ __constant__ unsigned char c_pair_b[36] = {0, 1, 2, 3, 4, 5, 6, 7, 1, 2, 3, 4, 5
                                            5, 6, 7, 3, 4, 5, 6, 7, 4, 5, 6, 7, 5, 6, 7, 6, 7, 7};
 __constant__ unsigned char c_comp_i[6] = {0, 0, 0, 1, 1, 2};
 __constant__ unsigned char c_comp_j[6] = {0, 1, 2, 1, 2, 2};
+
+// Workgroups of the cell cache per level: twice what is resident at once.
+constexpr int kCellBlocks = 1536;
 
 }  // namespace
 
@@ -81,13 +86,31 @@ hipError_t launch_validate(const RawConstraints& c, int nx0, int ny0, int nz0, d
 // One row per dense correspondence (eq. (2)) and three per sparse pair
 // (eq. (3): a point-to-point term is the sum of three axis-aligned
 // point-to-plane terms).  Row value: sn . sum_k alpha_k d_k - rho, with
-// sn = sqrt(w) * normal and rho = sn . (target - canonical).
+// sn = sqrt(w) * normal and rho = sn . (target - canonical).  With
+// `structure` also the cells' histogram of the first sort digit (block b's
+// rows are those of the sort's block b) and the cleared cell map.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_rows(RawConstraints c, LevelView<T> L, RowView<T> R,
+__global__ __launch_bounds__(kBlock) void k_rows(RawConstraints c, BuildLevels<T> B, SortLevels S,
                                                  double ox, double oy, double oz, double wd,
-                                                 double ws, unsigned* keys, int* vals) {
+                                                 double ws, int structure) {
+  const BuildLevel<T>& V = B.level[blockIdx.y];
+  const LevelView<T>& L = V.L;
+  const RowView<T>& R = V.R;
   const int rows = R.rows;
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < rows; i += gridDim.x * kBlock) {
+  __shared__ int h[kMaxBuckets];
+  const int buckets = 1 << S.level[blockIdx.y].digit_bits;
+  const bool counts = structure && (int)blockIdx.x * kRowTile < rows;
+  if (structure) {
+    for (int k = blockIdx.x * kBlock + threadIdx.x; k < V.ncell; k += gridDim.x * kBlock)
+      V.cell_map[k] = -1;
+    if (counts) {
+      for (int k = threadIdx.x; k < buckets; k += kBlock) h[k] = 0;
+      __syncthreads();
+    }
+  }
+  for (int j = threadIdx.x; j < kRowTile; j += kBlock) {
+    const int i = blockIdx.x * kRowTile + j;
+    if (i >= rows) break;
     double x[3], sn[3], rho;
     if (i < c.n_dense) {
       const size_t b = 3 * (size_t)i;
@@ -136,80 +159,104 @@ __global__ __launch_bounds__(kBlock) void k_rows(RawConstraints c, LevelView<T> 
     const int cell = cc[0] + (L.nx - 1) * (cc[1] + (L.ny - 1) * cc[2]);
     R.cell[i] = cell;
     R.rho[i] = (T)rho;
-    keys[i] = (unsigned)cell;
-    vals[i] = i;
+    if (structure) atomicAdd(&h[cell & (buckets - 1)], 1);
+  }
+  if (counts) {
+    __syncthreads();
+    int* hist = S.level[blockIdx.y].hist + (size_t)blockIdx.x * buckets;
+    for (int k = threadIdx.x; k < buckets; k += kBlock) hist[k] = h[k];
   }
 }
 
+// heads[b] = rows of block b of the sorted rows that are the first of a cell.
 template <typename T>
-hipError_t launch_rows(const RawConstraints& c, const LevelView<T>& L, const RowView<T>& R,
-                       const double* o, double wd, double ws, unsigned* keys, int* vals,
-                       hipStream_t s) {
-  if (R.rows == 0) return hipSuccess;
-  int grid = blocks_for(R.rows);
-  if (grid > 4096) grid = 4096;
-  k_rows<T><<<grid, kBlock, 0, s>>>(c, L, R, o[0], o[1], o[2], wd, ws, keys, vals);
-  return hipGetLastError();
+__global__ __launch_bounds__(kBlock) void k_heads(BuildLevels<T> B) {
+  const BuildLevel<T>& V = B.level[blockIdx.y];
+  const unsigned* __restrict__ keys = V.skeys;
+  int heads = 0;
+  for (int j = threadIdx.x; j < kRowTile; j += kBlock) {
+    const int i = blockIdx.x * kRowTile + j;
+    heads += i < V.R.rows && (i == 0 || keys[i] != keys[i - 1]);
+  }
+  int total;
+  (void)block_exclusive<kBlock / kWave>(heads, &total);
+  if (threadIdx.x == 0) V.heads[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(kBlock) void k_heads(const unsigned* skeys, int n, int* heads) {
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock)
-    heads[i] = (i == 0 || skeys[i] != skeys[i - 1]) ? 1 : 0;
+// Sum of counts[0 .. b) (all threads get it): a block adds up what the blocks
+// before it counted, 4 bytes each, instead of a scan of three launches; above
+// kDirectBlocks the counts are scanned first.
+constexpr int kDirectBlocks = 4096;
+__device__ __forceinline__ int blocks_before(const int* counts, int b, bool scanned) {
+  if (scanned) return counts[b];
+  int v = 0, total;
+  for (int k = threadIdx.x; k < b; k += kBlock) v += counts[k];
+  (void)block_exclusive<kBlock / kWave>(v, &total);
+  return total;
 }
 
-hipError_t launch_heads(const unsigned* skeys, int n, int* heads, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  int grid = blocks_for(n);
-  if (grid > 4096) grid = 4096;
-  k_heads<<<grid, kBlock, 0, s>>>(skeys, n, heads);
-  return hipGetLastError();
-}
-
-__global__ __launch_bounds__(kBlock) void k_fill_int(int* p, int v, int n) {
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = v;
-}
-
-// Active cells = distinct keys of the sorted rows.  `scan` is the exclusive
-// prefix sum of the head flags, i.e. the active index of each head.
+// Active cells = distinct keys of the sorted rows, in their order.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_segments(RowView<T> R, const unsigned* skeys,
-                                                     const int* scan, int* cell_map, Scalars* sc) {
+__global__ __launch_bounds__(kBlock) void k_segments(BuildLevels<T> B, int scanned) {
+  const BuildLevel<T>& V = B.level[blockIdx.y];
+  const RowView<T>& R = V.R;
+  const unsigned* __restrict__ keys = V.skeys;
   const int n = R.rows;
   if (n == 0) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-      sc->n_active = 0;
+      V.L.sc->n_active = 0;
       R.seg_start[0] = 0;
     }
     return;
   }
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-    const bool head = (i == 0 || skeys[i] != skeys[i - 1]);
-    if (head) {
-      const int a = scan[i];
+  constexpr int PER = kRowTile / kBlock;
+  const int i0 = blockIdx.x * kRowTile + threadIdx.x * PER;
+  unsigned key[PER + 1];
+  key[0] = i0 > 0 && i0 <= n ? keys[i0 - 1] : 0u;
+  int heads = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    key[k + 1] = i0 + k < n ? keys[i0 + k] : 0u;
+    heads += i0 + k < n && (i0 + k == 0 || key[k + 1] != key[k]);
+  }
+  int total;
+  int a = blocks_before(V.heads, blockIdx.x, scanned) +
+          block_exclusive<kBlock / kWave>(heads, &total);
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = i0 + k;
+    if (i >= n) break;
+    if (i == 0 || key[k + 1] != key[k]) {
       R.seg_start[a] = i;
-      R.active_cell[a] = (int)skeys[i];
-      cell_map[skeys[i]] = a;
+      R.active_cell[a] = (int)key[k + 1];
+      V.cell_map[key[k + 1]] = a;
+      ++a;
     }
     if (i == n - 1) {
-      const int total = scan[i] + (head ? 1 : 0);
-      R.seg_start[total] = n;
-      sc->n_active = total;
+      R.seg_start[a] = n;
+      V.L.sc->n_active = a;
     }
   }
 }
 
+// Nodes of block b (kBlock nodes) that are a corner of an active cell.
 template <typename T>
-hipError_t launch_segments(const LevelView<T>& L, const RowView<T>& R, const unsigned* skeys,
-                           const int* scan, int* cell_map_w, int ncell, hipStream_t s) {
-  int g = blocks_for(ncell);
-  if (g > 4096) g = 4096;
-  k_fill_int<<<g, kBlock, 0, s>>>(cell_map_w, -1, ncell);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  int grid = blocks_for(R.rows > 0 ? R.rows : 1);
-  if (grid > 4096) grid = 4096;
-  k_segments<T><<<grid, kBlock, 0, s>>>(R, skeys, scan, cell_map_w, L.sc);
-  return hipGetLastError();
+__device__ __forceinline__ void count_nodes(const BuildLevel<T>& V, int b) {
+  const LevelView<T>& L = V.L;
+  if (b * kBlock >= L.N) return;
+  const int i = b * kBlock + threadIdx.x;
+  int f = 0;
+  if (i < L.N) {
+    const int x = i % L.nx, y = (i / L.nx) % L.ny, z = i / (L.nx * L.ny);
+    const int cnx = L.nx - 1, cny = L.ny - 1, cnz = L.nz - 1;
+    for (int a = 0; a < 8; ++a) {
+      const int cx = x - (a & 1), cy = y - ((a >> 1) & 1), cz = z - (a >> 2);
+      if (in_box(cx, cy, cz, cnx, cny, cnz) && V.cell_map[cx + cnx * (cy + cny * cz)] >= 0) f = 1;
+    }
+    if (V.touched) V.touched[i] = (unsigned char)f;
+  }
+  const int total = __syncthreads_count(f);
+  if (threadIdx.x == 0) V.nodes[b] = total;
 }
 
 // B^T B and B^T b cached per active cell (the per-voxel cache of Sec. 7.1).
@@ -224,10 +271,17 @@ hipError_t launch_segments(const LevelView<T>& L, const RowView<T>& R, const uns
 // the one after are already being loaded (cells of coarse levels hold
 // thousands of rows).
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_build_cells(RowView<T> R, T* K, const Scalars* sc) {
+__global__ __launch_bounds__(kBlock) void k_build_cells(BuildLevels<T> B, int cell_blocks) {
+  const BuildLevel<T>& V = B.level[blockIdx.y];
+  if ((int)blockIdx.x >= cell_blocks) {
+    count_nodes(V, blockIdx.x - cell_blocks);
+    return;
+  }
+  const RowView<T>& R = V.R;
+  T* const K = V.K;
   constexpr int P = kBlock + 1;  // padded rows: conflict-free column reads
   __shared__ double s_u[25 * P];  // 24 products alpha_a sn_i, then rho
-  const int n_active = sc->n_active;
+  const int n_active = V.L.sc->n_active;
   const int rows = R.rows;
   const int j = threadIdx.x;
   int ka = 0, kb = 0, ca = 0, ci = 0, kind = 2;
@@ -245,7 +299,7 @@ __global__ __launch_bounds__(kBlock) void k_build_cells(RowView<T> R, T* K, cons
     kb = 24;
     kind = 1;
   }
-  for (int a = blockIdx.x; a < n_active; a += gridDim.x) {
+  for (int a = blockIdx.x; a < n_active; a += cell_blocks) {
     const int s0 = R.seg_start[a], s1 = R.seg_start[a + 1];
     // row of this thread in the chunk being staged (f, sn, rho) and the row
     // index of the following chunk
@@ -315,35 +369,6 @@ __global__ __launch_bounds__(kBlock) void k_build_cells(RowView<T> R, T* K, cons
   }
 }
 
-template <typename T>
-hipError_t launch_build_cells(const LevelView<T>& L, const RowView<T>& R, T* K, int grid,
-                              hipStream_t s) {
-  if (grid <= 0) return hipSuccess;
-  k_build_cells<T><<<grid, kBlock, 0, s>>>(R, K, L.sc);
-  return hipGetLastError();
-}
-
-// flags[i] = 1 when node i is a corner of at least one active cell.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_node_flags(LevelView<T> L, int* flags) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= L.N) return;
-  const int x = i % L.nx, y = (i / L.nx) % L.ny, z = i / (L.nx * L.ny);
-  const int cnx = L.nx - 1, cny = L.ny - 1, cnz = L.nz - 1;
-  int f = 0;
-  for (int a = 0; a < 8; ++a) {
-    const int cx = x - (a & 1), cy = y - ((a >> 1) & 1), cz = z - (a >> 2);
-    if (in_box(cx, cy, cz, cnx, cny, cnz) && L.cell_map[cx + cnx * (cy + cny * cz)] >= 0) f = 1;
-  }
-  flags[i] = f;
-}
-
-template <typename T>
-hipError_t launch_node_flags(const LevelView<T>& L, int* flags, hipStream_t s) {
-  k_node_flags<T><<<blocks_for(L.N), kBlock, 0, s>>>(L, flags);
-  return hipGetLastError();
-}
-
 // Per node: the data part of row i of A as a 27-point block stencil,
 // A27[delta] = sum over adjacent active cells c (i = corner a of c, neighbour
 // = corner b, delta = b - a) of K_c[a][b]; stored at the node's compact slot
@@ -353,22 +378,33 @@ hipError_t launch_node_flags(const LevelView<T>& L, int* flags, hipStream_t s) {
 // Jacobi diagonal 2 w_r |N_i| + diag(A27[0]), and the data right-hand side
 // b_i gathered from the cells.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_assemble_nodes(LevelView<T> L, RowView<T> R,
-                                                           const int* flags, const int* scan,
-                                                           int* node_slot, T* A27r) {
+__global__ __launch_bounds__(kBlock) void k_assemble_nodes(BuildLevels<T> B, int scanned) {
+  const BuildLevel<T>& V = B.level[blockIdx.y];
+  const LevelView<T>& L = V.L;
+  const RowView<T>& R = V.R;
+  if ((int)blockIdx.x * kBlock >= L.N) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {  // read by the energy kernel
+    L.sc->rows = R.rows;
+    L.sc->n_dense = R.n_dense;
+  }
   const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= L.N) return;
+  const int before = blocks_before(V.nodes, blockIdx.x, scanned);
   const int x = i % L.nx, y = (i / L.nx) % L.ny, z = i / (L.nx * L.ny);
   const int nb = (x > 0) + (x < L.nx - 1) + (y > 0) + (y < L.ny - 1) + (z > 0) + (z < L.nz - 1);
   const int cnx = L.nx - 1, cny = L.ny - 1, cnz = L.nz - 1;
-  int cells[8];
+  int cells[8], has = 0;
 #pragma unroll
   for (int a = 0; a < 8; ++a) {
     const int cx = x - (a & 1), cy = y - ((a >> 1) & 1), cz = z - (a >> 2);
-    cells[a] = in_box(cx, cy, cz, cnx, cny, cnz) ? L.cell_map[cx + cnx * (cy + cny * cz)] : -1;
+    cells[a] = i < L.N && in_box(cx, cy, cz, cnx, cny, cnz)
+                   ? V.cell_map[cx + cnx * (cy + cny * cz)] : -1;
+    has |= cells[a] >= 0;
   }
-  const int slot = flags[i] ? scan[i] : -1;
-  node_slot[i] = slot;
+  int total;
+  const int rank = block_exclusive<kBlock / kWave>(has, &total);
+  if (i >= L.N) return;
+  const int slot = has ? before + rank : -1;
+  V.node_slot[i] = slot;
   T dg[3] = {T(0), T(0), T(0)};
   T b[3] = {T(0), T(0), T(0)};
   if (slot >= 0) {
@@ -382,7 +418,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble_nodes(LevelView<T> L, RowVi
 #pragma unroll
     for (int a = 0; a < 8; ++a) {
       if (cells[a] < 0) continue;
-      const T* __restrict__ row = L.K + ((size_t)cells[a] * 64 + a * 8) * 6;
+      const T* __restrict__ row = V.K + ((size_t)cells[a] * 64 + a * 8) * 6;
 #pragma unroll
       for (int bb = 0; bb < 8; ++bb) {
         const int dl = ((bb & 1) - (a & 1) + 1) + 3 * ((((bb >> 1) & 1) - ((a >> 1) & 1) + 1) +
@@ -398,7 +434,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble_nodes(LevelView<T> L, RowVi
     // entry q of part m (block (dx, dy) of dz = m - 1, zero padded) at chunk
     // 3 (q / CW) + m, position q % CW
     constexpr int CW = 16 / (int)sizeof(T);
-    T* __restrict__ row_out = A27r + (size_t)slot * kA27Row;
+    T* __restrict__ row_out = V.A27r + (size_t)slot * kA27Row;
 #pragma unroll
     for (int m = 0; m < 3; ++m)
 #pragma unroll
@@ -432,9 +468,14 @@ __global__ __launch_bounds__(kBlock) void k_assemble_nodes(LevelView<T> L, RowVi
   }
 }
 
+// The optimised set M: the isosurface points (corners of the cells holding
+// samples) and their one-ring.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_dilate(LevelView<T> L, const int* flags,
-                                                   unsigned char* act) {
+__global__ __launch_bounds__(kBlock) void k_dilate(BuildLevels<T> B) {
+  const BuildLevel<T>& V = B.level[blockIdx.y];
+  const LevelView<T>& L = V.L;
+  const unsigned char* flags = V.touched;
+  if (!V.act) return;
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= L.N) return;
   const int x = i % L.nx, y = (i / L.nx) % L.ny, z = i / (L.nx * L.ny);
@@ -446,13 +487,51 @@ __global__ __launch_bounds__(kBlock) void k_dilate(LevelView<T> L, const int* fl
     if (pos[ax] > 0) f |= flags[i - st[ax]];
     if (pos[ax] < lim[ax] - 1) f |= flags[i + st[ax]];
   }
-  act[i] = f ? 1 : 0;
+  V.act[i] = f ? 1 : 0;
 }
 
+int build_row_blocks(int rows) { return rows > 0 ? (rows + kRowTile - 1) / kRowTile : 1; }
+int build_node_blocks(int n) { return blocks_for(n); }
+
 template <typename T>
-hipError_t launch_dilate(const LevelView<T>& L, const int* flags, unsigned char* act,
-                         hipStream_t s) {
-  k_dilate<T><<<blocks_for(L.N), kBlock, 0, s>>>(L, flags, act);
+hipError_t launch_build(const RawConstraints& c, const BuildLevels<T>& B, const SortLevels& S,
+                        const double* o, double wd, double ws, bool structure, void* temp,
+                        size_t temp_bytes, hipStream_t s) {
+  const int rows = B.level[0].R.rows, nb = build_row_blocks(rows);
+  int cells = 0, cap = 0, nodes = 0, act = 0;
+  for (int l = 0; l < B.n; ++l) {
+    const BuildLevel<T>& V = B.level[l];
+    cells = V.ncell > cells ? V.ncell : cells;
+    cap = V.cap_cells > cap ? V.cap_cells : cap;
+    nodes = V.L.N > nodes ? V.L.N : nodes;
+    act |= V.act != nullptr;
+  }
+  // scans of counts too many to be added up by every block
+  auto scan = [&](int* counts, int n) {
+    return exclusive_scan(temp, temp_bytes, counts, counts, n, s);
+  };
+  hipError_t e = hipSuccess;
+  if (rows > 0 || structure) {
+    int gx = nb;  // enough workgroups to clear the cell maps
+    if (structure && gx < 256) gx = std::min(256, std::max(gx, (cells + 4095) / 4096));
+    k_rows<T><<<dim3(gx, B.n), kBlock, 0, s>>>(c, B, S, o[0], o[1], o[2], wd, ws, structure);
+  }
+  if (structure) {
+    if ((e = sort_levels(S, s)) != hipSuccess) return e;
+    k_heads<T><<<dim3(nb, B.n), kBlock, 0, s>>>(B);
+    if (nb > kDirectBlocks)
+      for (int l = 0; l < B.n; ++l)
+        if ((e = scan(B.level[l].heads, nb)) != hipSuccess) return e;
+    k_segments<T><<<dim3(nb, B.n), kBlock, 0, s>>>(B, nb > kDirectBlocks);
+  }
+  const int cb = std::min(cap, kCellBlocks), gn = blocks_for(nodes);
+  k_build_cells<T><<<dim3(cb + gn, B.n), kBlock, 0, s>>>(B, cb);
+  if (act) k_dilate<T><<<dim3(gn, B.n), kBlock, 0, s>>>(B);
+  const bool scanned = gn > kDirectBlocks;
+  if (scanned)
+    for (int l = 0; l < B.n; ++l)
+      if ((e = scan(B.level[l].nodes, blocks_for(B.level[l].L.N))) != hipSuccess) return e;
+  k_assemble_nodes<T><<<dim3(gn, B.n), kBlock, 0, s>>>(B, scanned);
   return hipGetLastError();
 }
 
@@ -518,26 +597,6 @@ template <typename T>
 hipError_t launch_grow_commit(const LevelView<T>& L, const T* tmp_d, const T* tmp_r,
                               unsigned char* fresh, unsigned char* known, hipStream_t s) {
   k_grow_commit<T><<<blocks_for(L.N), kBlock, 0, s>>>(L, tmp_d, tmp_r, fresh, known);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_assemble_nodes(const LevelView<T>& L, const RowView<T>& R, const int* flags,
-                                 const int* scan, int* node_slot, T* A27r, hipStream_t s) {
-  k_assemble_nodes<T><<<blocks_for(L.N), kBlock, 0, s>>>(L, R, flags, scan, node_slot, A27r);
-  return hipGetLastError();
-}
-
-// Rows / dense-row counts of the current frame (read by the energy kernel).
-__global__ void k_set_counts(Scalars* sc, int rows, int n_dense) {
-  if (threadIdx.x == 0) {
-    sc->rows = rows;
-    sc->n_dense = n_dense;
-  }
-}
-
-hipError_t launch_set_counts(Scalars* sc, int rows, int n_dense, hipStream_t s) {
-  k_set_counts<<<1, 64, 0, s>>>(sc, rows, n_dense);
   return hipGetLastError();
 }
 
@@ -794,19 +853,9 @@ hipError_t launch_convert_back(const T* in, float* out, int n, hipStream_t s) {
 
 // ---- explicit instantiations -----------------------------------------------
 #define VD_INSTANTIATE(T)                                                                        \
-  template hipError_t launch_rows<T>(const RawConstraints&, const LevelView<T>&,                \
-                                     const RowView<T>&, const double*, double, double,          \
-                                     unsigned*, int*, hipStream_t);                             \
-  template hipError_t launch_segments<T>(const LevelView<T>&, const RowView<T>&,                \
-                                         const unsigned*, const int*, int*, int, hipStream_t);  \
-  template hipError_t launch_build_cells<T>(const LevelView<T>&, const RowView<T>&, T*, int,    \
-                                            hipStream_t);                                       \
-  template hipError_t launch_assemble_nodes<T>(const LevelView<T>&, const RowView<T>&,          \
-                                               const int*, const int*, int*, T*,             \
-                                               hipStream_t);                                    \
-  template hipError_t launch_node_flags<T>(const LevelView<T>&, int*, hipStream_t);             \
-  template hipError_t launch_dilate<T>(const LevelView<T>&, const int*, unsigned char*,         \
-                                       hipStream_t);                                             \
+  template hipError_t launch_build<T>(const RawConstraints&, const BuildLevels<T>&,              \
+                                      const SortLevels&, const double*, double, double, bool,   \
+                                      void*, size_t, hipStream_t);                              \
   template hipError_t launch_grow_layer<T>(const LevelView<T>&, const unsigned char*,           \
                                            const unsigned char*, T*, T*, unsigned char*, int*,  \
                                            hipStream_t);                                         \

@@ -523,4 +523,29 @@ VD_HD int fit_or_keep<float>(const float (&M)[9], const float (&R_prev)[9],
   return code == kFitKeep ? kFitKeep : kFitFp64;
 }
 
+// Exclusive prefix of v over the block's threads in thread order; *total
+// (shared by all threads) receives the block's sum.
+template <int kWaves>
+__device__ __forceinline__ int block_exclusive(int v, int* total) {
+  __shared__ int wave_sum[kWaves];
+  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  int inc = v;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int t = __shfl_up(inc, off, kWave);
+    if (lane >= off) inc += t;
+  }
+  if (lane == kWave - 1) wave_sum[wv] = inc;
+  __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    if (w < wv) before += wave_sum[w];
+    all += wave_sum[w];
+  }
+  __syncthreads();  // wave_sum may be reused by the next call
+  *total = all;
+  return before + inc - v;
+}
+
 }  // namespace vd

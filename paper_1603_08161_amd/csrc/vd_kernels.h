@@ -134,29 +134,59 @@ struct RawConstraints {
 hipError_t launch_validate(const RawConstraints& c, int nx0, int ny0, int nz0, double h0,
                            const double* origin, int* flags, hipStream_t s);
 
-template <typename T>
-hipError_t launch_rows(const RawConstraints& c, const LevelView<T>& L, const RowView<T>& R,
-                       const double* origin, double w_dense, double w_sparse,
-                       unsigned* keys, int* vals, hipStream_t s);
+// Stable radix sorts of (key, value) pairs of several levels over the same
+// number of rows, one launch per step of all of them (sort.hip).
+constexpr int kRowTile = 1024;       // rows per workgroup of a step
+constexpr int kMaxDigitBits = 10;
+constexpr int kMaxBuckets = 1 << kMaxDigitBits;
+struct SortLevel {
+  const unsigned* kin;
+  const int* vin;         // null: the row indices
+  unsigned *ktmp, *kout;
+  int *vtmp, *vout;
+  int* hist;              // [blocks][buckets]
+  int* total;             // [buckets]
+  int digit_bits, passes;
+};
+struct SortLevels {
+  SortLevel level[VD_MAX_LEVELS];
+  int n, rows;
+  int passes;   // the most of any level
+  int counted;  // hist holds the counts of every level's first digit
+};
 
+// What the constraint build of one level reads and writes.
 template <typename T>
-hipError_t launch_segments(const LevelView<T>& L, const RowView<T>& R, const unsigned* skeys,
-                           const int* scan, int* cell_map_w, int ncell, hipStream_t s);
-
-hipError_t launch_heads(const unsigned* skeys, int n, int* heads, hipStream_t s);
-
+struct BuildLevel {
+  LevelView<T> L;
+  RowView<T> R;
+  int ncell, cap_cells;
+  int* cell_map;
+  T* K;
+  int* node_slot;
+  T* A27r;
+  unsigned char* act;    // null: no active set
+  unsigned* skeys;       // rows' cells in sorted order
+  int* heads;            // [row blocks] first rows of a cell per block of kRowTile rows
+  int* nodes;            // [node blocks] nodes with data per block of kBlock nodes
+  unsigned char* touched;  // [N] 1: node with data (active sets)
+};
 template <typename T>
-hipError_t launch_build_cells(const LevelView<T>& L, const RowView<T>& R, T* K, int grid,
-                              hipStream_t s);
+struct BuildLevels {
+  BuildLevel<T> level[VD_MAX_LEVELS];
+  int n;
+};
 
+// Rows, cell cache and node blocks of all levels from the staged constraints.
+// With `structure` false only the values are recomputed: the rows' cells, the
+// sort by cell and the cell segments are those of the previous build.  temp:
+// scan_temp_bytes(build_scan_size(...)) bytes.
 template <typename T>
-hipError_t launch_node_flags(const LevelView<T>& L, int* flags, hipStream_t s);
-
-// act[i] = flags[i] or a 6-neighbour's flag (the one-ring of the flagged
-// isosurface points).
-template <typename T>
-hipError_t launch_dilate(const LevelView<T>& L, const int* flags, unsigned char* act,
-                         hipStream_t s);
+hipError_t launch_build(const RawConstraints& c, const BuildLevels<T>& B, const SortLevels& S,
+                        const double* origin, double w_dense, double w_sparse, bool structure,
+                        void* temp, size_t temp_bytes, hipStream_t s);
+int build_row_blocks(int rows);
+int build_node_blocks(int n);
 
 // One layer of grid growth on a level: every node of act that is not
 // `known` and has a known 6-neighbour takes the mean of their displacements
@@ -171,11 +201,6 @@ hipError_t launch_grow_layer(const LevelView<T>& L, const unsigned char* act,
 template <typename T>
 hipError_t launch_grow_commit(const LevelView<T>& L, const T* tmp_d, const T* tmp_r,
                               unsigned char* fresh, unsigned char* known, hipStream_t s);
-
-template <typename T>
-hipError_t launch_assemble_nodes(const LevelView<T>& L, const RowView<T>& R, const int* flags,
-                                 const int* scan, int* node_slot, T* A27r,
-                                 hipStream_t s);
 
 // ---- solve (solve.hip) ------------------------------------------------------
 enum StencilMode { kModeRhs = 1, kModeApply = 2, kModeGrad = 3 };
@@ -284,9 +309,6 @@ hipError_t launch_target_step(Scalars* sc, hipStream_t s);
 // flags |= 1 where any of the n floats is not finite.
 hipError_t launch_check_finite(const float* v, int64_t n, int* flags, hipStream_t s);
 
-// sc->rows, sc->n_dense of the current frame.
-hipError_t launch_set_counts(Scalars* sc, int rows, int n_dense, hipStream_t s);
-
 template <typename T>
 hipError_t launch_state_io(const LevelView<T>& L, const double* origin, float* pos, float* rot,
                            const float* pos_in, const float* rot_in, int dir, int* flags,
@@ -310,6 +332,8 @@ hipError_t launch_fit_batch(const float* M, const float* R_prev, float* R, int* 
 // keys and exclusive integer prefix sums (sort.hip); temp holds at least
 // sort_temp_bytes / scan_temp_bytes bytes.
 size_t sort_temp_bytes(int n);
+SortLevel sort_level(void* temp, int cap, int end_bit);  // laid out for up to cap rows
+hipError_t sort_levels(const SortLevels& S, hipStream_t s);
 hipError_t sort_pairs(void* temp, size_t bytes, const unsigned* kin, unsigned* kout,
                       const int* vin, int* vout, int n, int end_bit, hipStream_t s);
 size_t scan_temp_bytes(int n);

@@ -98,6 +98,27 @@ def test_cfg1_levels_match_oracle(cfg1):
                                    energy_terms(grid, t, R, cons), rtol=1e-6)
 
 
+@pytest.mark.parametrize("dims,n_dense,copies", [
+    ((104, 102, 102), 900, 1),    # more than 4096 blocks of 256 nodes
+    ((12, 11, 10), 1075, 4000),   # more than 4096 blocks of 1024 rows
+])
+def test_constraint_build_of_many_blocks(dims, n_dense, copies):
+    """The build's offsets over blocks of nodes and of rows when they are too
+    many to be added up directly.  n copies of a sample weigh as much as one
+    with n times its weight."""
+    scene = make_tiny(seed=9, dims=dims, n_dense=n_dense, n_sparse=4)
+    grid = grids_of(scene)[0]
+    lat = make_lattice(scene)
+    rep = [np.tile(a, (copies,) + (1,) * (a.ndim - 1))
+           for a in (scene.canon, scene.target, scene.normal, scene.weight)]
+    lat.set_constraints(*rep, scene.sparse_canon, scene.sparse_target)
+    scene.weight = scene.weight * np.float32(copies)
+    system = LevelSystem(grid, oracle_cons(scene))
+    p = np.random.default_rng(8).normal(size=(grid.n, 3)).astype(np.float32)
+    ref = (system.A @ p.astype(np.float64).reshape(-1)).reshape(-1, 3)
+    assert rel_err(lat.debug_apply(0, p), ref) < 1e-5
+
+
 @pytest.mark.parametrize("precision,tol", [("fp32", 1e-5), ("fp64", 3e-7)])
 def test_rotation_step_matches_oracle(precision, tol):
     scene = SCENES["ragged"]()
