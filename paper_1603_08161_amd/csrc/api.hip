@@ -169,6 +169,7 @@ struct LevelData {
   int ntiles = 0;     // workgroups of the current tile kind
   int max_tiles = 0;  // most workgroups over all tile kinds (partials capacity)
   int tile = 0;       // tile kind of the stencil / CG kernels
+  int large = -1;     // tile kind of one-launch CG solves that no other covers
 
   int rblocks() const { return blocks_of(cap_rows); }
 
@@ -176,6 +177,8 @@ struct LevelData {
     LevelView<T> v{};
     v.nx = nx; v.ny = ny; v.nz = nz; v.N = N; v.tile = tile; v.ntiles = ntiles;
     v.rblocks = rblocks();
+    v.loop_tile = large >= 0 ? large : tile;
+    v.loop_tiles = large >= 0 ? tile_blocks(large, nx, ny, nz) : ntiles;
     v.h = (T)h; v.wr = (T)wr;
     v.d = d; v.r = r; v.r2 = r2; v.pa = pa; v.pb = pb; v.ap = ap; v.ap2 = ap2;
     v.dinv = dinv; v.bnode = bnode; v.base = base; v.rot = rot;
@@ -195,9 +198,11 @@ struct LevelData {
   }
 };
 
-// Single-lattice dispatches of the four workgroup kinds.
+// Single-lattice dispatches of the workgroup kinds.
 template <typename T>
 Dispatch<T> tiles_of(const LevelView<T>& V) { return single(V, V.ntiles); }
+template <typename T>
+Dispatch<T> loop_tiles_of(const LevelView<T>& V) { return single(V, V.loop_tiles); }
 template <typename T>
 Dispatch<T> nodes_of(const LevelView<T>& V) { return single(V, node_blocks(V.N)); }
 template <typename T>
@@ -299,6 +304,8 @@ class Solver final : public ISolver {
       if (want < 0 || want > kTileKinds) return VD_EINVAL;
       v.tile = want > 0 ? want - 1 : default_tile(v.nx, v.ny, v.nz);
       v.ntiles = tile_blocks(v.tile, v.nx, v.ny, v.nz);
+      if (sizeof(T) == 4)
+        v.large = large_loop_tile(v.nx, v.ny, v.nz, (desc_.flags & VD_FLAG_ACTIVE_SET) != 0);
       for (int k = 0; k < kTileKinds; ++k)
         v.max_tiles = std::max(v.max_tiles, tile_blocks(k, v.nx, v.ny, v.nz));
       for (int k = 0; k < 3; ++k) dims[k] = (dims[k] + 1) / 2;
@@ -334,7 +341,9 @@ class Solver final : public ISolver {
       VD_CHECK(pool_.alloc(&v.gang, kGangHead + 12 * (size_t)v.max_tiles));
       VD_CHECK(ensure_partials(v, 0));
     }
-    for (int k = 0; k < kTileKinds; ++k)
+    const int kinds = sizeof(T) == 8 ? kTileKinds
+                      : desc_.flags & VD_FLAG_ACTIVE_SET ? kLoopKinds - 1 : kLoopKinds;
+    for (int k = 0; k < kinds; ++k)
       VD_TRY(cg_loop_capacity<T>(k, (desc_.flags & VD_FLAG_ACTIVE_SET) != 0, &loop_cap_[k]));
     if ((desc_.flags & VD_FLAG_PROFILE) && (desc_.flags & VD_FLAG_GRAPH))
       VD_CHECK(pool_.alloc(&stamps_, 2 * kMaxStamped));  // written by captured CG launches
@@ -990,7 +999,8 @@ class Solver final : public ISolver {
   int level_nodes(int l) const { return lv_[l].N; }
   int level_tile(int l) const { return lv_[l].tile; }
   int level_capacity(int l) const { return loop_cap_[lv_[l].tile]; }
-  bool level_loop(int l) const { return cg_loop(lv_[l]); }
+  // (a batch launches all its lattices with one tile kind: none of the large)
+  bool level_loop(int l) const { return lv_[l].large < 0 && cg_loop(lv_[l]); }
   void force_tile(int l, int kind) {
     if (lv_[l].tile == kind) return;
     lv_[l].tile = kind;
@@ -1151,7 +1161,7 @@ class Solver final : public ISolver {
           VD_TRY(hipEventRecord(e0, stream_));
           VD_TRY(launch_stencil<T>(kModeRhs, tiles_of(V), nullptr, nullptr, stream_));
           if (cg_loop(v)) {
-            VD_TRY(launch_cg_loop<T>(iters, tiles_of(V), stream_));
+            VD_TRY(launch_cg_loop<T>(iters, loop_tiles_of(V), stream_));
           } else {
             for (int m = 0; m < iters; ++m) VD_TRY(launch_cg<T>(m, tiles_of(V), stream_));
             if (iters > 0) VD_TRY(launch_cg_final<T>(iters - 1, nodes_of(V), stream_));
@@ -1226,7 +1236,7 @@ class Solver final : public ISolver {
             stamped_launches_ = pcg - 1;
           }
           VD_CHECK(timed(on, VD_PROF_CG_LOOP, s,
-                         [&] { return launch_cg_loop<T>(pcg, tiles_of(V), s, stamp, loop_ticks_); }));
+                         [&] { return launch_cg_loop<T>(pcg, loop_tiles_of(V), s, stamp, loop_ticks_); }));
         } else if (graph_prof && l == L_ - 1 && pcg > 1) {
           // captured frame: the device clock at the start of CG iteration 1
           // and of the final step (first workgroup of each), written on
@@ -1261,7 +1271,9 @@ class Solver final : public ISolver {
   // on the GPU together, unless VD_FLAG_ITERATIVE asks for one launch per
   // iteration.
   bool cg_loop(const LevelData<T>& v) const {
-    return !(desc_.flags & VD_FLAG_ITERATIVE) && v.ntiles <= loop_cap_[v.tile];
+    const int kind = v.large >= 0 ? v.large : v.tile;
+    return !(desc_.flags & VD_FLAG_ITERATIVE) &&
+           tile_blocks(kind, v.nx, v.ny, v.nz) <= loop_cap_[kind];
   }
 
   template <typename F>
@@ -1367,7 +1379,7 @@ class Solver final : public ISolver {
     auto g = [&](const Dispatch<T>& D) { return guarded(D, stop); };
     VD_TRY(launch_stencil<T>(kModeRhs, g(tiles_of(V)), nullptr, nullptr, s));
     if (cg_loop(finest()) && pcg > 0) {
-      VD_TRY(launch_cg_loop<T>(pcg, g(tiles_of(V)), s));
+      VD_TRY(launch_cg_loop<T>(pcg, g(loop_tiles_of(V)), s));
     } else {
       for (int m = 0; m < pcg; ++m) VD_TRY(launch_cg<T>(m, g(tiles_of(V)), s));
       if (pcg > 0) VD_TRY(launch_cg_final<T>(pcg - 1, g(nodes_of(V)), s));
@@ -1633,7 +1645,7 @@ class Solver final : public ISolver {
   bool energy_fresh_ = false;
   EventTimer timer_;  // timing of the last profiled frame
   int loop_ticks_ = kAssembleTicks;
-  int loop_cap_[kTileKinds] = {};  // most tiles of a one-launch CG solve, by tile kind
+  int loop_cap_[kLoopKinds] = {};  // most tiles of a one-launch CG solve, by tile kind
   // test scratch
   float* dbg_f_ = nullptr;
   T *dbg_t1_ = nullptr, *dbg_t2_ = nullptr, *dbg_rot_ = nullptr;

@@ -119,6 +119,9 @@ int tile_blocks(int kind, int nx, int ny, int nz) {
     case 5: return nb(TileY::TX, TileY::TY, TileY::TZ);
     case 6: return nb(TileH::TX, TileH::TY, TileH::TZ);
     case 7: return nb(TileC::TX, TileC::TY, TileC::TZ);
+    case 8: return nb(TileL4::TX, TileL4::TY, TileL4::TZ);
+    case 9: return nb(TileL6::TX, TileL6::TY, TileL6::TZ);
+    case 10: return nb(TileL7::TX, TileL7::TY, TileL7::TZ);
     default: return nb(TileS::TX, TileS::TY, TileS::TZ);
   }
 }
@@ -141,6 +144,22 @@ int default_tile(int nx, int ny, int nz) {
     if (best < 0 || n < tile_blocks(best, nx, ny, nz)) best = k;
   }
   return best >= 0 ? best : nx >= 24 ? 2 : 1;
+}
+
+// The tile of a one-launch CG solve on a level that is too large for every
+// kind of default_tile (float32; float64 state does not fit): the smallest
+// that covers it with kGangMaxTiles tiles, or -1.  One launch against one per
+// iteration, frames of 3 levels with 8 x 20 iterations: 72^3 (16x16x8) 4.6
+// and 5.6 ms, 84^3 (16x16x12) 5.9 and 7.6, 96^3 (16x16x14) 8.4 and 8.9; the
+// optimised set at 72^3 4.4 and 5.7.  With the optimised set at 96^3 the
+// largest tile spills 70 registers where the launches per iteration skip the
+// tiles without unknowns: 7.4 and 6.8, so it is not used there.
+int large_loop_tile(int nx, int ny, int nz, bool masked) {
+  for (int k = 0; k < kTileKinds; ++k)
+    if (tile_blocks(k, nx, ny, nz) <= kGangMaxTiles) return -1;
+  for (int k = kTileKinds; k < kLoopKinds - (masked ? 1 : 0); ++k)
+    if (tile_blocks(k, nx, ny, nz) <= kGangMaxTiles) return k;
+  return -1;
 }
 int node_blocks(int N) { return blocks_for(N); }
 int energy_blocks(int rblocks, int N) { return rblocks + blocks_for(N); }
@@ -359,14 +378,18 @@ __device__ __forceinline__ unsigned long long* gang_slots(const double* gang) {
 // so no sum looks empty.
 constexpr unsigned long long kEmptySlot = ~0ull;
 
-// The gradient pass before a solve empties the tile's slots (a tile without
-// unknowns: its sums, zero, for every iterate) and resets the head.
-__device__ __forceinline__ void gang_prepare(double* gang, int tiles, int local, bool empty) {
-  if (threadIdx.x < 12) {
+// The gradient pass before a solve empties the slots (of a tile without
+// unknowns: its sums, zero, for every iterate) and resets the head.  A solve
+// on larger tiles has fewer: their first workgroups' slots are emptied, and
+// the solve itself fills those of tiles without unknowns.
+template <typename T>
+__device__ __forceinline__ void gang_prepare(const LevelView<T>& L, int local, bool empty) {
+  if (threadIdx.x < 12 && local < L.loop_tiles) {
     const int set = threadIdx.x / 4, k = threadIdx.x % 4;
-    gang_slots(gang)[((size_t)set * 4 + k) * tiles + local] = empty ? 0ull : kEmptySlot;
+    gang_slots(L.gang)[((size_t)set * 4 + k) * L.loop_tiles + local] =
+        empty && L.loop_tile == L.tile ? 0ull : kEmptySlot;
   }
-  if (local == 0 && threadIdx.x < kGangHead) ((unsigned long long*)gang)[threadIdx.x] = 0ull;
+  if (local == 0 && threadIdx.x < kGangHead) ((unsigned long long*)L.gang)[threadIdx.x] = 0ull;
 }
 
 // kModeRhs : p = d; g = A d - b + w_r sum_j (2I - R_i - R_j) e_ij is the
@@ -400,11 +423,11 @@ __global__ __launch_bounds__(TL::NT) void k_stencil(Dispatch<T> D, const T* __re
         any |= act[gx + (size_t)L.nx * (gy + (size_t)L.ny * gz)];
     }
     if (!__syncthreads_or(any)) {
-      gang_prepare(L.gang, L.ntiles, w.local, w.local != 0);
+      gang_prepare(L, w.local, w.local != 0);
       return;
     }
   }
-  if (MODE == kModeRhs) gang_prepare(L.gang, L.ntiles, w.local, false);
+  if (MODE == kModeRhs) gang_prepare(L, w.local, false);
   // own nodes' data-block slots (loaded with the tile)
   int own_slot[TL::NPT];
 #pragma unroll
@@ -843,7 +866,13 @@ __global__ __launch_bounds__(TL::NT) void k_cg(Dispatch<T> D, int m, unsigned lo
 // What bounds an iteration is the instructions of the 16 waves of a compute
 // unit and the exchange's latency, so one wave alone forms the scalars, the
 // four sums share their wave reductions (wave_sum4), and the stencil has no
-// branches in waves away from the lattice's border.  The arithmetic and the
+// branches in waves away from the lattice's border.  The tiles of 2048 to
+// 3584 nodes hold all of a level of up to 96^3 in the registers of the chip;
+// there the rounds over the busiest tile's data nodes (940 at 96^3, 168 a
+// round, 2.6 us each) are half of an iteration's 35 us, and the rows of all
+// but the 16x16x8 tile are read again in every iteration.  A p packed by tile
+// face instead of in node order took 5 % longer (more index arithmetic in the
+// exchange), tiles dealt to the dies in turn 3 to 10 % longer.  The arithmetic and the
 // order of every sum are those of k_cg, so the results are the same bits.
 
 constexpr unsigned kSpinLimit = 1u << 18;         // polls before a wait gives up
@@ -1030,17 +1059,42 @@ struct Loop {
   static constexpr int ROUND = PW * kNodesPerWave;          // data nodes per round
   // rounds of items whose rows stay in registers (54 values per lane each)
   static constexpr int KEEP = sizeof(T) == 8 ? (NV > 1 || SPT > 2 ? 0 : 1)
-                                             : (NV > 1 ? 1 : 2);
-  // data nodes of the tile by owning wave, and the three parts of their sums
+                                             : (NV > 4 ? 0 : NV > 1 ? 1 : 2);
+  // the large tiles add a node's three parts up across lanes, as three arrays
+  // of parts would not fit LDS beside p
+  static constexpr bool LARGE = TL::TX * TL::TY * TL::TZ > 1024;
+  static constexpr int PARTS = LARGE ? 1 : kPartsPerNode;
+  // data nodes of the tile by owning wave, and the parts of their sums
   struct Share {
     int slot[ENT], node[ENT], cnt[OW];
-    T d[3][3][ENT];  // [part][component][entry]
+    T d[PARTS][3][ENT];  // [part][component][entry]
   };
+  // the calling lane's part of entry e (-1: none; whole waves call)
+  __device__ __forceinline__ static void leave(Share& ls, int part, int e, const T (&o)[3]) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      if (LARGE) {
+        const T o1 = __shfl_down(o[a], 1, kWave), o2 = __shfl_down(o[a], 2, kWave);
+        if (part == 0 && e >= 0) ls.d[0][a][e] = (o[a] + o1) + o2;
+      } else if (e >= 0) {
+        ls.d[part][a][e] = o[a];
+      }
+    }
+  }
+  __device__ __forceinline__ static T sum(const Share& ls, int a, int e) {
+    return LARGE ? ls.d[0][a][e]
+                 : (ls.d[0][a][e] + ls.d[PARTS > 1][a][e]) + ls.d[PARTS > 2 ? 2 : 0][a][e];
+  }
   __device__ __forceinline__ static int owner(int j) {  // the owning thread of own node j
     return (int)threadIdx.x + (j / TL::NPT) * PT;
   }
   __device__ __forceinline__ static bool owns(int j) {
     return TL::OWNERS % PT == 0 || owner(j) < TL::OWNERS;
+  }
+  // layers of own node j above own node 0
+  __device__ __forceinline__ static constexpr int layer(int j) {
+    static_assert(VT == 1 || PT % (TL::TX * TL::TY) == 0);
+    return (j / TL::NPT) * (PT / (TL::TX * TL::TY)) * TL::NPT + j % TL::NPT;
   }
   __device__ __forceinline__ static int own(int j) {  // LDS index of own node j
     const int t = owns(j) ? owner(j) : 0;
@@ -1095,7 +1149,7 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
   __shared__ Step<T> steps[2];
   const Where<T> w = locate_gang(D);
   const LevelView<T>& L = w.L;
-  const int n_tiles = L.ntiles;
+  const int n_tiles = L.loop_tiles;
   const size_t N = L.N;
   // (as values: a choice between two members of L would keep L in memory)
   T* const v_r = L.r;
@@ -1112,10 +1166,14 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
   const int part_id = lane % kPartsPerNode, item = wv * kNodesPerWave + lane / kPartsPerNode;
   const bool has_item = lane / kPartsPerNode < kNodesPerWave;
   T r[NV][3], q[NV][3], d[NV][3], ap[NV][3];  // own nodes
-  int node[NV];       // global index, -1: not an unknown
-  int rank[NV];       // entry of the node's data blocks in the wave's list
-  unsigned nbr[NV];   // bits 0..5: the neighbours it couples to (-x +x -y +y -z +z);
-                      // bit 6: on the tile's surface, neighbours read its A p
+  // bits 0..5: the neighbours it couples to (-x +x -y +y -z +z); bit 6: on the
+  // tile's surface, neighbours read its A p; bit 7: an unknown; from bit 8:
+  // 1 + the entry of its data blocks in the wave's list, 0 without
+  unsigned nbr[NV];
+  unsigned node0 = 0;  // global index of own node 0 (of the other own nodes: own_node)
+  const unsigned plane = (unsigned)L.nx * (unsigned)L.ny;
+  auto own_node = [&](int kk) { return node0 + plane * (unsigned)LP::layer(kk); };
+  auto unknown = [&](int kk) { return (nbr[kk] & 128u) != 0; };
   T hr[SPT][3], hq[SPT][3];  // halo nodes
   int hnode[SPT], hc[SPT];   // global index (-1: none), LDS index
   T keep[LP::KEEP > 0 ? LP::KEEP : 1][54];  // rows of the lane's first items,
@@ -1152,30 +1210,35 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
         const int gx = t.x0 + lx, gy = t.y0 + ly, gz = t.z0 + lz;
         const bool in = LP::owns(kk) && in_box(gx, gy, gz, L.nx, L.ny, L.nz);
         const size_t i = in ? gx + (size_t)L.nx * (gy + (size_t)L.ny * gz) : 0;
-        node[kk] = in && (!act || act[i]) ? (int)i : -1;
+        const bool is = in && (!act || act[i]);
+        if (kk == 0) node0 = gx + L.nx * (gy + L.ny * gz);
         // (solo: every A p is read back from memory)
         nbr[kk] = (gx > 0) | (gx < L.nx - 1) << 1 | (gy > 0) << 2 | (gy < L.ny - 1) << 3 |
                   (gz > 0) << 4 | (gz < L.nz - 1) << 5 |
-                  (node[kk] >= 0 && (solo || lx == 1 || lx == TL::TX || ly == 1 || ly == TL::TY ||
-                                     lz == 1 || lz == TL::TZ)) << 6;
-        slot[kk] = node[kk] >= 0 ? glob<const int>(L.node_slot)[i] : -1;
-        if (MASK && LP::owns(kk)) sm[c] = node[kk] >= 0;
+                  (is && (solo || lx == 1 || lx == TL::TX || ly == 1 || ly == TL::TY ||
+                          lz == 1 || lz == TL::TZ)) << 6 | is << 7;
+        slot[kk] = is ? glob<const int>(L.node_slot)[i] : -1;
+        if (MASK && LP::owns(kk)) sm[c] = is;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-          r[kk][a] = node[kk] >= 0 ? rin[a * N + i] : T(0);
-          q[kk][a] = node[kk] >= 0 ? dinv[a * N + i] : T(0);
-          d[kk][a] = node[kk] >= 0 ? dvec[a * N + i] : T(0);
-          const bool past = solo && m > 0 && node[kk] >= 0;  // else A p = p = 0
+          r[kk][a] = is ? rin[a * N + i] : T(0);
+          q[kk][a] = is ? dinv[a * N + i] : T(0);
+          d[kk][a] = is ? dvec[a * N + i] : T(0);
+          const bool past = solo && m > 0 && is;  // else A p = p = 0
           ap[kk][a] = past ? apin[a * N + i] : T(0);
           if (LP::owns(kk)) sp[a][c] = past ? pin[a * N + i] : T(0);
         }
       }
       if (MASK && act && !solo) {
-        // a tile without unknowns: its slots hold zeros already
+        // a tile without unknowns: its slots hold zeros already, or do now
         int any = 0;
 #pragma unroll
-        for (int kk = 0; kk < NV; ++kk) any |= node[kk] >= 0;
-        if (!__syncthreads_or(any) && tile != 0) return;
+        for (int kk = 0; kk < NV; ++kk) any |= unknown(kk);
+        if (!__syncthreads_or(any) && tile != 0) {
+          if (LP::LARGE && threadIdx.x < 12)
+            store_agent(slots + (size_t)threadIdx.x * n_tiles + tile, 0ull);
+          return;
+        }
       }
 #pragma unroll
       for (int h = 0; h < SPT; ++h) {
@@ -1205,11 +1268,11 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
         for (int z = 0; z < TL::NPT; ++z) {
           const int kk = vt * TL::NPT + z;
           const unsigned long long has = __ballot(slot[kk] >= 0);
-          rank[kk] = -1;
           if (slot[kk] >= 0) {
-            rank[kk] = ow * LP::SEG + base + __popcll(has & ((1ull << lane) - 1ull));
-            ls.slot[rank[kk]] = slot[kk];
-            ls.node[rank[kk]] = LP::own(kk);
+            const int e = ow * LP::SEG + base + __popcll(has & ((1ull << lane) - 1ull));
+            nbr[kk] |= (unsigned)(e + 1) << 8;
+            ls.slot[e] = slot[kk];
+            ls.node[e] = LP::own(kk);
           }
           base += __popcll(has);
         }
@@ -1305,14 +1368,14 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
     if (last || solo) {
 #pragma unroll
       for (int kk = 0; kk < NV; ++kk) {
-        if (node[kk] < 0) continue;
+        if (!unknown(kk)) continue;
         const int c = LP::own(kk);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-          dvec[a * N + node[kk]] = d[kk][a];
+          dvec[a * N + own_node(kk)] = d[kk][a];
           if (last) continue;
-          glob<T>(odd ? v_pb : v_pa)[a * N + node[kk]] = sp[a][c];
-          if (m > 0) glob<T>(odd ? v_r2 : v_r)[a * N + node[kk]] = r[kk][a];
+          glob<T>(odd ? v_pb : v_pa)[a * N + own_node(kk)] = sp[a][c];
+          if (m > 0) glob<T>(odd ? v_r2 : v_r)[a * N + own_node(kk)] = r[kk][a];
         }
       }
       if (last) {
@@ -1339,11 +1402,9 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
     // the rows kept in registers
 #pragma unroll
     for (int x = 0; x < LP::KEEP; ++x) {
-      if (ke[x] < 0) continue;
-      T o[3];
-      part_product<T, TL::HX>(sp, kcz[x], [&](int y) { return keep[x][y]; }, o);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) ls.d[part_id][a][ke[x]] = o[a];
+      T o[3] = {T(0), T(0), T(0)};
+      if (ke[x] >= 0) part_product<T, TL::HX>(sp, kcz[x], [&](int y) { return keep[x][y]; }, o);
+      LP::leave(ls, part_id, ke[x], o);
     }
     for (int v0 = LP::KEEP * LP::ROUND; v0 < n_data; v0 += LP::ROUND) {
       int e = ke[LP::KEEP], cz = kcz[LP::KEEP], at = kslot;
@@ -1352,15 +1413,15 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
         cz = e >= 0 ? ls.node[e] + TL::HX * TL::HY * (part_id - 1) : 0;
         at = e >= 0 ? ls.slot[e] : 0;
       }
-      if (e < 0) continue;
-      const gptr<const T> __restrict__ A = glob<const T>(static_cast<const T*>(
-          __builtin_assume_aligned(L.A27r + (size_t)at * kA27Row + part_id * CW, 16)));
-      T o[3];
-      part_product<T, TL::HX>(sp, cz,
-                              [&](int y) { return A[kPartsPerNode * CW * (y / CW) + y % CW]; },
-                              o);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) ls.d[part_id][a][e] = o[a];
+      T o[3] = {T(0), T(0), T(0)};
+      if (e >= 0) {
+        const gptr<const T> __restrict__ A = glob<const T>(static_cast<const T*>(
+            __builtin_assume_aligned(L.A27r + (size_t)at * kA27Row + part_id * CW, 16)));
+        part_product<T, TL::HX>(sp, cz,
+                                [&](int y) { return A[kPartsPerNode * CW * (y / CW) + y % CW]; },
+                                o);
+      }
+      LP::leave(ls, part_id, e, o);
     }
     __syncthreads();
     T* const ap_out = odd ? v_ap2 : v_ap;
@@ -1396,10 +1457,9 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
             }
         }
         T dd[3] = {T(0), T(0), T(0)};
-        if (rank[kk] >= 0) {
+        if (nbr[kk] >> 8) {
 #pragma unroll
-          for (int a = 0; a < 3; ++a)
-            dd[a] = (ls.d[0][a][rank[kk]] + ls.d[1][a][rank[kk]]) + ls.d[2][a][rank[kk]];
+          for (int a = 0; a < 3; ++a) dd[a] = LP::sum(ls, a, (int)(nbr[kk] >> 8) - 1);
         }
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -1409,7 +1469,7 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
             o = w2 * l[a];  // rounded before the data part, as in k_cg
             o = o + dd[a];
           }
-          ap[kk][a] = node[kk] >= 0 ? o : T(0);
+          ap[kk][a] = unknown(kk) ? o : T(0);
           const double qd = (double)q[kk][a], rd = (double)r[kk][a], pd = (double)p0[a];
           const double ad = (double)ap[kk][a];
           part[0] += rd * qd * rd;
@@ -1420,7 +1480,7 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
         if (nbr[kk] & 64u) {
 #pragma unroll
           for (int a = 0; a < 3; ++a)
-            store_agent(ap_out + a * N + (unsigned)node[kk], ap[kk][a]);
+            store_agent(ap_out + a * N + own_node(kk), ap[kk][a]);
         }
       }
       const double x = wave_sum4(part);
@@ -1501,6 +1561,14 @@ hipError_t launch_cg_final(int last, const Dispatch<T>& D, hipStream_t s,
 // registers each the same state spilled.
 template <typename T, bool MASK, typename F>
 hipError_t with_loop_kernel(int kind, F&& f) {
+  if constexpr (sizeof(T) == 4) {
+    switch (kind) {
+      case 8: return f(k_cg_loop<T, Loop<T, TileL4, 512>, MASK>, 512);
+      case 9: return f(k_cg_loop<T, Loop<T, TileL6, 512>, MASK>, 512);
+      case 10:
+        if constexpr (!MASK) return f(k_cg_loop<T, Loop<T, TileL7, 512>, MASK>, 512);
+    }
+  }
   switch (kind) {
     case 1: return f(k_cg_loop<T, Loop<T, TileM, 512>, MASK>, 512);
     case 2: return f(k_cg_loop<T, Loop<T, TileW, 256>, MASK>, 256);
@@ -1520,8 +1588,8 @@ hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s,
     kernel<<<D.blocks, threads, 0, s>>>(D, iters, stamp, ticks);
     return hipGetLastError();
   };
-  return D.masked ? with_loop_kernel<T, true>(D.one.tile, go)
-                  : with_loop_kernel<T, false>(D.one.tile, go);
+  return D.masked ? with_loop_kernel<T, true>(D.one.loop_tile, go)
+                  : with_loop_kernel<T, false>(D.one.loop_tile, go);
 }
 
 template <typename T>

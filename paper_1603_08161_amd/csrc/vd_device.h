@@ -54,6 +54,12 @@ using TileY = Tile<16, 4, 16, 1024>;
 using TileH = Tile<16, 4, 8, 512>;
 using TileC = Tile<8, 8, 4, 512>;
 constexpr int kTileKinds = 8;
+// Tiles of one-launch CG solves only (levels that no kind above covers with
+// kGangMaxTiles tiles): 4, 6 and 7 nodes per thread.
+using TileL4 = Tile<16, 16, 8, 512>;
+using TileL6 = Tile<16, 16, 12, 512>;
+using TileL7 = Tile<16, 16, 14, 512>;
+constexpr int kLoopKinds = 11;
 
 // Maps the hardware workgroup id to a logical tile id so that each XCD gets a
 // contiguous range of tiles (neighbouring tiles then share that XCD's L2).

@@ -76,7 +76,8 @@ struct LevelView {
   double* scg0;  // CG block partials [4][ntiles], even / odd iterates
   double* scg1;
   double* gang;  // one-launch CG solve: kGangHead words (state, next ticket,
-                 // tickets done), then the exchange slots [3][4][ntiles]
+                 // tickets done), then the exchange slots [3][4][loop_tiles]
+  int loop_tile, loop_tiles;  // tile kind and tiles of a one-launch CG solve
   double* pe;    // energy block partials [3][rblocks + node blocks]
   // constraint cache
   const int* cell_map;  // (nx-1)(ny-1)(nz-1) -> active cell index or -1
@@ -210,6 +211,7 @@ enum StencilMode { kModeRhs = 1, kModeApply = 2, kModeGrad = 3 };
 // workgroups of the node-parallel and energy kernels.
 int tile_blocks(int kind, int nx, int ny, int nz);
 int default_tile(int nx, int ny, int nz);
+int large_loop_tile(int nx, int ny, int nz, bool masked);
 int node_blocks(int N);
 int energy_blocks(int rblocks, int N);
 
@@ -236,9 +238,11 @@ hipError_t launch_cg_final(int last, const Dispatch<T>& D, hipStream_t s,
                            unsigned long long* stamp = nullptr);
 
 // All `iters` CG iterations and the last step of the position solve of every
-// lattice of D in one launch (tile workgroups; each lattice at most
+// lattice of D in one launch (loop_tiles workgroups; each lattice at most
 // cg_loop_capacity tiles).  Follows a gradient pass, which resets its
-// exchange slots.  Same bits as launch_cg + launch_cg_final.  stamp (may be
+// exchange slots.  Same bits as launch_cg + launch_cg_final where loop_tile is
+// the level's tile kind; the larger tiles add the same terms up in another
+// order.  stamp (may be
 // NULL): the device clock at the start of iteration 1 and of the last step.
 // ticks: how long a workgroup waits for the others before the solve is
 // abandoned to the ticket path (100 MHz clock; negative: at once, for tests).
@@ -247,7 +251,7 @@ template <typename T>
 hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s,
                           unsigned long long* stamp = nullptr, int ticks = kAssembleTicks);
 
-// Tiles of a kind that fit on the GPU together in launch_cg_loop.
+// Tiles of a kind (< kLoopKinds) that fit on the GPU together in launch_cg_loop.
 template <typename T>
 hipError_t cg_loop_capacity(int kind, bool masked, int* tiles);
 

@@ -368,3 +368,27 @@ def test_one_launch_solves_equal_per_iteration_launches(tile, precision, active)
         for mode in ("gang", "tickets"):
             np.testing.assert_array_equal(out[mode][0], out["iterative"][0])
             np.testing.assert_array_equal(out[mode][1], out["iterative"][1])
+
+
+@pytest.mark.parametrize("active", [False, True])
+@pytest.mark.parametrize("dims", [(65, 64, 65), (81, 80, 83), (96, 96, 96)])
+def test_one_launch_solves_on_large_levels(dims, active):
+    """Levels that only the 16x16x8, 16x16x12 and 16x16x14 tiles cover (one node
+    past the smaller kinds, remainders, the largest; with M tiles without
+    unknowns, and the largest back on launches per iteration): the gang and its abandoned form give the same bits, and the
+    state of one launch per iteration up to the order of the float64 sums,
+    whose rounding truncated float32 CG amplifies to about 1e-6 of a spacing."""
+    scene = make_tiny(seed=7, dims=dims, num_levels=1, gn=2, pcg=7,
+                      n_dense=300 if active else 12000, n_sparse=20,
+                      spacing=0.5, origin=(0.2, -1.0, 0.4))
+    out = {}
+    for mode in ("iterative", "gang", "tickets"):
+        lat = make_lattice(scene, iterative=mode == "iterative", active_set=active)
+        lat.debug_abandon_loops(mode == "tickets")
+        rep = lat.solve_frame(reset=True, report=True)
+        assert not rep["bits"] & 16
+        out[mode] = (rep["energy"], lat.get_state64()[0])
+    np.testing.assert_array_equal(out["tickets"][0], out["gang"][0])
+    np.testing.assert_array_equal(out["tickets"][1], out["gang"][1])
+    assert abs(out["gang"][0][0] / out["iterative"][0][0] - 1.0) < 1e-6
+    assert np.abs(out["gang"][1] - out["iterative"][1]).max() < 1e-5 * scene.spec.spacing
