@@ -210,6 +210,24 @@ Dispatch<T> energy_of(const LevelView<T>& V) { return single(V, energy_blocks(V.
 template <typename T>
 Dispatch<T> one_of(const LevelView<T>& V) { return single(V, 1); }
 
+// Whether a kernel on the current device may read `bytes` at p: inside one
+// allocation of this device and on a float boundary.  Anything else (another
+// device's memory, host memory, a range that a copy would refuse) is left to
+// the copy.
+bool readable_here(const void* p, size_t bytes) {
+  int dev = 0;
+  hipPointerAttribute_t at{};
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  const bool ok = (uintptr_t)p % sizeof(float) == 0 && hipGetDevice(&dev) == hipSuccess &&
+                  hipPointerGetAttributes(&at, p) == hipSuccess &&
+                  at.type == hipMemoryTypeDevice && at.device == dev &&
+                  hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) == hipSuccess &&
+                  (const char*)p + bytes <= (const char*)base + size;
+  if (!ok) (void)hipGetLastError();
+  return ok;
+}
+
 int bits_for(int n) {
   int b = 1;
   while ((1ll << b) < (long long)n) ++b;
@@ -360,7 +378,7 @@ class Solver final : public ISolver {
       VD_CHECK(pool_.alloc(&fresh_, (size_t)finest().N));
     }
     VD_CHECK(pool_.alloc(&d_flags_, 4));
-    VD_TRY(hipHostMalloc((void**)&h_flags_, 4 * sizeof(int), hipHostMallocDefault));
+    VD_TRY(hipHostMalloc((void**)&h_flags_, 8 * sizeof(int), hipHostMallocDefault));
     VD_TRY(hipHostMalloc((void**)&h_sc_, sizeof(Scalars), hipHostMallocDefault));
     VD_TRY(hipHostMalloc((void**)&h_pose_, 12 * sizeof(double), hipHostMallocDefault));
     VD_CHECK(ensure_track(0, 0, 0));
@@ -382,31 +400,39 @@ class Solver final : public ISolver {
     const int C = (int)c->n_dense, S = (int)c->n_sparse;
     // stage the inputs (the caller's buffers are not kept)
     VD_CHECK(ensure_staging(C, S));
+    const struct { float* dst; const float* src; size_t bytes; } in[6] = {
+        {st_canon_, c->canon, 12ull * C},           {st_target_, c->target, 12ull * C},
+        {st_normal_, c->normal, 12ull * C},         {st_weight_, c->weight, c->weight ? 4ull * C : 0},
+        {st_scanon_, c->sparse_canon, 12ull * S},   {st_starget_, c->sparse_target, 12ull * S}};
+    // buffers of this device are read by the kernel that checks them
+    bool direct = c->mem == VD_MEM_DEVICE;
+    for (const auto& x : in)
+      if (direct && x.bytes) direct = readable_here(x.src, x.bytes);
     const hipMemcpyKind kind = c->mem == VD_MEM_HOST ? hipMemcpyHostToDevice
                                                      : hipMemcpyDeviceToDevice;
-    if (C > 0) {
-      VD_TRY(hipMemcpyAsync(st_canon_, c->canon, 12ull * C, kind, stream_));
-      VD_TRY(hipMemcpyAsync(st_target_, c->target, 12ull * C, kind, stream_));
-      VD_TRY(hipMemcpyAsync(st_normal_, c->normal, 12ull * C, kind, stream_));
-      if (c->weight) VD_TRY(hipMemcpyAsync(st_weight_, c->weight, 4ull * C, kind, stream_));
-    }
-    if (S > 0) {
-      VD_TRY(hipMemcpyAsync(st_scanon_, c->sparse_canon, 12ull * S, kind, stream_));
-      VD_TRY(hipMemcpyAsync(st_starget_, c->sparse_target, 12ull * S, kind, stream_));
-    }
+    for (const auto& x : in)
+      if (!direct && x.bytes)
+        VD_TRY(hipMemcpyAsync(x.dst, x.src, x.bytes, kind, stream_));
     RawConstraints raw;
     raw.canon = st_canon_; raw.target = st_target_; raw.normal = st_normal_;
     raw.weight = c->weight ? st_weight_ : nullptr;
     raw.sparse_canon = st_scanon_; raw.sparse_target = st_starget_;
     raw.n_dense = C; raw.n_sparse = S;
     // validate before touching any per-level structure
-    VD_TRY(hipMemsetAsync(d_flags_, 0, sizeof(int), stream_));
+    RawConstraints given = raw;
+    Staging st{};
+    if (direct) {
+      given.canon = c->canon; given.target = c->target; given.normal = c->normal;
+      given.weight = c->weight;
+      given.sparse_canon = c->sparse_canon; given.sparse_target = c->sparse_target;
+      st = {st_canon_, st_target_, st_normal_, st_weight_, st_scanon_, st_starget_};
+    }
     const LevelData<T>& c0 = lv_[0];
-    VD_TRY(launch_validate(raw, c0.nx, c0.ny, c0.nz, c0.h, desc_.origin, d_flags_, stream_));
-    VD_TRY(hipMemcpyAsync(h_flags_, d_flags_, sizeof(int), hipMemcpyDeviceToHost, stream_));
+    h_flags_[4] = h_flags_[5] = 0;
+    VD_TRY(launch_stage(given, st, c0.nx, c0.ny, c0.nz, c0.h, desc_.origin, h_flags_ + 4, stream_));
     VD_TRY(hipStreamSynchronize(stream_));
-    if (h_flags_[0] & 1) return VD_EINVAL;
-    if (h_flags_[0] & 2) return VD_ERANGE;
+    if (h_flags_[4]) return VD_EINVAL;
+    if (h_flags_[5]) return VD_ERANGE;
     have_frame_ = false;
     return build_levels(raw, C, S, true);
   }

@@ -38,48 +38,83 @@ constexpr int kCellBlocks = 1536;
 // constraint validation and per-level rows
 // ===========================================================================
 
+// Faults of dense sample or sparse pair i: 1 a value that is not finite or a
+// negative weight, 2 a canonical point outside the coarsest level's node box.
+// The values also go to st's arrays where they are not null.
+__device__ __forceinline__ int sample_faults(const RawConstraints& c, const Staging& st, int i,
+                                             int nx0, int ny0, int nz0, double h0, double ox,
+                                             double oy, double oz) {
+  int f = 0;
+  const bool dense = i < c.n_dense;
+  const size_t j = 3 * (size_t)(dense ? i : i - c.n_dense);
+  const float* pc = (dense ? c.canon : c.sparse_canon) + j;
+  const float* pt = (dense ? c.target : c.sparse_target) + j;
+  const float x[3] = {pc[0], pc[1], pc[2]}, y[3] = {pt[0], pt[1], pt[2]};
+  if (dense) {
+    const float* pn = c.normal + j;
+    const float n[3] = {pn[0], pn[1], pn[2]};
+    const float w = c.weight ? c.weight[i] : 1.0f;
+    if (!isfinite(n[0]) || !isfinite(n[1]) || !isfinite(n[2])) f |= 1;
+    if (!isfinite(w) || w < 0.0f) f |= 1;
+    if (st.normal)
+      for (int k = 0; k < 3; ++k) st.normal[j + k] = n[k];
+    if (st.weight && c.weight) st.weight[i] = w;
+  }
+  float* const sc = dense ? st.canon : st.sparse_canon;
+  float* const sy = dense ? st.target : st.sparse_target;
+  const double o[3] = {ox, oy, oz};
+  const int n[3] = {nx0, ny0, nz0};
+  for (int k = 0; k < 3; ++k) {
+    if (sc) sc[j + k] = x[k];
+    if (sy) sy[j + k] = y[k];
+    if (!isfinite(x[k]) || !isfinite(y[k])) f |= 1;
+    const double u = ((double)x[k] - o[k]) / h0;
+    if (!(u >= 0.0 && u <= (double)(n[k] - 1))) f |= 2;
+  }
+  return f;
+}
+
 __global__ __launch_bounds__(kBlock) void k_validate(RawConstraints c, int nx0, int ny0, int nz0,
                                                      double h0, double ox, double oy, double oz,
                                                      int* flags) {
   const int total = c.n_dense + c.n_sparse;
   int f = 0;
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < total; i += gridDim.x * kBlock) {
-    const float* pc;
-    const float* pt;
-    if (i < c.n_dense) {
-      pc = c.canon + 3 * (size_t)i;
-      pt = c.target + 3 * (size_t)i;
-      const float* pn = c.normal + 3 * (size_t)i;
-      for (int k = 0; k < 3; ++k)
-        if (!isfinite(pn[k])) f |= 1;
-      if (c.weight) {
-        const float w = c.weight[i];
-        if (!isfinite(w) || w < 0.0f) f |= 1;
-      }
-    } else {
-      const int s = i - c.n_dense;
-      pc = c.sparse_canon + 3 * (size_t)s;
-      pt = c.sparse_target + 3 * (size_t)s;
-    }
-    for (int k = 0; k < 3; ++k)
-      if (!isfinite(pc[k]) || !isfinite(pt[k])) f |= 1;
-    const double o[3] = {ox, oy, oz};
-    const int n[3] = {nx0, ny0, nz0};
-    for (int k = 0; k < 3; ++k) {
-      const double u = ((double)pc[k] - o[k]) / h0;
-      if (!(u >= 0.0 && u <= (double)(n[k] - 1))) f |= 2;
-    }
-  }
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < total; i += gridDim.x * kBlock)
+    f |= sample_faults(c, Staging{}, i, nx0, ny0, nz0, h0, ox, oy, oz);
   if (f) atomicOr(flags, f);
+}
+
+// Copies a frame's inputs and checks them on the way, with the faults written
+// to host memory: one launch in place of six copies, a cleared flag, the check
+// and a copy of the flag, whose launches cost more than the bytes (3.5 MB at
+// 87 000 samples).
+__global__ __launch_bounds__(kBlock) void k_stage(RawConstraints c, Staging st, int nx0, int ny0,
+                                                  int nz0, double h0, double ox, double oy,
+                                                  double oz, int* host_flags) {
+  const int total = c.n_dense + c.n_sparse;
+  int f = 0;
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < total; i += gridDim.x * kBlock)
+    f |= sample_faults(c, st, i, nx0, ny0, nz0, h0, ox, oy, oz);
+  // (plain stores of the same value: atomics may not reach host memory)
+  if (f & 1) __hip_atomic_store(host_flags, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (f & 2) __hip_atomic_store(host_flags + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 hipError_t launch_validate(const RawConstraints& c, int nx0, int ny0, int nz0, double h0,
                            const double* o, int* flags, hipStream_t s) {
   const int total = c.n_dense + c.n_sparse;
   if (total == 0) return hipSuccess;
-  int grid = blocks_for(total);
-  if (grid > 4096) grid = 4096;
+  const int grid = std::min(blocks_for(total), 4096);
   k_validate<<<grid, kBlock, 0, s>>>(c, nx0, ny0, nz0, h0, o[0], o[1], o[2], flags);
+  return hipGetLastError();
+}
+
+hipError_t launch_stage(const RawConstraints& c, const Staging& st, int nx0, int ny0, int nz0,
+                        double h0, const double* o, int* host_flags, hipStream_t s) {
+  const int total = c.n_dense + c.n_sparse;
+  if (total == 0) return hipSuccess;
+  const int grid = std::min(blocks_for(total), 4096);
+  k_stage<<<grid, kBlock, 0, s>>>(c, st, nx0, ny0, nz0, h0, o[0], o[1], o[2], host_flags);
   return hipGetLastError();
 }
 

@@ -131,7 +131,16 @@ struct RawConstraints {
   int n_dense, n_sparse;
 };
 
+// Where a frame's inputs are kept (null: they are there already).
+struct Staging {
+  float *canon, *target, *normal, *weight, *sparse_canon, *sparse_target;
+};
+
 // ---- constraint build ----------------------------------------------------
+// Copies the inputs to `st` and checks them; host_flags (host memory, two ints
+// cleared by the caller): an invalid value, a point out of range.
+hipError_t launch_stage(const RawConstraints& c, const Staging& st, int nx0, int ny0, int nz0,
+                        double h0, const double* origin, int* host_flags, hipStream_t s);
 hipError_t launch_validate(const RawConstraints& c, int nx0, int ny0, int nz0, double h0,
                            const double* origin, int* flags, hipStream_t s);
 

@@ -392,3 +392,41 @@ def test_one_launch_solves_on_large_levels(dims, active):
     np.testing.assert_array_equal(out["tickets"][1], out["gang"][1])
     assert abs(out["gang"][0][0] / out["iterative"][0][0] - 1.0) < 1e-6
     assert np.abs(out["gang"][1] - out["iterative"][1]).max() < 1e-5 * scene.spec.spacing
+
+
+@pytest.mark.parametrize("n_dense,n_sparse", [(0, 3), (1, 0), (257, 5), (3000, 40)])
+def test_device_inputs_equal_host_inputs(n_dense, n_sparse):
+    """Inputs in device memory, at odd float offsets: the state of host inputs,
+    to the last bit, and the same errors for bad values (empty parts, one
+    sample, one past a workgroup, several workgroups)."""
+    import torch
+    from paper_1603_08161_amd import Lattice, VDError, VD_ERANGE, VD_EINVAL
+    scene = make_tiny(seed=2, dims=(12, 9, 10), n_dense=max(n_dense, 1), n_sparse=n_sparse)
+    host = [scene.canon, scene.target, scene.normal, scene.weight, scene.sparse_canon,
+            scene.sparse_target]
+    host = [x[:n_dense] for x in host[:4]] + host[4:]
+
+    def shifted(x):
+        flat = torch.zeros(x.size + 3, device="cuda")
+        flat[3:] = torch.from_numpy(np.ascontiguousarray(x)).reshape(-1).cuda()
+        return flat[3:].view(x.shape)
+
+    def solved(arrays):
+        lat = Lattice.from_spec(scene.spec)
+        lat.set_constraints(*[x if len(x) else None for x in arrays])
+        lat.solve_frame(reset=True)
+        return lat.get_state()
+    ref = solved(host)
+    got = solved([shifted(x) for x in host])
+    np.testing.assert_array_equal(got[0], ref[0])
+    np.testing.assert_array_equal(got[1], ref[1])
+    for k, value, code in ((0, 99.0, VD_ERANGE), (1, np.nan, VD_EINVAL), (2, np.inf, VD_EINVAL),
+                           (3, -1.0, VD_EINVAL), (4, -99.0, VD_ERANGE), (5, np.nan, VD_EINVAL)):
+        if len(host[k]) == 0:
+            continue
+        bad = [np.array(x) for x in host]
+        bad[k].reshape(-1)[-1] = value
+        for arrays in (bad, [shifted(x) for x in bad]):
+            with pytest.raises(VDError) as ei:
+                solved(arrays)
+            assert ei.value.code == code
