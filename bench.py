@@ -122,7 +122,7 @@ def main() -> int:
     ap.add_argument("--warm-frames", type=int, default=22,
                     help="frames of the held-out sequence in the warm-vs-plain leg")
     ap.add_argument("--persistent", action="store_true",
-                    help="one persistent launch per CG solve on levels of <= 128 tiles")
+                    help="accepted for earlier command lines: one-launch CG solves are the default")
     ap.add_argument("--tiles", type=str, default=None,
                     help="stencil tile kinds per level, e.g. 1,1,7 (default: the autotuner's "
                          "choice; fixed tiles make profiled runs time the same kernels)")
@@ -303,7 +303,7 @@ def main() -> int:
         "max_rel_energy_err": max_rel,
         "roofline": {
             "bound": "hbm",
-            "kernel": "fused CG iteration (k_cg<float>) on the 64^3 level",
+            "kernel": "one CG iteration of the one-launch solve (k_cg_loop<float>) on the 64^3 level",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
@@ -314,9 +314,9 @@ def main() -> int:
             "timing": "device clock stamps captured in the frame graph around the 64^3 "
                       "level's CG iterations 1..19 of each flip-flop iteration, last timed "
                       "replay (rocprofv3 kernel-trace mean in profiles/k_cg_frame64.md)",
-            "note": "effective bandwidth: the 64^3 level's ~40 MB per launch stays in the "
-                    "256 MB last-level cache (MALL) across iterations; the HBM-bound case is "
-                    "--workload batch32 (~530 MB per launch)",
+            "note": "bytes of an iteration that streams every vector, over its time: the solve "
+                    "keeps the vectors in registers and LDS instead and moves only the halo "
+                    "exchange and the data rows that do not fit, so this is no HBM traffic",
         },
         "kernel_mean_us_eager": prof_us,
         "set_constraints_ms": set_constraints_ms,
