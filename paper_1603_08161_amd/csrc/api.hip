@@ -1262,7 +1262,7 @@ class Solver final : public ISolver {
             stamped_launches_ = pcg - 1;
           }
           VD_CHECK(timed(on, VD_PROF_CG_LOOP, s,
-                         [&] { return launch_cg_loop<T>(pcg, loop_tiles_of(V), s, stamp, loop_ticks_); }));
+                         [&] { return launch_cg_loop<T>(pcg, loop_tiles_of(V), s, stamp, loop_ticks(v, pcg)); }));
         } else if (graph_prof && l == L_ - 1 && pcg > 1) {
           // captured frame: the device clock at the start of CG iteration 1
           // and of the final step (first workgroup of each), written on
@@ -1300,6 +1300,14 @@ class Solver final : public ISolver {
     const int kind = v.large >= 0 ? v.large : v.tile;
     return !(desc_.flags & VD_FLAG_ITERATIVE) &&
            tile_blocks(kind, v.nx, v.ny, v.nz) <= loop_cap_[kind];
+  }
+
+  // How long a solve waits for its tiles: longer than a solve of the same size
+  // that another stream may run before it (large tiles: 50 us an iteration; two
+  // 96^3 frames on two streams 26.2 ms with the short wait, 15.2 with this one).
+  int loop_ticks(const LevelData<T>& v, int pcg) const {
+    if (loop_ticks_ < 0 || v.large < 0) return loop_ticks_;
+    return loop_ticks_ + 5000 * std::min(pcg, 10000);
   }
 
   template <typename F>
@@ -1405,7 +1413,7 @@ class Solver final : public ISolver {
     auto g = [&](const Dispatch<T>& D) { return guarded(D, stop); };
     VD_TRY(launch_stencil<T>(kModeRhs, g(tiles_of(V)), nullptr, nullptr, s));
     if (cg_loop(finest()) && pcg > 0) {
-      VD_TRY(launch_cg_loop<T>(pcg, g(loop_tiles_of(V)), s));
+      VD_TRY(launch_cg_loop<T>(pcg, g(loop_tiles_of(V)), s, nullptr, loop_ticks(finest(), pcg)));
     } else {
       for (int m = 0; m < pcg; ++m) VD_TRY(launch_cg<T>(m, g(tiles_of(V)), s));
       if (pcg > 0) VD_TRY(launch_cg_final<T>(pcg - 1, g(nodes_of(V)), s));
