@@ -398,7 +398,10 @@ int vd_debug_exclusive_scan(const int32_t* in, int32_t* out, int64_t n, int32_t 
 
 /* on != 0: later one-launch CG solves of the handle behave as if their
  * workgroups could not all become resident together: they are abandoned at
- * their first exchange and finished from the ticket counter.  Same results. */
+ * their first exchange and finished from the ticket counter.  on = 1 + t:
+ * besides, every second workgroup starts only after t tickets are done (or
+ * after 10 ms); solves on other tiles than 8x8x4, 16x4x8 and 16x16x8 then fail
+ * with VD_EHIP.  Same results. */
 int vd_debug_abandon_loops(vd_lattice* l, int32_t on);
 
 /* Prolongation of a coarse per-node field (level-1) to `level`: out[3N_fine]

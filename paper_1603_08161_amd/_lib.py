@@ -667,7 +667,7 @@ class Lattice:
                                        out.ctypes.data, VD_MEM_HOST), "vd_debug_rotations")
         return out
 
-    def debug_abandon_loops(self, on: bool = True) -> None:
+    def debug_abandon_loops(self, on: int = True) -> None:
         _check(_lib.vd_debug_abandon_loops(self._h, int(on)), "vd_debug_abandon_loops")
 
     def debug_prolong(self, level: int, coarse) -> np.ndarray:

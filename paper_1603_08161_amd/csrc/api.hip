@@ -336,7 +336,7 @@ class Solver final : public ISolver {
       VD_CHECK(pool_.alloc(&v.r, 3 * N));
       VD_CHECK(pool_.alloc(&v.pa, 3 * N));
       VD_CHECK(pool_.alloc(&v.pb, 3 * N));
-      VD_CHECK(pool_.alloc(&v.ap, 3 * N));
+      VD_CHECK(pool_.alloc(&v.ap, 6 * N));
       VD_CHECK(pool_.alloc(&v.dinv, 3 * N));
       VD_CHECK(pool_.alloc(&v.bnode, 3 * N));
       VD_CHECK(pool_.alloc(&v.base, 3 * N));
@@ -356,7 +356,7 @@ class Solver final : public ISolver {
       }
       VD_CHECK(pool_.alloc(&v.scg[0], 4 * (size_t)v.max_tiles));
       VD_CHECK(pool_.alloc(&v.scg[1], 4 * (size_t)v.max_tiles));
-      VD_CHECK(pool_.alloc(&v.gang, kGangHead + 12 * (size_t)v.max_tiles));
+      VD_CHECK(pool_.alloc(&v.gang, kGangHead + 2 * kGangSlots * (size_t)v.max_tiles));
       VD_CHECK(ensure_partials(v, 0));
     }
     const int kinds = sizeof(T) == 8 ? kTileKinds
@@ -1148,7 +1148,7 @@ class Solver final : public ISolver {
   }
 
   int abandon_loops(int on) override {
-    loop_ticks_ = on ? -1 : kAssembleTicks;
+    loop_ticks_ = on > 1 ? -on : on ? -1 : kAssembleTicks;
     ++alloc_gen_;  // captured schedules hold the old limit
     return VD_OK;
   }

@@ -384,7 +384,7 @@ constexpr unsigned long long kEmptySlot = ~0ull;
 // the solve itself fills those of tiles without unknowns.
 template <typename T>
 __device__ __forceinline__ void gang_prepare(const LevelView<T>& L, int local, bool empty) {
-  if (threadIdx.x < 12 && local < L.loop_tiles) {
+  if (threadIdx.x < kGangSlots && local < L.loop_tiles) {
     const int set = threadIdx.x / 4, k = threadIdx.x % 4;
     gang_slots(L.gang)[((size_t)set * 4 + k) * L.loop_tiles + local] =
         empty && L.loop_tile == L.tile ? 0ull : kEmptySlot;
@@ -857,11 +857,15 @@ __global__ __launch_bounds__(TL::NT) void k_cg(Dispatch<T> D, int m, unsigned lo
 // the solve running once it has seen every workgroup's first partials, and
 // any workgroup that has waited `ticks` of the clock declares it abandoned (one
 // compare-and-swap word, so all agree).  Once it runs every workgroup stays
-// resident until its end, so no later wait can starve.  An abandoned solve
-// has changed nothing but scratch: its workgroups, and those that start later,
-// finish it from a ticket counter, one (iterate, tile) per ticket in order.
-// The holder of a ticket waits only for tickets handed out before its own, so
-// this makes progress with any number of resident workgroups.
+// resident until its end, so no later wait can starve.  The workgroups of an
+// abandoned solve, and those that start later, finish it from a ticket
+// counter, one (iterate, tile) per ticket in order.  The holder of a ticket
+// waits only for tickets handed out before its own, so this makes progress
+// with any number of resident workgroups.  A workgroup goes through iterate 0
+// before it learns that the solve is abandoned, and may do so when the tickets
+// are many iterates ahead: what it then reads is no longer r_0.  So no ticket
+// reads what iterate 0 of the gang stores: tickets have slot sets of their own
+// and keep A p of even iterates behind ap's 3N.
 //
 // What bounds an iteration is the instructions of the 16 waves of a compute
 // unit and the exchange's latency, so one wave alone forms the scalars, the
@@ -1025,6 +1029,18 @@ __device__ __forceinline__ void finish_ticket(double* gang) {
   }
 }
 
+// For tests: waits until `tickets` tickets of an abandoned solve are done, at
+// most 10 ms of the 100 MHz clock.
+__device__ __forceinline__ void start_late(double* gang, unsigned tickets) {
+  if (threadIdx.x == 0) {
+    const long long t0 = wall_clock64();
+    while (load_agent((unsigned long long*)gang + 2) < tickets &&
+           wall_clock64() - t0 < 1000000)
+      __builtin_amdgcn_s_sleep(1);
+  }
+  __syncthreads();
+}
+
 // The tile of workgroup g: lattices in dispatch order (so that a launch over
 // several fills up lattice by lattice), and within a lattice a contiguous
 // range of tiles per die.
@@ -1133,8 +1149,9 @@ __device__ __forceinline__ void part_product(const T (&sp)[3][LEN], int cz, R&& 
 }
 
 // All iterations of one CG solve and its last step.  stamp (may be null):
-// two clock stamps, at the start of iteration 1 and of the last step.
-template <typename T, typename LP, bool MASK>
+// two clock stamps, at the start of iteration 1 and of the last step.  LATE
+// (tests): odd tiles start after -1 - ticks tickets.
+template <typename T, typename LP, bool MASK, bool LATE = false>
 __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
                                                     unsigned long long* stamp, int ticks) {
   if (skipped(D)) return;
@@ -1197,10 +1214,11 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
     if (load) {
       // the tile's state: r_0 and d, or (solo) that of iterate m - 1
       load = false;
+      if (LATE && !solo && (tile & 1)) start_late(L.gang, -1 - ticks);
       const TilePos<TL> t(L.nx, L.ny, tile);
       const gptr<const T> __restrict__ rin = glob<const T>(m == 0 || odd ? v_r : v_r2);
       const gptr<const T> __restrict__ pin = glob<const T>(odd ? v_pa : v_pb);
-      const gptr<const T> __restrict__ apin = glob<const T>(odd ? v_ap : v_ap2);
+      const gptr<const T> __restrict__ apin = glob<const T>(odd ? v_ap + 3 * N : v_ap2);  // (solo)
       const gptr<const T> __restrict__ dinv = glob<const T>(L.dinv);
       int slot[NV];
 #pragma unroll
@@ -1235,7 +1253,7 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
 #pragma unroll
         for (int kk = 0; kk < NV; ++kk) any |= unknown(kk);
         if (!__syncthreads_or(any) && tile != 0) {
-          if (LP::LARGE && threadIdx.x < 12)
+          if (LP::LARGE && threadIdx.x < kGangSlots)
             store_agent(slots + (size_t)threadIdx.x * n_tiles + tile, 0ull);
           return;
         }
@@ -1314,14 +1332,14 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
     for (int h = 0; h < SPT; ++h) ha[h][0] = ha[h][1] = ha[h][2] = T(0);
     if (m > 0) {
       // 1. the scalars of iterate m - 1 (wave 0) and the halo's A p
-      const unsigned long long* s = slots + (size_t)((m - 1) % 3) * 4 * n_tiles;
+      const unsigned long long* s = slots + (size_t)((m - 1) % 3 + 3 * solo) * 4 * n_tiles;
       if (m == 1 && !solo && !gang_assembled(L.gang, s, n_tiles, tile == 0, ticks)) {
         solo = true;
         continue;
       }
       if (wv < 4) gang_poll(s, n_tiles, gsums, limit, &L.sc->bar_timeouts);
       __syncthreads();
-      const T* const ap_in = odd ? v_ap : v_ap2;
+      const T* const ap_in = odd ? v_ap + (solo ? 3 * N : 0) : v_ap2;
 #pragma unroll
       for (int h = 0; h < SPT; ++h) {
         if (hnode[h] < 0) continue;
@@ -1424,7 +1442,7 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
       LP::leave(ls, part_id, e, o);
     }
     __syncthreads();
-    T* const ap_out = odd ? v_ap2 : v_ap;
+    T* const ap_out = odd ? v_ap2 : v_ap + (solo ? 3 * N : 0);
     // empty the slots of the next iterate
     if (m > 0 && !solo && threadIdx.x < 4)
       store_agent(slots + ((size_t)((m + 1) % 3) * 4 + threadIdx.x) * n_tiles + tile, kEmptySlot);
@@ -1493,7 +1511,8 @@ __global__ __launch_bounds__(LP::PT) void k_cg_loop(Dispatch<T> D, int iters,
       double x = 0.0;
 #pragma unroll
       for (int u = 0; u < LP::OW; ++u) x += sums[threadIdx.x * LP::OW + u];
-      store_agent(slots + ((size_t)(m % 3) * 4 + threadIdx.x) * n_tiles + tile, slot_bits(x));
+      const int set = m % 3 + 3 * solo;
+      store_agent(slots + ((size_t)set * 4 + threadIdx.x) * n_tiles + tile, slot_bits(x));
     }
     if (solo) finish_ticket(L.gang);
     else ++m;
@@ -1580,6 +1599,18 @@ hipError_t with_loop_kernel(int kind, F&& f) {
   }
 }
 
+// The same for the kinds with an instance whose odd tiles start late.
+template <typename T, bool MASK, typename F>
+hipError_t with_late_kernel(int kind, F&& f) {
+  switch (kind) {
+    case 0: return f(k_cg_loop<T, Loop<T, TileS, 512>, MASK, true>, 512);
+    case 6: return f(k_cg_loop<T, Loop<T, TileH, 512>, MASK, true>, 512);
+    case 8:
+      if constexpr (sizeof(T) == 4) return f(k_cg_loop<T, Loop<T, TileL4, 512>, MASK, true>, 512);
+  }
+  return hipErrorNotSupported;
+}
+
 template <typename T>
 hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s,
                           unsigned long long* stamp, int ticks) {
@@ -1588,6 +1619,9 @@ hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s,
     kernel<<<D.blocks, threads, 0, s>>>(D, iters, stamp, ticks);
     return hipGetLastError();
   };
+  if (ticks < -1)
+    return D.masked ? with_late_kernel<T, true>(D.one.loop_tile, go)
+                    : with_late_kernel<T, false>(D.one.loop_tile, go);
   return D.masked ? with_loop_kernel<T, true>(D.one.loop_tile, go)
                   : with_loop_kernel<T, false>(D.one.loop_tile, go);
 }

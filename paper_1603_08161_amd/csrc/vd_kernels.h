@@ -23,6 +23,7 @@ constexpr int kA27Row = 3 * kA27Part;
 
 constexpr int kGangMaxTiles = 256;  // tiles of a lattice in a one-launch CG solve
 constexpr int kGangHead = 16;  // 8-byte words before the slots of LevelView::gang
+constexpr int kGangSlots = 12;  // exchange slots per tile: [3 sets][4 sums]
 
 struct Scalars {
   double rz;      // r^T D^-1 r of the current CG iterate
@@ -64,8 +65,8 @@ struct LevelView {
   T* r2;      // odd CG iterates
   T* pa;      // CG directions, even / odd iterates
   T* pb;
-  T* ap;      // A p, even / odd iterates
-  T* ap2;
+  T* ap;      // A p, even / odd iterates; behind ap's 3N, that of the even
+  T* ap2;     // iterates of an abandoned one-launch solve
   T* dinv;    // Jacobi preconditioner 1 / diag(A)
   T* bnode;   // J^T (weighted targets) of the data rows, per node
   T* base;    // finest state injected to this level (for the increment)
@@ -76,7 +77,8 @@ struct LevelView {
   double* scg0;  // CG block partials [4][ntiles], even / odd iterates
   double* scg1;
   double* gang;  // one-launch CG solve: kGangHead words (state, next ticket,
-                 // tickets done), then the exchange slots [3][4][loop_tiles]
+                 // tickets done), then the exchange slots [3][4][loop_tiles], and
+                 // as many of an abandoned solve
   int loop_tile, loop_tiles;  // tile kind and tiles of a one-launch CG solve
   double* pe;    // energy block partials [3][rblocks + node blocks]
   // constraint cache
@@ -254,7 +256,8 @@ hipError_t launch_cg_final(int last, const Dispatch<T>& D, hipStream_t s,
 // order.  stamp (may be
 // NULL): the device clock at the start of iteration 1 and of the last step.
 // ticks: how long a workgroup waits for the others before the solve is
-// abandoned to the ticket path (100 MHz clock; negative: at once, for tests).
+// abandoned to the ticket path (100 MHz clock; for tests -1: at once, -1 - t:
+// besides, the workgroups of odd tiles start late, after t tickets are done).
 constexpr int kAssembleTicks = 30000;
 template <typename T>
 hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s,

@@ -430,3 +430,106 @@ def test_device_inputs_equal_host_inputs(n_dense, n_sparse):
             with pytest.raises(VDError) as ei:
                 solved(arrays)
             assert ei.value.code == code
+
+
+def _tiles(dims, tile):
+    return int(np.prod([-(-n // t) for n, t in zip(dims, tile)]))
+
+
+@pytest.mark.parametrize("tile", [(8, 8, 4), (16, 4, 8)])
+@pytest.mark.parametrize("precision,active", [("fp32", False), ("fp32", True), ("fp64", False),
+                                              ("fp64", True)])
+def test_abandoned_solves_with_late_workgroups(tile, precision, active):
+    """Every second workgroup of an abandoned solve starts only when the tickets
+    of the others are 2 to 8 iterates ahead (and at once after the last one):
+    the bits of one launch per iteration."""
+    dims, pcg = (37, 11, 18), 11
+    scene = make_tiny(seed=5, dims=dims, num_levels=1, gn=2, pcg=pcg, n_dense=3000,
+                      n_sparse=20, spacing=0.6, origin=(0.2, -1.0, 0.4))
+    kw = dict(tiles=({(8, 8, 4): 1, (16, 4, 8): 7}[tile],), precision=precision,
+              active_set=active)
+    ref = make_lattice(scene, iterative=True, **kw)
+    e = ref.solve_frame(reset=True, report=True)["energy"]
+    n = _tiles(dims, tile)
+    lat = make_lattice(scene, **kw)
+    for late in (1, 2 * n, 3 * n, 3 * n + 1, 4 * n, 5 * n + n // 2, 6 * n, 7 * n + 1, 8 * n,
+                 (pcg + 1) * n):
+        lat.debug_abandon_loops(1 + late)
+        rep = lat.solve_frame(reset=True, report=True)
+        assert not rep["bits"] & 16
+        np.testing.assert_array_equal(rep["energy"], e)
+        np.testing.assert_array_equal(lat.get_state64()[0], ref.get_state64()[0])
+
+
+@pytest.mark.parametrize("active", [False, True])
+@pytest.mark.parametrize("dims", [(65, 64, 65), (79, 71, 80)])
+def test_abandoned_large_solves_with_late_workgroups(dims, active):
+    """The same on tiles of 16x16x8, against the solve that is not abandoned (the
+    launches per iteration add the same sums up in another order)."""
+    scene = make_tiny(seed=7, dims=dims, num_levels=1, gn=2, pcg=9,
+                      n_dense=300 if active else 12000, n_sparse=20,
+                      spacing=0.5, origin=(0.2, -1.0, 0.4))
+    lat = make_lattice(scene, active_set=active)
+    e = lat.solve_frame(reset=True, report=True)["energy"]
+    ref = lat.get_state64()[0]
+    n = _tiles(dims, (16, 16, 8))
+    for late in (2 * n, 3 * n + 1, 4 * n, 6 * n, 8 * n):
+        lat.debug_abandon_loops(1 + late)
+        rep = lat.solve_frame(reset=True, report=True)
+        assert not rep["bits"] & 16
+        np.testing.assert_array_equal(rep["energy"], e)
+        np.testing.assert_array_equal(lat.get_state64()[0], ref)
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("sizes", [(80, 64), (64, 64), (96, 40), (48, 16)])
+def test_solves_on_two_streams_equal_solves_alone(sizes, graph):
+    """Frames of two lattices whose solves cannot all be resident together, on
+    two streams: each has the bits it has alone."""
+    import torch
+    lats, alone = [], []
+    for k, n in enumerate(sizes):
+        scene = make_tiny(seed=20 + k, dims=(n, n - 1, n), num_levels=2, gn=3, pcg=25,
+                          n_dense=4000, n_sparse=20, spacing=0.5)
+        stream = torch.cuda.Stream()
+        lat = make_lattice(scene, graph=graph, stream=stream.cuda_stream)
+        lat.stream_object = stream
+        lat.solve_frame(reset=True)
+        torch.cuda.synchronize()
+        alone.append(lat.get_state64()[0])
+        lats.append(lat)
+    for repeat in range(4):
+        for frame in range(3):
+            for lat in lats if (repeat + frame) % 2 else lats[::-1]:
+                lat.solve_frame(reset=True)
+        torch.cuda.synchronize()
+        for lat, ref in zip(lats, alone):
+            np.testing.assert_array_equal(lat.get_state64()[0], ref)
+
+
+def test_solves_beside_foreign_kernels_equal_solves_alone():
+    """A kernel of another stream holds a compute unit for 0.2 to 5 ms, so that
+    the last workgroup of a solve on all of them (256 tiles, 100 iterations)
+    starts while the others are at work on the abandoned solve."""
+    import torch
+    scene = make_tiny(seed=31, dims=(64, 64, 64), num_levels=1, gn=1, pcg=100, n_dense=4000,
+                      n_sparse=20, spacing=0.5)
+    lat = make_lattice(scene, tiles=(5,))
+    lat.solve_frame(reset=True)
+    ref = lat.get_state64()[0]
+    side = torch.cuda.Stream()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(1000)
+        a.record()
+        torch.cuda._sleep(1_000_000)
+        b.record()
+    side.synchronize()
+    per_ms = 1_000_000 / a.elapsed_time(b)
+    for ms in np.linspace(0.2, 5.0, 25):
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(int(ms * per_ms))
+        rep = lat.solve_frame(reset=True, report=True)
+        torch.cuda.synchronize()
+        assert not rep["bits"] & 16
+        np.testing.assert_array_equal(lat.get_state64()[0], ref)
