@@ -63,6 +63,11 @@ int64_t vd_net_param_count(void);
 int vd_net_create(int32_t nx, int32_t ny, int32_t nz, int32_t max_batch, void* stream,
                   vd_net** out);
 
+/* Test entry point (no GPU needed): floats of the weight-gradient partials
+ * that a batch stores, and those that a network of max_batch allocates. */
+int vd_debug_net_partials(int32_t nx, int32_t ny, int32_t nz, int32_t max_batch, int32_t batch,
+                          int64_t* need, int64_t* have);
+
 /* Free the network.  NULL is a no-op. */
 int vd_net_destroy(vd_net* n);
 

@@ -49,6 +49,7 @@ EXPORTED = (
     "vd_debug_abandon_loops",
     "vd_batch_create", "vd_batch_solve", "vd_batch_destroy", "vd_batch_profile",
     "vd_get_profile", "vd_warm_features", "vd_net_param_count", "vd_net_create", "vd_net_destroy",
+    "vd_debug_net_partials",
     "vd_net_set_params", "vd_net_get_params", "vd_net_forward", "vd_net_gradients",
     "vd_net_train_step", "vd_associate", "vd_rigid_pose", "vd_set_depth_frame", "vd_get_pose",
     "vd_set_pose", "vd_track_frame", "vd_debug_associate", "vd_rigid_pose_noalloc",
@@ -235,6 +236,8 @@ def _load() -> C.CDLL:
         "vd_get_profile": ([vp, dp, C.POINTER(C.c_int32)], C.c_int),
         "vd_warm_features": ([vp, vp, vp, i32], C.c_int),
         "vd_net_param_count": ([], i64),
+        "vd_debug_net_partials": ([i32, i32, i32, i32, i32, C.POINTER(i64), C.POINTER(i64)],
+                                  C.c_int),
         "vd_net_create": ([i32, i32, i32, i32, vp, C.POINTER(vp)], C.c_int),
         "vd_net_destroy": ([vp], C.c_int),
         "vd_net_set_params": ([vp, vp, i32], C.c_int),

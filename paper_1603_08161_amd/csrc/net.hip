@@ -850,6 +850,25 @@ class Net {
     for (void* p : ptrs_) (void)hipFree(p);
   }
 
+  // Floats of wpart_: what the weight gradients of any layer and any batch of
+  // up to max_batch_ samples store.  (The chunks of a smaller batch can be
+  // more than those of the largest, as their length is rounded up.)
+  int64_t wpart_capacity() const {
+    int64_t n = 1;
+    for (int l = 0; l < kNumLayers; ++l) {
+      const WgPlan p = wg_plan(l, max_batch_);
+      n = std::max(n, (int64_t)p.most_chunks * p.mpad * p.npad);
+    }
+    return n;
+  }
+
+  // Most floats that a batch's weight gradients store in wpart_.
+  int64_t wpart_need(int batch) const {
+    int64_t n = 0;
+    for (int l = 0; l < kNumLayers; ++l) n = std::max(n, wg_plan(l, batch).partials());
+    return n;
+  }
+
   static int64_t param_count() {
     int64_t n = 0;
     for (const LayerDef& d : kLayers) n += layer_params(d);
@@ -906,13 +925,7 @@ class Net {
     mse_blocks_ = (int)((n0 + kBlock - 1) / kBlock);
     VD_NET_CHECK(alloc(&mse_part_, mse_blocks_));
     VD_NET_CHECK(alloc(&loss_, 1));
-    // weight-gradient partials: the largest layer's need
-    size_t need = 1;
-    for (int l = 0; l < kNumLayers; ++l) {
-      const WgPlan p = wg_plan(l, B);
-      need = std::max(need, (size_t)p.nchunks * p.mpad * p.npad);
-    }
-    VD_NET_CHECK(alloc(&wpart_, need));
+    VD_NET_CHECK(alloc(&wpart_, wpart_capacity()));
     return pack() == hipSuccess ? VD_OK : VD_EHIP;
   }
 
@@ -1015,7 +1028,9 @@ class Net {
  private:
   struct WgPlan {
     int mpad, npad, nb, mtiles, nchunks;
+    int most_chunks;  // nchunks of no smaller batch is above this
     int64_t vox_per_chunk;
+    int64_t partials() const { return (int64_t)nchunks * mpad * npad; }
   };
 
   template <typename P>
@@ -1056,6 +1071,7 @@ class Net {
     int64_t nch = (512 + p.mtiles - 1) / p.mtiles;
     if (nch > steps) nch = steps;
     if (nch < 1) nch = 1;
+    p.most_chunks = (int)nch;
     p.vox_per_chunk = (steps + nch - 1) / nch * kWgVox;
     p.nchunks = (int)((M + p.vox_per_chunk - 1) / p.vox_per_chunk);
     return p;
@@ -1195,6 +1211,7 @@ class Net {
 
   hipError_t launch_wgrad(int l, const uint16_t* x, const uint16_t* gy, int batch) {
     const WgPlan p = wg_plan(l, batch);
+    if (p.partials() > wpart_capacity()) return hipErrorInvalidValue;
     const ConvArgs A = fwd_args(l, x, batch);
     WgradArgs G{};
     G.dy = gy;
@@ -1386,6 +1403,17 @@ int vd_net_create(int32_t nx, int32_t ny, int32_t nz, int32_t max_batch, void* s
     return VD_ENOMEM;
   }
   *out = h;
+  return VD_OK;
+}
+
+int vd_debug_net_partials(int32_t nx, int32_t ny, int32_t nz, int32_t max_batch, int32_t batch,
+                          int64_t* need, int64_t* have) {
+  if (nx < 1 || ny < 1 || nz < 1 || batch < 1 || batch > max_batch || !need || !have)
+    return VD_EINVAL;
+  if ((int64_t)nx * ny * nz * max_batch > (int64_t)1 << 28) return VD_EINVAL;
+  const vd::net::Net plan(nx, ny, nz, max_batch, nullptr);
+  *need = plan.wpart_need(batch);
+  *have = plan.wpart_capacity();
   return VD_OK;
 }
 
