@@ -404,6 +404,10 @@ int vd_debug_exclusive_scan(const int32_t* in, int32_t* out, int64_t n, int32_t 
  * with VD_EHIP.  Same results. */
 int vd_debug_abandon_loops(vd_lattice* l, int32_t on);
 
+/* The tile (1 .. VD_TILE_KINDS) that a level of dims nodes gets when
+ * vd_lattice_desc.tile is 0.  Needs no GPU. */
+int vd_debug_default_tile(const int32_t dims[3], int32_t precision, uint32_t flags);
+
 /* Prolongation of a coarse per-node field (level-1) to `level`: out[3N_fine]
  * = trilinear evaluation of coarse[3N_coarse] at the fine rest positions.
  * Synchronous. */

@@ -46,7 +46,7 @@ EXPORTED = (
     "vd_get_energy", "vd_get_state", "vd_set_state", "vd_level_info", "vd_strerror",
     "vd_debug_apply", "vd_debug_gradient", "vd_debug_energy", "vd_debug_diag",
     "vd_debug_rotations", "vd_debug_fit_rotations", "vd_debug_prolong", "vd_tune",
-    "vd_debug_abandon_loops",
+    "vd_debug_abandon_loops", "vd_debug_default_tile",
     "vd_batch_create", "vd_batch_solve", "vd_batch_destroy", "vd_batch_profile",
     "vd_get_profile", "vd_warm_features", "vd_net_param_count", "vd_net_create", "vd_net_destroy",
     "vd_debug_net_partials",
@@ -228,6 +228,7 @@ def _load() -> C.CDLL:
         "vd_get_state64": ([vp, vp, vp, i32], C.c_int),
         "vd_debug_prolong": ([vp, i32, vp, vp, i32], C.c_int),
         "vd_debug_abandon_loops": ([vp, i32], C.c_int),
+        "vd_debug_default_tile": ([C.POINTER(i32), i32, C.c_uint32], C.c_int),
         "vd_tune": ([vp, i32, C.POINTER(C.c_int32), dp], C.c_int),
         "vd_batch_create": ([C.POINTER(vp), i32, C.POINTER(vp)], C.c_int),
         "vd_batch_solve": ([vp, C.POINTER(SolveOpts), dp], C.c_int),

@@ -320,10 +320,11 @@ class Solver final : public ISolver {
       v.ncell = (v.nx - 1) * (v.ny - 1) * (v.nz - 1);
       const int want = desc_.tile[l];
       if (want < 0 || want > kTileKinds) return VD_EINVAL;
-      v.tile = want > 0 ? want - 1 : default_tile(v.nx, v.ny, v.nz);
+      const bool masked = (desc_.flags & VD_FLAG_ACTIVE_SET) != 0;
+      v.tile = want > 0 ? want - 1 : default_tile(v.nx, v.ny, v.nz, sizeof(T) == 8, masked,
+                                                   (desc_.flags & VD_FLAG_ITERATIVE) != 0);
       v.ntiles = tile_blocks(v.tile, v.nx, v.ny, v.nz);
-      if (sizeof(T) == 4)
-        v.large = large_loop_tile(v.nx, v.ny, v.nz, (desc_.flags & VD_FLAG_ACTIVE_SET) != 0);
+      if (sizeof(T) == 4) v.large = large_loop_tile(v.nx, v.ny, v.nz, masked);
       for (int k = 0; k < kTileKinds; ++k)
         v.max_tiles = std::max(v.max_tiles, tile_blocks(k, v.nx, v.ny, v.nz));
       for (int k = 0; k < 3; ++k) dims[k] = (dims[k] + 1) / 2;
@@ -2376,6 +2377,12 @@ int vd_debug_rotations(vd_lattice* l, int32_t level, const float* pos, const flo
                        float* rot_out, int32_t mem) {
   if (!l) return VD_EINVAL;
   return l->impl->debug_rotations(level, pos, rot_prev, rot_out, mem);
+}
+
+int vd_debug_default_tile(const int32_t dims[3], int32_t precision, uint32_t flags) {
+  if (!dims || dims[0] < 2 || dims[1] < 2 || dims[2] < 2) return VD_EINVAL;
+  return 1 + vd::default_tile(dims[0], dims[1], dims[2], precision == VD_FP64,
+                              (flags & VD_FLAG_ACTIVE_SET) != 0, (flags & VD_FLAG_ITERATIVE) != 0);
 }
 
 int vd_debug_abandon_loops(vd_lattice* l, int32_t on) {

@@ -132,18 +132,24 @@ int tile_blocks(int kind, int nx, int ny, int nz) {
 // gradient pass: 32^3 in 128 tiles of 8x8x4 4.7, in 64 of 16x4x8 4.9, in 32 of
 // 32x8x4 8.7; 48^3 in 216 of 16x4x8 6.7, in 108 of 32x8x4 8.1); among the
 // 1024-node kinds the one that pads least.  Larger levels run one launch per
-// iteration, fastest with 128-byte rows (96^3: 37.7 with 32x8x4 on 256
-// threads, 42.6 with 8x8x8).
-int default_tile(int nx, int ny, int nz) {
+// iteration: in float32 fastest with 128-byte rows (2 x 20 iterations at 110^3:
+// 3.04 ms with 32x8x4 on 256 threads, 3.23 with 8x8x8), in float64 and with
+// the optimised set, whose tiles without unknowns are skipped, with 8x8x8
+// (110^3: float64 7.18 against 9.29, optimised set 1.23 against 1.69, both 1.66
+// against 3.51).  So do, in float64, levels of the 1024-node kinds where one
+// launch per iteration is asked for (64^3: 1.68 against 1.74 ms with 32x8x4 on
+// 1024 threads; in float32 1.07 against 1.02).
+int default_tile(int nx, int ny, int nz, bool f64, bool masked, bool iterative) {
   const int order[] = {7, 6, 3, 5, 4};
   int best = -1;
   for (const int k : order) {
     const int n = tile_blocks(k, nx, ny, nz);
     if (n > kGangMaxTiles) continue;
     if (k == 7 || k == 6) return k;
+    if (f64 && iterative) break;
     if (best < 0 || n < tile_blocks(best, nx, ny, nz)) best = k;
   }
-  return best >= 0 ? best : nx >= 24 ? 2 : 1;
+  return best >= 0 ? best : nx >= 24 && !f64 && !masked ? 2 : 1;
 }
 
 // The tile of a one-launch CG solve on a level that is too large for every

@@ -221,7 +221,7 @@ enum StencilMode { kModeRhs = 1, kModeApply = 2, kModeGrad = 3 };
 // 1: 8x8x8, 2: 32x8x4), the kind used when none is chosen, and the
 // workgroups of the node-parallel and energy kernels.
 int tile_blocks(int kind, int nx, int ny, int nz);
-int default_tile(int nx, int ny, int nz);
+int default_tile(int nx, int ny, int nz, bool f64, bool masked, bool iterative);
 int large_loop_tile(int nx, int ny, int nz, bool masked);
 int node_blocks(int N);
 int energy_blocks(int rblocks, int N);
