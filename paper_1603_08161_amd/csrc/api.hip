@@ -360,9 +360,7 @@ class Solver final : public ISolver {
       VD_CHECK(pool_.alloc(&v.gang, kGangHead + 2 * kGangSlots * (size_t)v.max_tiles));
       VD_CHECK(ensure_partials(v, 0));
     }
-    const int kinds = sizeof(T) == 8 ? kTileKinds
-                      : desc_.flags & VD_FLAG_ACTIVE_SET ? kLoopKinds - 1 : kLoopKinds;
-    for (int k = 0; k < kinds; ++k)
+    for (int k = 0; k < kLoopKinds; ++k)
       VD_TRY(cg_loop_capacity<T>(k, (desc_.flags & VD_FLAG_ACTIVE_SET) != 0, &loop_cap_[k]));
     if ((desc_.flags & VD_FLAG_PROFILE) && (desc_.flags & VD_FLAG_GRAPH))
       VD_CHECK(pool_.alloc(&stamps_, 2 * kMaxStamped));  // written by captured CG launches
@@ -1025,9 +1023,11 @@ class Solver final : public ISolver {
   const vd_lattice_desc& desc() const { return desc_; }
   int level_nodes(int l) const { return lv_[l].N; }
   int level_tile(int l) const { return lv_[l].tile; }
-  int level_capacity(int l) const { return loop_cap_[lv_[l].tile]; }
-  // (a batch launches all its lattices with one tile kind: none of the large)
-  bool level_loop(int l) const { return lv_[l].large < 0 && cg_loop(lv_[l]); }
+  // Tiles of level l where a batch may run its solves as one launch, else 0.
+  // (A batch launches all its lattices with one tile kind: none of the large.)
+  int level_loop_tiles(int l) const {
+    return lv_[l].large < 0 && !(desc_.flags & VD_FLAG_ITERATIVE) ? lv_[l].ntiles : 0;
+  }
   void force_tile(int l, int kind) {
     if (lv_[l].tile == kind) return;
     lv_[l].tile = kind;
@@ -1767,6 +1767,10 @@ class Batch final : public IBatch {
     stream_ = h_[0]->stream();
     graph_ = (h_[0]->desc().flags & VD_FLAG_GRAPH) != 0;
     prof_ = !graph_ && (h_[0]->desc().flags & VD_FLAG_PROFILE) != 0;
+    // one lattice with a set M and the launches are those with masks
+    bool masked = false;
+    for (const auto* h : h_) masked |= (h->desc().flags & VD_FLAG_ACTIVE_SET) != 0;
+    for (int k = 0; k < kTileKinds; ++k) VD_TRY(cg_loop_capacity<T>(k, masked, &loop_cap_[k]));
     // one tile kind per level: that of the largest lattice
     for (int l = 0; l < L_; ++l) {
       int big = 0;
@@ -1846,8 +1850,11 @@ class Batch final : public IBatch {
 
   // Whether the position solves of level l run as one launch.
   bool loops(int l) const {
-    for (const auto* h : h_)
-      if (!h->level_loop(l)) return false;
+    const int cap = loop_cap_[h_[0]->level_tile(l)];
+    for (const auto* h : h_) {
+      const int tiles = h->level_loop_tiles(l);
+      if (tiles == 0 || tiles > cap) return false;
+    }
     return true;
   }
 
@@ -1870,7 +1877,7 @@ class Batch final : public IBatch {
       while (g < groups.size() && left[g] < tiles(b)) ++g;
       if (g == groups.size()) {
         groups.emplace_back();
-        left.push_back(h_[0]->level_capacity(F));
+        left.push_back(loop_cap_[h_[0]->level_tile(F)]);
       }
       groups[g].push_back(b);
       left[g] -= tiles(b);
@@ -2055,6 +2062,7 @@ class Batch final : public IBatch {
   bool graph_ = false;
   hipGraphExec_t exec_[2] = {nullptr, nullptr};
   bool prof_ = false;
+  int loop_cap_[kTileKinds] = {};  // most tiles of a lattice's one-launch CG solve
   EventTimer timer_;
   std::vector<Tables> tables_;
   std::vector<long> gens_;

@@ -1595,14 +1595,16 @@ hipError_t with_loop_kernel(int kind, F&& f) {
     }
   }
   switch (kind) {
+    case 0:
+    case 7: return f(k_cg_loop<T, Loop<T, TileS, 512>, MASK>, 512);
     case 1: return f(k_cg_loop<T, Loop<T, TileM, 512>, MASK>, 512);
     case 2: return f(k_cg_loop<T, Loop<T, TileW, 256>, MASK>, 256);
     case 3: return f(k_cg_loop<T, Loop<T, TileX, 512>, MASK>, 512);
     case 4: return f(k_cg_loop<T, Loop<T, TileZ, 512>, MASK>, 512);
     case 5: return f(k_cg_loop<T, Loop<T, TileY, 512>, MASK>, 512);
     case 6: return f(k_cg_loop<T, Loop<T, TileH, 512>, MASK>, 512);
-    default: return f(k_cg_loop<T, Loop<T, TileS, 512>, MASK>, 512);
   }
+  return hipErrorNotSupported;  // a large tile without an instance
 }
 
 // The same for the kinds with an instance whose odd tiles start late.
@@ -1642,6 +1644,7 @@ hipError_t cg_loop_capacity(int kind, bool masked, int* tiles) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0);
   };
   e = masked ? with_loop_kernel<T, true>(kind, ask) : with_loop_kernel<T, false>(kind, ask);
+  if (e == hipErrorNotSupported) e = hipSuccess;  // per_cu is 0
   *tiles = std::min(cus * per_cu, kGangMaxTiles);
   return e;
 }

@@ -263,7 +263,8 @@ template <typename T>
 hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s,
                           unsigned long long* stamp = nullptr, int ticks = kAssembleTicks);
 
-// Tiles of a kind (< kLoopKinds) that fit on the GPU together in launch_cg_loop.
+// Tiles of a kind (< kLoopKinds) that fit on the GPU together in launch_cg_loop
+// (0: it has no instance).
 template <typename T>
 hipError_t cg_loop_capacity(int kind, bool masked, int* tiles);
 

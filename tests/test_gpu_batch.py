@@ -163,3 +163,20 @@ def test_batch_of_more_tiles_than_the_gpu_holds(tile):
         rep = ref.solve_frame(reset=True, report=True)
         np.testing.assert_array_equal(e, rep["energy"])
         np.testing.assert_array_equal(lat.get_state()[0], ref.get_state()[0])
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("tile", [1, 5])
+def test_batch_of_lattices_with_and_without_the_optimised_set(precision, tile):
+    """One lattice with a set M makes the batch's launches those with masks; the
+    others' solves keep the bits of their own launches without."""
+    from paper_1603_08161_amd import Batch
+    scenes = _scenes(gn=2, pcg=6)
+    kw = {"tiles": (tile, tile, tile), "precision": precision}
+    lats = [make_lattice(s, active_set=k % 2 == 1, **kw) for k, s in enumerate(scenes)]
+    E = Batch(lats).solve(reset=True, energies=True)
+    for k, (s, lat, e) in enumerate(zip(scenes, lats, E)):
+        ref = make_lattice(s, active_set=k % 2 == 1, **kw)
+        rep = ref.solve_frame(reset=True, report=True)
+        np.testing.assert_array_equal(e, rep["energy"])
+        np.testing.assert_array_equal(lat.get_state64()[0], ref.get_state64()[0])
