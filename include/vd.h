@@ -266,8 +266,10 @@ int vd_solve_frame(vd_lattice* l, const vd_solve_opts* opts, vd_solve_report* re
  * it, so both parts overlap on the GPU, unless both have levels whose CG
  * solves are one launch (those hold whole compute units until their lattice
  * is done; the parts then run one after the other).  The batch does not own
- * the handles: they must outlive it.  Creating it sets every handle's stencil tile, per
- * level, to the tile of the largest lattice of its part at that level.
+ * the handles: they must outlive it.  Creating it sets every handle's stencil
+ * tile, per level, to the tile of the largest lattice of its part at that
+ * level if that was chosen (vd_lattice_desc.tile, vd_tune, another batch), else
+ * to one that suits the launches over all of them.
  * VD_EINVAL on mismatched handles. */
 int vd_batch_create(vd_lattice* const* lattices, int32_t n, vd_batch** out);
 
@@ -282,12 +284,13 @@ int vd_batch_solve(vd_batch* b, const vd_solve_opts* opts, double* energies);
 /* Tile autotuner of the batch (as vd_tune, over the batched launches): per
  * part (float32 lattices, then float64 ones) and level, times one batched
  * position step (gradient pass and `iters` CG iterations) from the current
- * state with every tile kind, keeps the fastest for every handle of the part
- * and restores the displacements.  tile_out[2 * VD_MAX_LEVELS] (may be NULL)
+ * state with every tile kind, its solve as one launch and as one per iteration,
+ * keeps the fastest for every handle of the part and restores the
+ * displacements.  tile_out[2 * VD_MAX_LEVELS] (may be NULL)
  * receives the chosen kinds (1-based; 0 for a missing part), us_out[2 *
  * VD_MAX_LEVELS * VD_TILE_KINDS] (may be NULL) the microseconds per CG
- * iteration, gradient pass included, of every (part, level, kind).
- * VD_ESTATE if a handle has no constraints.  Waits for the stream. */
+ * iteration, gradient pass included, of every (part, level, kind) in its faster
+ * form.  VD_ESTATE if a handle has no constraints.  Waits for the stream. */
 int vd_batch_tune(vd_batch* b, int32_t iters, int32_t* tile_out, double* us_out);
 
 /* Mean duration (us) and count of the finest level's launches per kernel

@@ -1023,10 +1023,13 @@ class Solver final : public ISolver {
   const vd_lattice_desc& desc() const { return desc_; }
   int level_nodes(int l) const { return lv_[l].N; }
   int level_tile(int l) const { return lv_[l].tile; }
-  // Tiles of level l where a batch may run its solves as one launch, else 0.
-  // (A batch launches all its lattices with one tile kind: none of the large.)
-  int level_loop_tiles(int l) const {
-    return lv_[l].large < 0 && !(desc_.flags & VD_FLAG_ITERATIVE) ? lv_[l].ntiles : 0;
+  // Whether a batch may run the solves of level l as one launch.  (It launches
+  // all its lattices with one tile kind: none of the large.)
+  bool level_loop(int l) const {
+    return lv_[l].large < 0 && !(desc_.flags & VD_FLAG_ITERATIVE);
+  }
+  int level_tiles(int l, int kind) const {
+    return tile_blocks(kind, lv_[l].nx, lv_[l].ny, lv_[l].nz);
   }
   void force_tile(int l, int kind) {
     if (lv_[l].tile == kind) return;
@@ -1739,7 +1742,7 @@ class IBatch {
  public:
   virtual ~IBatch() {}
   // Queue one frame of every lattice on `s` (graph replay or eager).
-  virtual bool one_launch() const = 0;  // some level's solves are one launch each
+  virtual bool one_launch() = 0;  // some level's solves are one launch each
   virtual int launch(const vd_solve_opts* o, hipStream_t s) = 0;
   // Final energies (4 per lattice) after the frame finished.
   virtual int energies(double* e) = 0;
@@ -1768,15 +1771,14 @@ class Batch final : public IBatch {
     graph_ = (h_[0]->desc().flags & VD_FLAG_GRAPH) != 0;
     prof_ = !graph_ && (h_[0]->desc().flags & VD_FLAG_PROFILE) != 0;
     // one lattice with a set M and the launches are those with masks
-    bool masked = false;
-    for (const auto* h : h_) masked |= (h->desc().flags & VD_FLAG_ACTIVE_SET) != 0;
-    for (int k = 0; k < kTileKinds; ++k) VD_TRY(cg_loop_capacity<T>(k, masked, &loop_cap_[k]));
-    // one tile kind per level: that of the largest lattice
+    for (const auto* h : h_) masked_ |= (h->desc().flags & VD_FLAG_ACTIVE_SET) != 0;
+    for (int k = 0; k < kTileKinds; ++k) VD_TRY(cg_loop_capacity<T>(k, masked_, &loop_cap_[k]));
+    // one tile kind per level: that of the largest lattice if it was chosen
     for (int l = 0; l < L_; ++l) {
       int big = 0;
       for (int b = 1; b < n_; ++b)
         if (h_[b]->level_nodes(l) > h_[big]->level_nodes(l)) big = b;
-      const int kind = h_[big]->level_tile(l);
+      const int kind = h_[big]->desc().tile[l] > 0 ? h_[big]->level_tile(l) : default_kind(l);
       for (int b = 0; b < n_; ++b) h_[b]->force_tile(l, kind);
     }
     tables_.resize(L_);
@@ -1788,9 +1790,10 @@ class Batch final : public IBatch {
     return VD_OK;
   }
 
-  bool one_launch() const override {
+  bool one_launch() override {
+    if (stale()) set_loops();
     for (int l = 0; l < L_; ++l)
-      if (loops(l)) return true;
+      if (loops_[l]) return true;
     return false;
   }
 
@@ -1799,9 +1802,7 @@ class Batch final : public IBatch {
     for (auto* h : h_)
       if (!h->has_constraints()) return VD_ESTATE;
     const int reset = (o && o->reset_to_rest) ? 1 : 0;
-    bool stale = false;
-    for (int b = 0; b < n_; ++b) stale |= (gens_[b] != h_[b]->generation());
-    if (stale) {
+    if (stale()) {
       VD_CHECK(build_tables());
       for (auto& g : exec_)
         if (g) {
@@ -1848,48 +1849,109 @@ class Batch final : public IBatch {
     LevelView<T> first{};
   };
 
-  // Whether the position solves of level l run as one launch.
-  bool loops(int l) const {
-    const int cap = loop_cap_[h_[0]->level_tile(l)];
-    for (const auto* h : h_) {
-      const int tiles = h->level_loop_tiles(l);
-      if (tiles == 0 || tiles > cap) return false;
-    }
-    return true;
+  // Whether a handle was reallocated or re-tiled since the tables were built.
+  bool stale() const {
+    for (int b = 0; b < n_; ++b)
+      if (gens_[b] != h_[b]->generation()) return true;
+    return false;
   }
 
-  // The lattices in launch order.  A lattice of a one-launch solve waits until
-  // all its tiles are resident, and tiles become resident in launch order:
-  // groups that fill the GPU (first fit, largest first) leave the fewest
-  // compute units waiting for an earlier lattice to end.
-  std::vector<int> launch_order() const {
-    std::vector<int> by_size(n_);
-    for (int b = 0; b < n_; ++b) by_size[b] = b;
-    const int F = L_ - 1;
-    if (!loops(F)) return by_size;
-    auto tiles = [&](int b) { return h_[b]->level_view(F).ntiles; };
+  // A lattice of a one-launch solve waits until all its tiles are resident, and
+  // tiles become resident in launch order: groups that fill the GPU (first fit,
+  // largest first) leave the fewest compute units waiting for an earlier
+  // lattice to end.  The groups of level l with tile kind `kind`; none where a
+  // lattice does not fit or wants one launch per iteration.
+  std::vector<std::vector<int>> groups_of(int l, int kind) const {
+    std::vector<int> tiles(n_), by_size(n_);
+    for (int b = 0; b < n_; ++b) {
+      by_size[b] = b;
+      tiles[b] = h_[b]->level_tiles(l, kind);
+      if (!h_[b]->level_loop(l) || tiles[b] > loop_cap_[kind]) return {};
+    }
     std::stable_sort(by_size.begin(), by_size.end(),
-                     [&](int a, int b) { return tiles(a) > tiles(b); });
+                     [&](int a, int b) { return tiles[a] > tiles[b]; });
     std::vector<std::vector<int>> groups;
     std::vector<int> left;
     for (const int b : by_size) {
       size_t g = 0;
-      while (g < groups.size() && left[g] < tiles(b)) ++g;
+      while (g < groups.size() && left[g] < tiles[b]) ++g;
       if (g == groups.size()) {
         groups.emplace_back();
-        left.push_back(loop_cap_[h_[0]->level_tile(F)]);
+        left.push_back(loop_cap_[kind]);
       }
       groups[g].push_back(b);
-      left[g] -= tiles(b);
+      left[g] -= tiles[b];
     }
+    return groups;
+  }
+
+  // Nodes of level l, or with a tile kind the places of its tiles.
+  int64_t nodes_of(int l, int kind = -1) const {
+    int64_t n = 0;
+    for (const auto* h : h_)
+      n += kind < 0 ? h->level_nodes(l)
+                    : (kind == 2 ? 1024 : 512) * (int64_t)h->level_tiles(l, kind);
+    return n;
+  }
+  double loop_us(int l, int kind, int rounds) const {
+    return batch_loop_us(kind, rounds, nodes_of(l), sizeof(T) == 8, masked_);
+  }
+  double iter_us(int l) const {
+    return batch_iter_us(nodes_of(l), nodes_of(l, 1), sizeof(T) == 8, masked_);
+  }
+
+  // Whether the position solves of each level run as one launch: where all
+  // lattices are resident together, or where the rounds that the GPU is filled
+  // cost less than streaming every lattice in each iteration, by the tuner's
+  // timings of the tile or else as expected.
+  void set_loops() {
+    loops_.assign(L_, 0);
+    for (int l = 0; l < L_; ++l) {
+      const int kind = h_[0]->level_tile(l), rounds = (int)groups_of(l, kind).size();
+      if (rounds == 0) continue;
+      loops_[l] = tuned_[l].kind == kind ? tuned_[l].loop
+                                         : rounds == 1 || loop_us(l, kind, rounds) < iter_us(l);
+    }
+  }
+
+  // The tile of level l unless the largest lattice's was chosen: the kind with
+  // the fastest one-launch solves, or, where a launch per iteration is expected
+  // to be faster, 8x8x8 (32x8x4 where it pads little: 12 lattices of 64^3 4.3
+  // against 5.3 ms, of 48^3, a third more nodes, 1.31 against 1.23 for 8).
+  int default_kind(int l) const {
+    int best = -1;
+    double best_us = 0.0;
+    for (const int k : {7, 6, 5, 4, 3}) {
+      const int rounds = (int)groups_of(l, k).size();
+      if (rounds == 0) continue;
+      const double us = loop_us(l, k, rounds);
+      if (best < 0 || us < best_us) {
+        best = k;
+        best_us = us;
+      }
+      if (rounds == 1) return best;
+    }
+    if (best >= 0 && best_us < iter_us(l)) return best;
+    return sizeof(T) == 4 && !masked_ && 20 * nodes_of(l, 2) <= 23 * nodes_of(l) ? 2 : 1;
+  }
+
+  // The lattices in launch order.
+  std::vector<int> launch_order() const {
     std::vector<int> order;
-    for (const auto& g : groups) order.insert(order.end(), g.begin(), g.end());
+    const int F = L_ - 1;
+    if (loops_[F]) {
+      for (const auto& g : groups_of(F, h_[0]->level_tile(F)))
+        order.insert(order.end(), g.begin(), g.end());
+    } else {
+      for (int b = 0; b < n_; ++b) order.push_back(b);
+    }
     return order;
   }
 
   // Device tables of the lattices' level views and the first workgroup of
   // each lattice for every workgroup kind (rebuilt when a handle reallocates).
   int build_tables() {
+    set_loops();
     const std::vector<int> order = launch_order();
     for (int l = 0; l < L_; ++l) {
       std::vector<LevelView<T>> views(n_);
@@ -1930,10 +1992,10 @@ class Batch final : public IBatch {
 
   int profile(double* us, int* n) override { return timer_.collect(us, n); }
 
-  // Per level, every tile kind for all lattices of this part, timed over one
-  // batched position step (the gradient pass and `iters` CG iterations) from
-  // the lattices' current state; the fastest kind is kept and the lattices'
-  // displacements are restored.  The fastest of three timings after a
+  // Per level, every tile kind for all lattices of this part, in both forms of
+  // the solve, timed over one batched position step (the gradient pass and
+  // `iters` CG iterations) from the lattices' current state; the fastest kind
+  // and form are kept and the lattices' displacements are restored.  The fastest of three timings after a
   // warm-up counts, as in the single-lattice tuner.
   int tune(int iters, hipStream_t s, int* tile_out, double* us_out) override {
     if (iters < 1) return VD_EINVAL;
@@ -1961,8 +2023,19 @@ class Batch final : public IBatch {
       };
       double best = 1e300;
       int best_kind = h_[0]->level_tile(l);
-      for (int kind = 0; kind < kTileKinds && rc == VD_OK; ++kind) {
+      bool best_loop = false;
+      int timed = -1;  // the kind that us_out was last written for
+      for (int t = 0; t < 2 * kTileKinds && rc == VD_OK; ++t) {
+        const int kind = t / 2;
+        const bool loop = (t & 1) != 0;
+        // (not a form expected to take half as long again as the other)
+        const int rounds = (int)groups_of(l, kind).size();
+        const double as_loop = rounds > 1 ? loop_us(l, kind, rounds) : 0.0;
+        if (loop ? rounds == 0 || as_loop > 1.5 * iter_us(l)
+                 : rounds > 0 && iter_us(l) > 1.5 * as_loop) continue;
         for (auto* h : h_) h->force_tile(l, kind);
+        tuned_[l].kind = kind;
+        tuned_[l].loop = loop;
         rc = build_tables();
         float best_ms = 1e30f;
         for (int rep = 0; rep < 4 && rc == VD_OK; ++rep) {
@@ -1978,13 +2051,20 @@ class Batch final : public IBatch {
           if (rep > 0) best_ms = std::min(best_ms, ms);
         }
         const double us = 1000.0 * best_ms / iters;
-        if (us_out) us_out[VD_TILE_KINDS * l + kind] = us;
+        if (us_out) {
+          double& out = us_out[VD_TILE_KINDS * l + kind];
+          out = timed == kind ? std::min(out, us) : us;
+        }
+        timed = kind;
         if (us < best) {
           best = us;
           best_kind = kind;
+          best_loop = loop;
         }
       }
       for (auto* h : h_) h->force_tile(l, best_kind);
+      tuned_[l].kind = best_kind;
+      tuned_[l].loop = best_loop;
       if (tile_out) tile_out[l] = best_kind + 1;
       if (rc == VD_OK) rc = restore();
       if (rc == VD_OK) rc = hipStreamSynchronize(s) == hipSuccess ? VD_OK : VD_EHIP;
@@ -2002,14 +2082,11 @@ class Batch final : public IBatch {
     return rc;
   }
 
-  // The CG solve of level l: one launch where every lattice allows it (25
-  // float32 lattices of 33 .. 64 nodes per axis: 154 us per iteration of the
-  // finest level against 165 with one launch per iteration, which streams
-  // every row and vector again; fewer or smaller lattices gain more).  A
-  // lattice that is launched behind others waits for one of their solves, so
-  // the limit of that wait grows with the iterations (50 us each).
+  // The CG solve of level l, as one launch or one per iteration.  A lattice
+  // that is launched behind others waits for one of their solves, so the limit
+  // of that wait grows with the iterations (50 us each).
   int solve(int l, int pcg, bool on, hipStream_t s) {
-    if (pcg > 0 && loops(l))
+    if (pcg > 0 && loops_[l])
       return timer_.timed(on, VD_PROF_CG_LOOP, s, [&] {
         return launch_cg_loop<T>(pcg, D(l, kTiles), s, nullptr, kAssembleTicks + 5000 * std::min(pcg, 10000));
       });
@@ -2062,7 +2139,13 @@ class Batch final : public IBatch {
   bool graph_ = false;
   hipGraphExec_t exec_[2] = {nullptr, nullptr};
   bool prof_ = false;
+  bool masked_ = false;            // some lattice has an optimised set
   int loop_cap_[kTileKinds] = {};  // most tiles of a lattice's one-launch CG solve
+  std::vector<char> loops_;        // per level: its CG solves are one launch
+  struct Tuned {
+    int kind = -1;
+    bool loop = false;
+  } tuned_[VD_MAX_LEVELS];         // the tuner's choice per level
   EventTimer timer_;
   std::vector<Tables> tables_;
   std::vector<long> gens_;

@@ -167,6 +167,30 @@ int large_loop_tile(int nx, int ny, int nz, bool masked) {
     if (tile_blocks(k, nx, ny, nz) <= kGangMaxTiles) return k;
   return -1;
 }
+
+// Costs by which a batch chooses its tiles and the form of its solves.  One
+// launch over solves holds whole compute units: an iteration takes `rounds`
+// times that of a full GPU, a quarter of which goes by how full the tiles and
+// the rounds are.  A launch per iteration streams every node's vectors (and
+// some of its tiles' empty places), in float32 more slowly once they exceed the
+// last-level cache.  Fitted to batches of 2 .. 100 lattices of 8^3 .. 64^3
+// nodes (ms of 2 x 15 iterations, one launch against one per iteration: 12 x
+// 64^3 3.34 and 4.32, 16 x 48^3 2.12 and 2.52, 100 x 16^3 0.52 and 0.80, but 16
+// x 33^3 1.41 and 1.12, 64 x 33^3 5.29 and 4.71 and, with the optimised set, 8
+// x 48^3 0.94 and 0.72: lattices that leave much of their tiles, or of the GPU
+// beside them, empty).
+double batch_loop_us(int kind, int rounds, int64_t nodes, bool f64, bool masked) {
+  const int size = kind == 0 || kind == 7 ? 0 : kind == 1 || kind == 6 ? 1 : kind == 2 ? 3 : 2;
+  static const double us[2][2][4] = {{{5.8, 7.0, 9.2, 12.5}, {5.1, 6.0, 7.4, 9.2}},
+                                     {{7.2, 11.4, 15.6, 20.0}, {6.2, 9.3, 11.8, 15.5}}};
+  const double places = (double)rounds * kGangMaxTiles * (size == 0 ? 256 : size == 1 ? 512 : 1024);
+  return rounds * us[f64][masked][size] * (0.75 + 0.25 * (double)nodes / places);
+}
+double batch_iter_us(int64_t nodes, int64_t places, bool f64, bool masked) {
+  const double k = 1e-3 * (0.75 * (double)nodes + 0.25 * (double)places);
+  if (masked) return 10.0 + k / (f64 ? 32.0 : 50.0);
+  return f64 ? 8.0 + k / 13.0 : 8.0 + k / 27.0 + std::max(0.0, 1e-3 * (double)nodes - 1200.0) / 35.0;
+}
 int node_blocks(int N) { return blocks_for(N); }
 int energy_blocks(int rblocks, int N) { return rblocks + blocks_for(N); }
 

@@ -223,6 +223,11 @@ enum StencilMode { kModeRhs = 1, kModeApply = 2, kModeGrad = 3 };
 int tile_blocks(int kind, int nx, int ny, int nz);
 int default_tile(int nx, int ny, int nz, bool f64, bool masked, bool iterative);
 int large_loop_tile(int nx, int ny, int nz, bool masked);
+// Expected us of a CG iteration over a batch's `nodes`: of one launch over the
+// solves of `rounds` groups of lattices that fill the GPU in turn, and of a
+// launch per iteration (`places`: nodes of the 8x8x8 tiles).
+double batch_loop_us(int kind, int rounds, int64_t nodes, bool f64, bool masked);
+double batch_iter_us(int64_t nodes, int64_t places, bool f64, bool masked);
 int node_blocks(int N);
 int energy_blocks(int rblocks, int N);
 

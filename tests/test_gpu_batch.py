@@ -180,3 +180,28 @@ def test_batch_of_lattices_with_and_without_the_optimised_set(precision, tile):
         rep = ref.solve_frame(reset=True, report=True)
         np.testing.assert_array_equal(e, rep["energy"])
         np.testing.assert_array_equal(lat.get_state64()[0], ref.get_state64()[0])
+
+
+@pytest.mark.parametrize("tile", [0, 6])
+@pytest.mark.parametrize("sizes,one_launch", [
+    ([64, 48, 47, 63], True),   # three rounds that fill the GPU
+    ([33] * 24, False),         # eight rounds, more than half of the tiles empty
+    ([16] * 5, True)])          # all resident together
+def test_form_of_batched_solves(sizes, one_launch, tile):
+    """Batched solves run as one launch where all lattices are resident together
+    or the rounds that the GPU is filled cost less than a launch per iteration,
+    with the bits of single solves launched per iteration."""
+    from paper_1603_08161_amd import Batch
+    scenes = [make_batch_lattice(800 + k, n, 1500, 20, num_levels=1, gn=2, pcg=6)
+              for k, n in enumerate(sizes)]
+    lats = [make_lattice(s, tiles=(tile,), profile=True) for s in scenes]
+    batch = Batch(lats)
+    E = batch.solve(reset=True, energies=True)
+    prof = batch.profile()
+    assert ("cg_loop" in prof, "cg_a" in prof) == (one_launch, not one_launch)
+    for s, lat, e in zip(scenes, lats, E):
+        ref = make_lattice(s, tiles=(tile,), iterative=True)
+        rep = ref.solve_frame(reset=True, report=True)
+        np.testing.assert_allclose(e, rep["energy"], rtol=0 if tile else 1e-6)
+        dx = np.abs(lat.get_state()[0] - ref.get_state()[0]).max() / s.spec.spacing
+        assert dx <= (0 if tile else 1e-5)
