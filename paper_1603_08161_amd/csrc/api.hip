@@ -1152,7 +1152,7 @@ class Solver final : public ISolver {
   }
 
   int abandon_loops(int on) override {
-    loop_ticks_ = on > 1 ? -on : on ? -1 : kAssembleTicks;
+    loop_ticks_ = on > 1 ? -on : on ? -1 : 0;
     ++alloc_gen_;  // captured schedules hold the old limit
     return VD_OK;
   }
@@ -1191,7 +1191,8 @@ class Solver final : public ISolver {
           VD_TRY(hipEventRecord(e0, stream_));
           VD_TRY(launch_stencil<T>(kModeRhs, tiles_of(V), nullptr, nullptr, stream_));
           if (cg_loop(v)) {
-            VD_TRY(launch_cg_loop<T>(iters, loop_tiles_of(V), stream_));
+            VD_TRY(launch_cg_loop<T>(iters, loop_tiles_of(V), stream_, nullptr,
+                                     assemble_ticks(iters)));
           } else {
             for (int m = 0; m < iters; ++m) VD_TRY(launch_cg<T>(m, tiles_of(V), stream_));
             if (iters > 0) VD_TRY(launch_cg_final<T>(iters - 1, nodes_of(V), stream_));
@@ -1265,8 +1266,9 @@ class Solver final : public ISolver {
             if (n_stamped_ < kMaxStamped - 1) ++n_stamped_;
             stamped_launches_ = pcg - 1;
           }
-          VD_CHECK(timed(on, VD_PROF_CG_LOOP, s,
-                         [&] { return launch_cg_loop<T>(pcg, loop_tiles_of(V), s, stamp, loop_ticks(v, pcg)); }));
+          VD_CHECK(timed(on, VD_PROF_CG_LOOP, s, [&] {
+            return launch_cg_loop<T>(pcg, loop_tiles_of(V), s, stamp, loop_ticks(pcg));
+          }));
         } else if (graph_prof && l == L_ - 1 && pcg > 1) {
           // captured frame: the device clock at the start of CG iteration 1
           // and of the final step (first workgroup of each), written on
@@ -1306,13 +1308,8 @@ class Solver final : public ISolver {
            tile_blocks(kind, v.nx, v.ny, v.nz) <= loop_cap_[kind];
   }
 
-  // How long a solve waits for its tiles: longer than a solve of the same size
-  // that another stream may run before it (large tiles: 50 us an iteration; two
-  // 96^3 frames on two streams 26.2 ms with the short wait, 15.2 with this one).
-  int loop_ticks(const LevelData<T>& v, int pcg) const {
-    if (loop_ticks_ < 0 || v.large < 0) return loop_ticks_;
-    return loop_ticks_ + 5000 * std::min(pcg, 10000);
-  }
+  // How long a solve waits for its tiles (negative: test settings).
+  int loop_ticks(int pcg) const { return loop_ticks_ < 0 ? loop_ticks_ : assemble_ticks(pcg); }
 
   template <typename F>
   int timed(bool on, int kind, hipStream_t s, F&& launch, int count = 1) {
@@ -1417,7 +1414,7 @@ class Solver final : public ISolver {
     auto g = [&](const Dispatch<T>& D) { return guarded(D, stop); };
     VD_TRY(launch_stencil<T>(kModeRhs, g(tiles_of(V)), nullptr, nullptr, s));
     if (cg_loop(finest()) && pcg > 0) {
-      VD_TRY(launch_cg_loop<T>(pcg, g(loop_tiles_of(V)), s, nullptr, loop_ticks(finest(), pcg)));
+      VD_TRY(launch_cg_loop<T>(pcg, g(loop_tiles_of(V)), s, nullptr, loop_ticks(pcg)));
     } else {
       for (int m = 0; m < pcg; ++m) VD_TRY(launch_cg<T>(m, g(tiles_of(V)), s));
       if (pcg > 0) VD_TRY(launch_cg_final<T>(pcg - 1, g(nodes_of(V)), s));
@@ -1682,7 +1679,7 @@ class Solver final : public ISolver {
   bool have_constraints_ = false;
   bool energy_fresh_ = false;
   EventTimer timer_;  // timing of the last profiled frame
-  int loop_ticks_ = kAssembleTicks;
+  int loop_ticks_ = 0;  // negative: test settings of vd_debug_abandon_loops
   int loop_cap_[kLoopKinds] = {};  // most tiles of a one-launch CG solve, by tile kind
   // test scratch
   float* dbg_f_ = nullptr;
@@ -2082,13 +2079,11 @@ class Batch final : public IBatch {
     return rc;
   }
 
-  // The CG solve of level l, as one launch or one per iteration.  A lattice
-  // that is launched behind others waits for one of their solves, so the limit
-  // of that wait grows with the iterations (50 us each).
+  // The CG solve of level l, as one launch or one per iteration.
   int solve(int l, int pcg, bool on, hipStream_t s) {
     if (pcg > 0 && loops_[l])
       return timer_.timed(on, VD_PROF_CG_LOOP, s, [&] {
-        return launch_cg_loop<T>(pcg, D(l, kTiles), s, nullptr, kAssembleTicks + 5000 * std::min(pcg, 10000));
+        return launch_cg_loop<T>(pcg, D(l, kTiles), s, nullptr, assemble_ticks(pcg));
       });
     for (int m = 0; m < pcg; ++m)
       VD_CHECK(timer_.timed(on, VD_PROF_CG_A, s,

@@ -263,10 +263,20 @@ hipError_t launch_cg_final(int last, const Dispatch<T>& D, hipStream_t s,
 // ticks: how long a workgroup waits for the others before the solve is
 // abandoned to the ticket path (100 MHz clock; for tests -1: at once, -1 - t:
 // besides, the workgroups of odd tiles start late, after t tickets are done).
-constexpr int kAssembleTicks = 30000;
 template <typename T>
 hipError_t launch_cg_loop(int iters, const Dispatch<T>& D, hipStream_t s,
-                          unsigned long long* stamp = nullptr, int ticks = kAssembleTicks);
+                          unsigned long long* stamp, int ticks);
+
+// That wait: 0.3 ms and 50 us per iteration, more than a solve with as many
+// iterations takes on any tiles (35 us an iteration at 96^3), as the tiles may
+// have to wait for one on another stream or, in a batch, of a lattice before
+// them.  An abandoned solve costs more than the wait: two 96^3 frames of 4 x 20
+// iterations on two streams take 10.4 ms with 0.3 ms alone and 4.8 with this, a
+// 64^3 frame beside 1 GB copies 3.9 and 2.2, beside a kernel that holds one
+// compute unit for milliseconds 4.8 and 2.3 (float64 5.6 and 3.2).
+inline int assemble_ticks(int iters) {
+  return 30000 + 5000 * (iters < 10000 ? iters : 10000);
+}
 
 // Tiles of a kind (< kLoopKinds) that fit on the GPU together in launch_cg_loop
 // (0: it has no instance).

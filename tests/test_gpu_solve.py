@@ -508,11 +508,11 @@ def test_solves_on_two_streams_equal_solves_alone(sizes, graph):
 
 
 def test_solves_beside_foreign_kernels_equal_solves_alone():
-    """A kernel of another stream holds a compute unit for 0.2 to 5 ms, so that
-    the last workgroup of a solve on all of them (256 tiles, 100 iterations)
-    starts while the others are at work on the abandoned solve."""
+    """A kernel of another stream holds a compute unit for 1.5 to 3.5 ms, so that
+    the last workgroup of a solve on all of them (256 tiles, 30 iterations, which
+    is abandoned after 1.8 ms) starts while the others are at work on it."""
     import torch
-    scene = make_tiny(seed=31, dims=(64, 64, 64), num_levels=1, gn=1, pcg=100, n_dense=4000,
+    scene = make_tiny(seed=31, dims=(64, 64, 64), num_levels=1, gn=1, pcg=30, n_dense=4000,
                       n_sparse=20, spacing=0.5)
     lat = make_lattice(scene, tiles=(5,))
     lat.solve_frame(reset=True)
@@ -526,10 +526,31 @@ def test_solves_beside_foreign_kernels_equal_solves_alone():
         b.record()
     side.synchronize()
     per_ms = 1_000_000 / a.elapsed_time(b)
-    for ms in np.linspace(0.2, 5.0, 25):
+    for ms in np.linspace(1.5, 3.5, 41):
         with torch.cuda.stream(side):
             torch.cuda._sleep(int(ms * per_ms))
         rep = lat.solve_frame(reset=True, report=True)
         torch.cuda.synchronize()
         assert not rep["bits"] & 16
+        np.testing.assert_array_equal(lat.get_state64()[0], ref)
+
+
+def test_solves_of_many_iterations_on_two_streams_equal_launches_per_iteration():
+    """Solves of 64^3 that take longer than a millisecond each, on two streams and
+    in both precisions: the bits of one launch per iteration."""
+    import torch
+    lats, refs = [], []
+    for k, precision in enumerate(("fp32", "fp64", "fp32")):
+        scene = make_tiny(seed=40 + k, dims=(64, 63, 64), num_levels=1, gn=2, pcg=120,
+                          n_dense=4000, n_sparse=20, spacing=0.5)
+        ref = make_lattice(scene, precision=precision, tiles=(6,), iterative=True)
+        ref.solve_frame(reset=True)
+        refs.append(ref.get_state64()[0])
+        lats.append(make_lattice(scene, precision=precision, tiles=(6,),
+                                 stream=torch.cuda.Stream().cuda_stream))
+    torch.cuda.synchronize()
+    for lat in lats * 3:
+        lat.solve_frame(reset=True)
+    torch.cuda.synchronize()
+    for lat, ref in zip(lats, refs):
         np.testing.assert_array_equal(lat.get_state64()[0], ref)
