@@ -79,10 +79,10 @@ __global__ __launch_bounds__(kThreads) void k_scan_sums(int* sums, int nb) {
   }
 }
 
-// out = exclusive prefix sum of in, given the scanned block sums.
-__global__ __launch_bounds__(kThreads) void k_scan_apply(const int* __restrict__ in, int64_t n,
-                                                         const int* __restrict__ sums,
-                                                         int* __restrict__ out) {
+// out = exclusive prefix sum of in, given the scanned block sums.  out may be
+// in: a thread reads its elements before it writes them.
+__global__ __launch_bounds__(kThreads) void k_scan_apply(const int* in, int64_t n,
+                                                         const int* __restrict__ sums, int* out) {
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kPerThread;
   int v[kPerThread], s = 0;
 #pragma unroll

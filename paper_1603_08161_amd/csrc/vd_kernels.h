@@ -369,6 +369,7 @@ hipError_t sort_levels(const SortLevels& S, hipStream_t s);
 hipError_t sort_pairs(void* temp, size_t bytes, const unsigned* kin, unsigned* kout,
                       const int* vin, int* vout, int n, int end_bit, hipStream_t s);
 size_t scan_temp_bytes(int n);
+// (out may be in)
 hipError_t exclusive_scan(void* temp, size_t bytes, const int* in, int* out, int n,
                           hipStream_t s);
 

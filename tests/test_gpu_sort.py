@@ -59,3 +59,17 @@ def test_exclusive_scan(n):
     out = exclusive_scan(x)
     ref = np.concatenate([[0], np.cumsum(x, dtype=np.int64)[:-1]]).astype(np.int32)
     np.testing.assert_array_equal(out, ref)
+
+
+@pytest.mark.parametrize("n", [1, 1024, 1025, 262144, 1024 * 1024 + 3])
+def test_exclusive_scan_in_place(n):
+    """The constraint build scans its counts where they are."""
+    import ctypes as C
+    import torch
+    from paper_1603_08161_amd import _lib as L
+    x = np.random.default_rng(n).integers(0, 6, size=n).astype(np.int32)
+    t = torch.from_numpy(x.copy()).cuda()
+    p = C.c_void_p(t.data_ptr())
+    assert L._lib.vd_debug_exclusive_scan(p, p, n, L.VD_MEM_DEVICE, None) == 0
+    ref = np.concatenate([[0], np.cumsum(x, dtype=np.int64)[:-1]]).astype(np.int32)
+    np.testing.assert_array_equal(t.cpu().numpy(), ref)
