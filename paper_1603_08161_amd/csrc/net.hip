@@ -1190,8 +1190,8 @@ class Net {
   }
 
   // The staged block of k_wgrad: the most 32-voxel steps (at most 16) whose
-  // dY and input lines a workgroup loads at once and two workgroups hold in a
-  // compute unit's LDS.  Returns the LDS bytes, 0 where not even one step
+  // dY and input lines a workgroup loads at once, 64 KB, so that two workgroups
+  // fit a compute unit's LDS.  Returns the LDS bytes, 0 where not even one step
   // fits (rows of some 600 voxels) and k_wgrad_gather runs instead.
   static size_t wgrad_block(const ConvArgs& A, int co, WgradArgs* G) {
     const int S = A.stride, W = S * (A.ow - 1) + 3;
@@ -1201,7 +1201,7 @@ class Net {
       const int64_t planes = (rows + A.oh - 2) / A.oh + 1;
       const int64_t lines = S * (rows - 1) + (3 - S) * (planes - 1) + 3;
       const int64_t groups = 32 * ks * co * 2 + lines * W * 2;
-      if (groups > kWgLoads * kWgThreads || groups * 16 > 80 * 1024) continue;
+      if (groups > kWgLoads * kWgThreads) continue;
       G->ksteps = ks;
       G->lines = (int)lines;
       return (size_t)groups * 16;
