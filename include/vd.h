@@ -87,12 +87,16 @@ extern "C" {
                                   it are initialised by extrapolating the
                                   field (Sec. 8; see vd_get_active) */
 #define VD_FLAG_ITERATIVE 32u /* one launch per CG iteration on every level.
-                                 By default a level of at most 256 tiles runs
-                                 each CG solve as one launch whose workgroups
-                                 stay resident and exchange halos (the
-                                 iterates are the same).  If concurrent work
-                                 keeps them from becoming resident together,
-                                 those that are finish the solve from a ticket
+                                 By default a level that at most 256 tiles
+                                 cover (up to 64^3 nodes, in float32 96^3; in
+                                 a batch also by cost, see vd_batch_create)
+                                 runs each CG solve as one launch whose
+                                 workgroups stay resident and exchange halos
+                                 (the iterates are the same).  If concurrent
+                                 work keeps them from becoming resident
+                                 together within 0.3 ms and 50 us per
+                                 iteration, those that are and those that
+                                 start later finish the solve from a ticket
                                  counter, slower and with the same results;
                                  VD_REPORT_BARRIER_TIMEOUT reports a wait that
                                  gave up nevertheless */
@@ -104,7 +108,7 @@ extern "C" {
 #define VD_PROF_ROTATION 3  /* rotation fits */
 #define VD_PROF_ENERGY 4    /* energy evaluation */
 #define VD_PROF_TRANSFER 5  /* injection / prolongation */
-#define VD_PROF_CG_LOOP 6   /* a whole CG solve in one persistent launch */
+#define VD_PROF_CG_LOOP 6   /* a whole CG solve in one launch */
 #define VD_PROF_KINDS 8
 
 /* ---- report bits -------------------------------------------------------- */
@@ -260,12 +264,14 @@ int vd_solve_frame(vd_lattice* l, const vd_solve_opts* opts, vd_solve_report* re
 /* Batched solve of several independent lattices (same number of levels,
  * schedule, stream and VD_FLAG_GRAPH setting; any sizes and either
  * precision).  Every step of the frame schedule is one launch covering the
- * workgroups of all lattices of one precision, with per-lattice reductions;
- * the float64 lattices, if any, form a second part that runs on a
- * library-owned stream forked from the lattices' stream and joined back into
- * it, so both parts overlap on the GPU, unless both have levels whose CG
- * solves are one launch (those hold whole compute units until their lattice
- * is done; the parts then run one after the other).  The batch does not own
+ * workgroups of all lattices of one precision, with per-lattice reductions; the
+ * CG solves of a level are one launch where the lattices are resident together
+ * or fill the GPU well in turn, else one launch per iteration; the float64
+ * lattices, if any, form a second part that runs on a library-owned stream
+ * forked from the lattices' stream and joined back into it, so both parts
+ * overlap on the GPU, or one after the other where one-launch solves of both
+ * (which hold whole compute units until their lattice is done) do not fit
+ * beside each other.  The batch does not own
  * the handles: they must outlive it.  Creating it sets every handle's stencil
  * tile, per level, to the tile of the largest lattice of its part at that
  * level if that was chosen (vd_lattice_desc.tile, vd_tune, another batch), else

@@ -864,8 +864,9 @@ __global__ __launch_bounds__(TL::NT) void k_cg(Dispatch<T> D, int m, unsigned lo
 // ---------------------------------------------------------------------------
 //
 // One workgroup per tile for all iterations.  A workgroup keeps r, D^-1, d and
-// A p of its own nodes, r and D^-1 of its halo nodes and (as far as one round
-// of items covers them) the rows of its data nodes in registers and p in LDS,
+// A p of its own nodes, r and D^-1 of its halo nodes and (as far as registers
+// last, up to two rounds of items) the rows of its data nodes in registers and
+// p in LDS,
 // and applies the scalar updates to its halo itself, so per iteration it
 // exchanges only A p of the tile's surface nodes and the four block partials.
 // The per-iteration launches stream every vector instead (36 MB at 64^3).
@@ -906,8 +907,10 @@ __global__ __launch_bounds__(TL::NT) void k_cg(Dispatch<T> D, int m, unsigned lo
 // round, 2.6 us each) are half of an iteration's 35 us, and the rows of all
 // but the 16x16x8 tile are read again in every iteration.  A p packed by tile
 // face instead of in node order took 5 % longer (more index arithmetic in the
-// exchange), tiles dealt to the dies in turn 3 to 10 % longer.  The arithmetic and the
-// order of every sum are those of k_cg, so the results are the same bits.
+// exchange), tiles dealt to the dies in turn 3 to 10 % longer.  The arithmetic
+// is that of k_cg, and with the same tile kind so is the order of every sum:
+// the results are the same bits.  (The large tiles have no k_cg form; they add
+// the same terms up in another order.)
 
 constexpr unsigned kSpinLimit = 1u << 18;         // polls before a wait gives up
 

@@ -192,7 +192,7 @@ struct BuildLevels {
 // Rows, cell cache and node blocks of all levels from the staged constraints.
 // With `structure` false only the values are recomputed: the rows' cells, the
 // sort by cell and the cell segments are those of the previous build.  temp:
-// scan_temp_bytes(build_scan_size(...)) bytes.
+// scan_temp_bytes of the row or node blocks of the largest level, if more.
 template <typename T>
 hipError_t launch_build(const RawConstraints& c, const BuildLevels<T>& B, const SortLevels& S,
                         const double* origin, double w_dense, double w_sparse, bool structure,
@@ -258,8 +258,8 @@ hipError_t launch_cg_final(int last, const Dispatch<T>& D, hipStream_t s,
 // cg_loop_capacity tiles).  Follows a gradient pass, which resets its
 // exchange slots.  Same bits as launch_cg + launch_cg_final where loop_tile is
 // the level's tile kind; the larger tiles add the same terms up in another
-// order.  stamp (may be
-// NULL): the device clock at the start of iteration 1 and of the last step.
+// order.  stamp (may be NULL): the device clock at the start of iteration 1 and
+// of the last step.
 // ticks: how long a workgroup waits for the others before the solve is
 // abandoned to the ticket path (100 MHz clock; for tests -1: at once, -1 - t:
 // besides, the workgroups of odd tiles start late, after t tickets are done).

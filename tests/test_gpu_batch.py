@@ -205,3 +205,26 @@ def test_form_of_batched_solves(sizes, one_launch, tile):
         np.testing.assert_allclose(e, rep["energy"], rtol=0 if tile else 1e-6)
         dx = np.abs(lat.get_state()[0] - ref.get_state()[0]).max() / s.spec.spacing
         assert dx <= (0 if tile else 1e-5)
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("n32,n64,tile", [(24, 24, 6), (40, 24, 5), (64, 32, 6), (48, 64, 6)])
+def test_parts_of_one_launch_solves(n32, n64, tile, graph):
+    """Batches of both precisions whose solves fit beside each other (the parts
+    overlap) or not (one after the other), two frames in a row: the bits of
+    single solves."""
+    from paper_1603_08161_amd import Batch
+    sizes = [n32] * 3 + [n64] * 2
+    precs = ["fp32"] * 3 + ["fp64"] * 2
+    scenes = [make_batch_lattice(900 + k, n, 1500, 20, num_levels=1, gn=2, pcg=6)
+              for k, n in enumerate(sizes)]
+    kw = dict(tiles=(tile,), graph=graph)
+    lats = [make_lattice(s, precision=p, **kw) for s, p in zip(scenes, precs)]
+    batch = Batch(lats)
+    for frame in range(2):
+        E = batch.solve(reset=True, energies=True)
+    for s, p, lat, e in zip(scenes, precs, lats, E):
+        ref = make_lattice(s, precision=p, tiles=(tile,))
+        rep = ref.solve_frame(reset=True, report=True)
+        np.testing.assert_array_equal(e, rep["energy"])
+        np.testing.assert_array_equal(lat.get_state64()[0], ref.get_state64()[0])
