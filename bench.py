@@ -54,12 +54,12 @@ def kernel_source_sha() -> str:
     return h.hexdigest()[:16]
 
 
-def measured_traffic(key: str, name: str = "traffic_k_cg_frame64.md"):
-    """HBM bytes per launch of a CG-iteration kernel from a committed
-    rocprofv3 counter summary (FETCH_SIZE + WRITE_SIZE, scaled by the same
-    counters on a plain copy), e.g. key "tile7" for the 64^3 kernel with
-    stencil tile 7; None if the summary is missing, has no such entry, or the
-    kernel's sources changed since the counters were taken."""
+def measured_traffic(key: str, name: str = "traffic_k_cg_loop.md"):
+    """Bytes per launch of a CG kernel between its caches and memory, from a
+    committed rocprofv3 counter summary (FETCH_SIZE + WRITE_SIZE, scaled by the
+    same counters on a plain copy), e.g. key "frame64_tile6" for a solve of the
+    64^3 level with tile 6; None if the summary is missing, has no such entry,
+    or the kernel's sources changed since the counters were taken."""
     path = os.path.join(ROOT, "profiles", name)
     if not os.path.exists(path):
         return None
@@ -220,7 +220,10 @@ def main() -> int:
     prof_us = rep["prof_us"]
     n_fine = spec.dims[0] * spec.dims[1] * spec.dims[2]
     nbytes = cg_iteration_bytes(n_fine, scene.n_dense, scene.n_sparse)
-    achieved = nbytes / (cg_a_us * 1e-6) / 1e9
+    # counted bytes of a solve (one launch of all its iterations)
+    pcg = spec.pcg_iters[-1]
+    traffic = measured_traffic(f"frame64_tile{tiles[-1]}")
+    achieved = None if traffic is None else traffic / pcg / (cg_a_us * 1e-6) / 1e9
     print(f"# 64^3 CG iteration in the timed graph: {cg_a_us:.2f} us mean over "
           f"{graph_n['cg_a']} launches; eager finest-level kernel means (us): "
           + ", ".join(f"{k}={v:.2f}" for k, v in prof_us.items()), flush=True)
@@ -302,21 +305,25 @@ def main() -> int:
         "energy_oracle": e_ref,
         "max_rel_energy_err": max_rel,
         "roofline": {
-            "bound": "hbm",
+            "bound": "latency",
             "kernel": "one CG iteration of the one-launch solve (k_cg_loop<float>) on the 64^3 level",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS,
-            "traffic": measured_traffic(f"tile{tiles[-1]}"),
-            "bytes_per_launch": nbytes,
+            "frac": None if achieved is None else achieved / HBM_PEAK_GBS,
+            "traffic": traffic,
+            "traffic_iterations": pcg,
             "mean_us": cg_a_us,
+            "streamed_model_bytes": nbytes,
             "timing": "device clock stamps captured in the frame graph around the 64^3 "
                       "level's CG iterations 1..19 of each flip-flop iteration, last timed "
-                      "replay (rocprofv3 kernel-trace mean in profiles/k_cg_frame64.md)",
-            "note": "bytes of an iteration that streams every vector, over its time: the solve "
-                    "keeps the vectors in registers and LDS instead and moves only the halo "
-                    "exchange and the data rows that do not fit, so this is no HBM traffic",
+                      "replay (rocprofv3 kernel trace in profiles/frame64_trace.md)",
+            "note": "achieved: counted bytes of a solve (profiles/traffic_k_cg_loop.md), most of "
+                    "which the last-level cache serves, per iteration over its time; null when "
+                    "the sources changed since or the tile has no entry.  The solve keeps its "
+                    "vectors in registers and LDS, so it moves a fraction of "
+                    "streamed_model_bytes, those of an iteration that streams every vector, and "
+                    "is bound by the exchange between workgroups and by instruction issue",
         },
         "kernel_mean_us_eager": prof_us,
         "set_constraints_ms": set_constraints_ms,
@@ -333,8 +340,7 @@ def active_set_leg(args, scene, inputs):
     """The same 64^3 frame restricted to the optimised set M of Sec. 6-7
     (isosurface points plus their one-ring, VD_FLAG_ACTIVE_SET): frames/s of
     the same timed step, its own autotuned tiles, the oracle gate against the
-    restricted FP64 solve, and the CG iteration's time and model bytes
-    (144 B per point of M + 24 B per dense and 12 B per sparse sample)."""
+    restricted FP64 solve, and the CG iteration's time."""
     import numpy as np
     import torch
 
@@ -362,7 +368,6 @@ def active_set_leg(args, scene, inputs):
     elapsed = time.perf_counter() - t0
     graph_us, _ = lat.profile()
     cg_us = float(graph_us["cg_a"])
-    nbytes = 144.0 * n_act + 24.0 * scene.n_dense + 12.0 * scene.n_sparse
     e_ref = None
     solved = args.steps
     rel = None
@@ -382,8 +387,7 @@ def active_set_leg(args, scene, inputs):
             args.steps, "solved_frames": solved, "active_points": n_act,
             "energy_gpu": float(energies[-1][0]), "energy_oracle": e_ref,
             "max_rel_energy_err": None if rel is None else float(rel.max()),
-            "tiles": tiles, "cg_iteration_us": cg_us, "cg_model_bytes": nbytes,
-            "cg_effective_GBs": nbytes / (cg_us * 1e-6) / 1e9}
+            "tiles": tiles, "cg_iteration_us": cg_us}
 
 
 def tracked_frame_leg(args, tiles, rigid_iters: int = 2, icp_iters: int = 2):
@@ -533,9 +537,12 @@ def bench_batch(args) -> int:
         loop_us = prof_us.get("cg_loop", 0.0) / scenes[f32[0]].spec.pcg_iters[-1]
         cg.append(prof_us.get("cg_a", loop_us))
     cg_us = float(np.mean(cg))
+    loop = "cg_loop" in prof_us
     nbytes = sum(cg_iteration_bytes(n_nodes[k], scenes[k].n_dense, scenes[k].n_sparse)
                  for k in f32)
-    achieved = nbytes / (cg_us * 1e-6) / 1e9
+    iters = scenes[f32[0]].spec.pcg_iters[-1] if loop else 1  # per launch
+    traffic = measured_traffic(f"batch_f32_{'loop_' if loop else ''}tile{batch_tiles['fp32'][-1]}")
+    achieved = None if traffic is None else traffic / iters / (cg_us * 1e-6) / 1e9
     print("# finest-level kernel means (us): "
           + ", ".join(f"{k}={v:.2f}" for k, v in prof_us.items()), flush=True)
 
@@ -594,20 +601,24 @@ def bench_batch(args) -> int:
                    "finest_nodes": sum(n_nodes),
                    "n_dense": sum(s.n_dense for s in scenes),
                    "precision": precs,
-                   "launch": "one launch per schedule step (a CG solve is one) over the "
-                             "lattices of each precision, hipGraph; one part after the other",
+                   "launch": "one launch per schedule step over the lattices of each precision "
+                             "(a CG solve, or an iteration of it, by the tuner's timings), "
+                             "hipGraph",
                    "tiles": batch_tiles},
         "oracle_gate": gate,
-        "roofline": {"bound": "hbm", "kernel": "batched CG iteration (k_cg_loop<float>) "
-                                               "on the finest level of the float32 lattices",
+        "roofline": {"bound": "latency" if loop else "hbm",
+                     "kernel": f"batched CG iteration ({'k_cg_loop' if loop else 'k_cg'}<float>) "
+                               "on the finest level of the float32 lattices",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": measured_traffic(f"batch_f32_tile{batch_tiles['fp32'][-1]}",
-                                                 "traffic_k_cg_batch32.md"),
-                     "bytes_per_launch": nbytes, "mean_us": cg_us,
+                     "frac": None if achieved is None else achieved / HBM_PEAK_GBS,
+                     "traffic": traffic, "traffic_iterations": iters, "mean_us": cg_us,
+                     "streamed_model_bytes": nbytes,
                      "timing": "profiled eager batch of the float32 lattices, stream events "
-                               "around each launch (rocprofv3 kernel-trace mean in "
-                               "profiles/traffic_k_cg_batch32.md)"},
+                               "around each launch (rocprofv3 kernel trace in "
+                               "profiles/batch32_trace.md)",
+                     "note": "achieved: counted bytes (profiles/traffic_k_cg_loop.md) over the "
+                             "time of an iteration; null when the sources changed since or the "
+                             "tile has no entry"},
         "kernel_mean_us": prof_us,
     }
     print(json.dumps(line), flush=True)

@@ -554,3 +554,19 @@ def test_solves_of_many_iterations_on_two_streams_equal_launches_per_iteration()
     torch.cuda.synchronize()
     for lat, ref in zip(lats, refs):
         np.testing.assert_array_equal(lat.get_state64()[0], ref)
+
+
+@pytest.mark.parametrize("tile", [4, 6, 7, 8])
+def test_one_launch_solves_of_tiles_full_of_data_nodes(tile):
+    """A lattice whose every node carries data blocks (20-40 tiles): the bits of
+    one launch per iteration."""
+    scene = make_tiny(seed=13, dims=(24, 20, 16), num_levels=1, gn=2, pcg=8, n_dense=20000,
+                      n_sparse=40, spacing=0.5, origin=(0.3, 0.1, -0.2))
+    out = {}
+    for iterative in (True, False):
+        lat = make_lattice(scene, tiles=(tile,), iterative=iterative)
+        rep = lat.solve_frame(report=True)
+        assert not rep["bits"] & 16
+        out[iterative] = (rep["energy"], lat.get_state64()[0])
+    np.testing.assert_array_equal(out[False][0], out[True][0])
+    np.testing.assert_array_equal(out[False][1], out[True][1])
