@@ -275,7 +275,8 @@ int vd_solve_frame(vd_lattice* l, const vd_solve_opts* opts, vd_solve_report* re
  * the handles: they must outlive it.  Creating it sets every handle's stencil
  * tile, per level, to the tile of the largest lattice of its part at that
  * level if that was chosen (vd_lattice_desc.tile, vd_tune, another batch), else
- * to one that suits the launches over all of them.
+ * to one that suits the launches over all of them.  A solve of the batch sets
+ * them again where a handle has got others since.
  * VD_EINVAL on mismatched handles. */
 int vd_batch_create(vd_lattice* const* lattices, int32_t n, vd_batch** out);
 

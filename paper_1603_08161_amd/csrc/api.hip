@@ -1776,9 +1776,9 @@ class Batch final : public IBatch {
       int big = 0;
       for (int b = 1; b < n_; ++b)
         if (h_[b]->level_nodes(l) > h_[big]->level_nodes(l)) big = b;
-      const int kind = h_[big]->desc().tile[l] > 0 ? h_[big]->level_tile(l) : default_kind(l);
-      for (int b = 0; b < n_; ++b) h_[b]->force_tile(l, kind);
+      kinds_[l] = h_[big]->desc().tile[l] > 0 ? h_[big]->level_tile(l) : default_kind(l);
     }
+    set_tiles();
     tables_.resize(L_);
     for (int l = 0; l < L_; ++l) {
       VD_CHECK(pool_.alloc(&tables_[l].views, (size_t)n_));
@@ -1792,7 +1792,7 @@ class Batch final : public IBatch {
     if (stale()) set_loops();
     double share = 0.0;
     for (int l = 0; l < L_; ++l) {
-      const int kind = h_[0]->level_tile(l);
+      const int kind = kinds_[l];
       for (const auto* h : h_)
         if (loops_[l]) share = std::max(share, (double)h->level_tiles(l, kind) / loop_cap_[kind]);
     }
@@ -1805,6 +1805,7 @@ class Batch final : public IBatch {
       if (!h->has_constraints()) return VD_ESTATE;
     const int reset = (o && o->reset_to_rest) ? 1 : 0;
     if (stale()) {
+      set_tiles();
       VD_CHECK(build_tables());
       for (auto& g : exec_)
         if (g) {
@@ -1858,6 +1859,13 @@ class Batch final : public IBatch {
     return false;
   }
 
+  // The batch's tiles on every handle: a launch has one tile kind, and a handle
+  // may have got another since (vd_tune, another batch).
+  void set_tiles() {
+    for (int l = 0; l < L_; ++l)
+      for (auto* h : h_) h->force_tile(l, kinds_[l]);
+  }
+
   // A lattice of a one-launch solve waits until all its tiles are resident, and
   // tiles become resident in launch order: groups that fill the GPU (first fit,
   // largest first) leave the fewest compute units waiting for an earlier
@@ -1909,7 +1917,7 @@ class Batch final : public IBatch {
   void set_loops() {
     loops_.assign(L_, 0);
     for (int l = 0; l < L_; ++l) {
-      const int kind = h_[0]->level_tile(l), rounds = (int)groups_of(l, kind).size();
+      const int kind = kinds_[l], rounds = (int)groups_of(l, kind).size();
       if (rounds == 0) continue;
       loops_[l] = tuned_[l].kind == kind ? tuned_[l].loop
                                          : rounds == 1 || loop_us(l, kind, rounds) < iter_us(l);
@@ -1942,7 +1950,7 @@ class Batch final : public IBatch {
     std::vector<int> order;
     const int F = L_ - 1;
     if (loops_[F]) {
-      for (const auto& g : groups_of(F, h_[0]->level_tile(F)))
+      for (const auto& g : groups_of(F, kinds_[F]))
         order.insert(order.end(), g.begin(), g.end());
     } else {
       for (int b = 0; b < n_; ++b) order.push_back(b);
@@ -2024,7 +2032,7 @@ class Batch final : public IBatch {
         return VD_OK;
       };
       double best = 1e300;
-      int best_kind = h_[0]->level_tile(l);
+      int best_kind = kinds_[l];
       bool best_loop = false;
       int timed = -1;  // the kind that us_out was last written for
       for (int t = 0; t < 2 * kTileKinds && rc == VD_OK; ++t) {
@@ -2035,7 +2043,8 @@ class Batch final : public IBatch {
         const double as_loop = rounds > 1 ? loop_us(l, kind, rounds) : 0.0;
         if (loop ? rounds == 0 || as_loop > 1.5 * iter_us(l)
                  : rounds > 0 && iter_us(l) > 1.5 * as_loop) continue;
-        for (auto* h : h_) h->force_tile(l, kind);
+        kinds_[l] = kind;
+        set_tiles();
         tuned_[l].kind = kind;
         tuned_[l].loop = loop;
         rc = build_tables();
@@ -2064,7 +2073,8 @@ class Batch final : public IBatch {
           best_loop = loop;
         }
       }
-      for (auto* h : h_) h->force_tile(l, best_kind);
+      kinds_[l] = best_kind;
+      set_tiles();
       tuned_[l].kind = best_kind;
       tuned_[l].loop = best_loop;
       if (tile_out) tile_out[l] = best_kind + 1;
@@ -2139,6 +2149,7 @@ class Batch final : public IBatch {
   bool graph_ = false;
   hipGraphExec_t exec_[2] = {nullptr, nullptr};
   bool prof_ = false;
+  int kinds_[VD_MAX_LEVELS] = {};  // the tile kind of each level
   bool masked_ = false;            // some lattice has an optimised set
   int loop_cap_[kTileKinds] = {};  // most tiles of a lattice's one-launch CG solve
   std::vector<char> loops_;        // per level: its CG solves are one launch

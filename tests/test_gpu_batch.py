@@ -228,3 +228,32 @@ def test_parts_of_one_launch_solves(n32, n64, tile, graph):
         rep = ref.solve_frame(reset=True, report=True)
         np.testing.assert_array_equal(e, rep["energy"])
         np.testing.assert_array_equal(lat.get_state64()[0], ref.get_state64()[0])
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_batches_that_share_lattices_keep_their_tiles(graph):
+    """A handle's tiles change under a batch: another batch takes it with other
+    tiles, its own tuner runs.  Every solve of the batches has the bits of
+    single solves with the batch's tiles."""
+    from paper_1603_08161_amd import Batch
+    scenes = [make_batch_lattice(950 + k, n, 1500, 20, num_levels=1, gn=2, pcg=6)
+              for k, n in enumerate([33, 21, 30, 48])]
+    kw = dict(precision="fp64", graph=graph)
+    lats = [make_lattice(s, tiles=(t,), **kw) for s, t in zip(scenes, (2, 5, 5, 7))]
+    first, second = Batch(lats[:3]), Batch(lats[1:])
+
+    def check(batch, members, tile):
+        E = batch.solve(reset=True, energies=True)
+        for k, e in zip(members, E):
+            ref = make_lattice(scenes[k], tiles=(tile,), precision="fp64")
+            rep = ref.solve_frame(reset=True, report=True)
+            np.testing.assert_array_equal(e, rep["energy"])
+            np.testing.assert_array_equal(lats[k].get_state64()[0], ref.get_state64()[0])
+
+    check(first, (0, 1, 2), 2)
+    check(second, (1, 2, 3), 7)
+    check(first, (0, 1, 2), 2)
+    lats[0].tune(iters=2)
+    lats[2].tune(iters=2)
+    check(first, (0, 1, 2), 2)
+    check(second, (1, 2, 3), 7)
